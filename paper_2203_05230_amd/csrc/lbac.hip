@@ -60,6 +60,7 @@ void release(lbac_ctx* h) {
     dev_free(h, h->vtab);
     dev_free(h, h->vtabf);
     dev_free(h, h->t_dev);
+    dev_free(h, h->tfac);
     dev_free(h, h->rows);
     dev_free(h, h->red5);
     dev_free(h, h->dtmp);
@@ -149,11 +150,17 @@ StepArgs lbac_host::make_args(const lbac_ctx* h, int src, int32_t k) {
     a.vtab = h->vtab;
     a.vtabf = h->vtabf;
     a.t_dev = h->t_dev;
+    a.tfac = h->tfac;
     a.k = k;
     a.period_T = time_period(h->p);
     a.eps = h->p.eps;
     a.tau = h->p.tau;
     a.delta = h->p.delta;
+    a.psi_scale = a.eps * 0.69314718055994530942;
+    a.s_scale = 1.0 / (a.eps * (1.0 + 2.0 * a.delta) * (1.0 + 2.0 * a.delta));
+    a.omega = 1.0 / a.tau;
+    a.kforce = 1.0 - 0.5 / a.tau;
+    a.keep = 1.0 - 1.0 / a.tau;
     a.cl_w = h->cl_w;
     a.cl_b = h->cl_b;
     a.cl_theta = h->cl_theta;
@@ -369,23 +376,34 @@ hipError_t launch_stepS(const lbac_ctx* h, int src, int32_t k, int S) {
     }
 }
 
-// Queues `n` steps starting at offset k0 of the current run from pop[src]:
-// S steps per launch where the variant allows, single steps for the rest.
-// *flips gets the number of launches (buffer swaps).
-hipError_t launch_steps(const lbac_ctx* h, int src, int64_t k0, int64_t n, int64_t* flips) {
+void launch_set_time(const lbac_ctx* h, int64_t t) {
+    hipLaunchKernelGGL(set_time_kernel, dim3(1), dim3(kTimeThreads), 0, h->stream, h->t_dev, h->tfac,
+                       time_period(h->p), t);
+}
+
+// Queues `n` steps from pop[src], S steps per launch where the variant
+// allows and single steps for the rest, and the advance of the step counter.
+// The counter (and the table of time factors with it) moves after every
+// kTimeFactors steps at the latest.  *flips gets the number of launches
+// (buffer swaps).
+hipError_t launch_steps(const lbac_ctx* h, int src, int64_t n, int64_t* flips) {
     int64_t f = 0;
     hipError_t e = hipSuccess;
     const int S = launch_steps_of(h);
-    for (int64_t k = 0; k < n && e == hipSuccess;) {
+    int32_t k = 0;  // steps queued since the counter moved
+    for (int64_t left = n; left > 0 && e == hipSuccess;) {
         const int cur = src ^ (int)(f & 1);
-        if (S > 1 && n - k >= S) {
-            e = launch_stepS(h, cur, (int32_t)(k0 + k), S);
-            k += S;
-        } else {
-            e = launch_step(h, cur, (int32_t)(k0 + k));
-            k += 1;
-        }
+        const int s = S > 1 && left >= S ? S : 1;
+        e = s > 1 ? launch_stepS(h, cur, k, s) : launch_step(h, cur, k);
+        k += s;
+        left -= s;
         ++f;
+        if (e == hipSuccess && (left == 0 || k + std::min<int64_t>(S, left) > kTimeFactors)) {
+            hipLaunchKernelGGL(advance_kernel, dim3(1), dim3(kTimeThreads), 0, h->stream, h->t_dev, h->tfac,
+                               time_period(h->p), (int64_t)k);
+            e = hipGetLastError();
+            k = 0;
+        }
     }
     *flips = f;
     return e;
@@ -526,10 +544,11 @@ int lbac_host::create(const lbac_params* p, const double* phi0, bool phi0_on_dev
     h->vtabf = (float*)dev_alloc(h, tab.size() * sizeof(float));
     std::vector<float> tabf(tab.begin(), tab.end());
     h->t_dev = (int64_t*)dev_alloc(h, 64);
+    h->tfac = (double*)dev_alloc(h, (kTimeFactors + 1) * sizeof(double));
     h->rows = dev_alloc(h, 10 * sizeof(double) * (size_t)p->ny);  // five compensated pairs per row
     h->red5 = (double*)dev_alloc(h, 64);
     h->dtmp = (double*)dev_alloc(h, n * sizeof(double));
-    if (!h->vtab || !h->vtabf || !h->t_dev || !h->rows || !h->red5 || !h->dtmp) return bail(LBAC_ENOMEM);
+    if (!h->vtab || !h->vtabf || !h->t_dev || !h->tfac || !h->rows || !h->red5 || !h->dtmp) return bail(LBAC_ENOMEM);
     if (hipHostMalloc((void**)&h->host5, 8 * sizeof(double), hipHostMallocDefault) != hipSuccess) {
         h->host5 = nullptr;
         return bail(LBAC_ENOMEM);
@@ -545,7 +564,7 @@ int lbac_host::create(const lbac_params* p, const double* phi0, bool phi0_on_dev
             return bail(LBAC_EDEVICE);
         src0 = h->dtmp;
     }
-    hipLaunchKernelGGL(set_time_kernel, dim3(1), dim3(64), 0, h->stream, h->t_dev, (int64_t)0);
+    launch_set_time(h, 0);
     StepArgs a = make_args(h, 1, 0);  // dst = pop[0]
     if (launch_aux(h, 0, a, nullptr, nullptr, src0) != hipSuccess) return bail(LBAC_EDEVICE);
     if (hipStreamSynchronize(h->stream) != hipSuccess) return bail(LBAC_EDEVICE);
@@ -572,11 +591,7 @@ int capture_graph(lbac_ctx* h, int parity) {
     }
     HIPCHK(h, hipStreamBeginCapture(h->stream, hipStreamCaptureModeThreadLocal));
     int64_t flips = 0;
-    hipError_t e = launch_steps(h, parity, 0, h->graph_chunk, &flips);
-    if (e == hipSuccess) {
-        hipLaunchKernelGGL(advance_kernel, dim3(1), dim3(64), 0, h->stream, h->t_dev, (int64_t)h->graph_chunk);
-        e = hipGetLastError();
-    }
+    hipError_t e = launch_steps(h, parity, h->graph_chunk, &flips);
     hipGraph_t g = nullptr;
     hipError_t e2 = hipStreamEndCapture(h->stream, &g);
     if (e != hipSuccess || e2 != hipSuccess) {
@@ -656,9 +671,7 @@ int lbac_step(lbac_ctx* h, int64_t n) {
     const int64_t r = n - done;
     if (r > 0) {
         int64_t flips = 0;
-        HIPCHK(h, launch_steps(h, h->cur, 0, r, &flips));
-        hipLaunchKernelGGL(advance_kernel, dim3(1), dim3(64), 0, h->stream, h->t_dev, r);
-        HIPCHK(h, hipGetLastError());
+        HIPCHK(h, launch_steps(h, h->cur, r, &flips));
         h->cur ^= (int)(flips & 1);
         h->t += r;
     }
@@ -772,7 +785,7 @@ int lbac_set_state(lbac_ctx* h, const void* buf, size_t bytes) {
         HIPCHK(h, hipMemcpyAsync((char*)h->pop[h->cur] + (size_t)q * h->plane_stride * h->elem_bytes, d + q * plane,
                                  plane, hipMemcpyHostToDevice, h->stream));
     if (phib) HIPCHK(h, hipMemcpyAsync(h->phis[h->cur], d + h->nplanes * plane, phib, hipMemcpyHostToDevice, h->stream));
-    hipLaunchKernelGGL(set_time_kernel, dim3(1), dim3(64), 0, h->stream, h->t_dev, t);
+    launch_set_time(h, t);
     HIPCHK(h, hipGetLastError());
     HIPCHK(h, hipStreamSynchronize(h->stream));
     h->t = t;

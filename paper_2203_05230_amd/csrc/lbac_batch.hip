@@ -397,8 +397,7 @@ int capture(lbac_batch* b) {
     }
     launch_slots(1);
     if (e == hipSuccess) {
-        hipLaunchKernelGGL(batch_advance_kernel, dim3((count + 255) / 256), dim3(256), 0, b->stream, b->d_inst, count,
-                           b->d_ctl);
+        hipLaunchKernelGGL(batch_advance_kernel, dim3(count), dim3(kTimeThreads), 0, b->stream, b->d_inst, b->d_ctl);
         e = hipGetLastError();
     }
     hipGraph_t g = nullptr;

@@ -261,11 +261,16 @@ static __global__ void batch_reset_kernel(int32_t* done, int32_t nitems, BatchCt
     }
 }
 
-// Advances every instance's step counter by its step count (skipped on dry runs).
-static __global__ void batch_advance_kernel(const BatchInst* __restrict__ insts, int32_t count, const BatchCtl* ctl) {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k < count && ctl->dry == 0 && ctl->err == 0)
-        const_cast<int64_t*>(insts[2 * k].a.t_dev)[0] += insts[2 * k].nsteps;
+// Advances the step counter of instance blockIdx.x by its step count and
+// refills its time factors (skipped on dry runs).
+static __global__ __launch_bounds__(kTimeThreads) void batch_advance_kernel(const BatchInst* __restrict__ insts,
+                                                                            const BatchCtl* ctl) {
+    const BatchInst& b = insts[2 * blockIdx.x];
+    if (ctl->dry != 0 || ctl->err != 0) return;
+    int64_t* t_dev = const_cast<int64_t*>(b.a.t_dev);
+    const int64_t t = t_dev[0] + b.nsteps;
+    __syncthreads();  // every thread has read the counter
+    fill_factors(t_dev, const_cast<double*>(b.a.tfac), b.a.period_T, t);
 }
 
 }  // namespace lbac

@@ -47,6 +47,7 @@ struct lbac_ctx {
     double* vtab = nullptr;
     float* vtabf = nullptr;  // vtab rounded to FP32
     int64_t* t_dev = nullptr;
+    double* tfac = nullptr;  // time factors from t_dev on (kTimeFactors + 1 values)
     void* rows = nullptr;    // per-row partial sums (working precision)
     double* red5 = nullptr;
     double* dtmp = nullptr;  // ny*nx doubles (phi0 upload, phi output, reference field)

@@ -67,9 +67,14 @@ struct StepArgs {
     const double* vtab;     // Ax[nx], Bx[nx], Ay[ny], By[ny]: u = s(t) Ax Ay, v = s(t) Bx By
     const float* vtabf;     // the same table rounded to FP32
     const int64_t* t_dev;   // step count at the start of this launch sequence
+    const double* tfac;     // s(t_dev[0] - 1 + j), j = 0 .. kTimeFactors (see fill_factors)
     int32_t k;              // this launch is step t_dev[0] + k
     double period_T;        // s(t) = cos(pi t / period_T) when > 0, else 1
     double eps, tau, delta;
+    // constants of the update, formed once on the host (IEEE double, as the device would)
+    double psi_scale;       // eps ln 2: psi = eps ln2 (log2 a - log2 b)
+    double s_scale;         // 1 / (eps (1 + 2 delta)^2)
+    double omega, kforce, keep;  // 1 / tau, 1 - 1 / (2 tau), 1 - 1 / tau
     int32_t nbx, nby;       // tiles of the step launch (columns blocks x strips)
     int32_t n_xcd;          // XCDs the workgroups are dispatched over
     const uint16_t* cl_w;   // learned closure: packed BF16 weights (ClosurePack layout), or null
@@ -260,23 +265,43 @@ __device__ __forceinline__ float row_factor(const float* vtabf, int64_t i) {
     return ((const __attribute__((address_space(4))) float*)vtabf)[i];
 }
 
+// Steps one fill of the time-factor table serves.
+constexpr int kTimeFactors = 256;
+
 // Per-step constants of the update.
 template <typename R>
 struct NodeConst {
     R eps, delta, psi_scale, s_scale, omega, kforce, keep, s_now, s_old;
     bool first;
     __device__ __forceinline__ NodeConst() {}
-    __device__ __forceinline__ NodeConst(const StepArgs& a, int64_t t) {
-        first = (t == 0);
-        s_now = R(time_factor(a.period_T, t));
-        s_old = first ? s_now : R(time_factor(a.period_T, t - 1));
+    // step t_dev[0] + a.k + j of a launch sequence: the time factors from the
+    // table, as scalar loads (an FP64 cosine per step, lane and launch had
+    // been 2 to 3 us of every launch's start)
+    __device__ __forceinline__ NodeConst(const StepArgs& a, int j) {
+        typedef const __attribute__((address_space(4))) double* D4;
+        typedef const __attribute__((address_space(4))) int64_t* I4;
+        first = ((I4)a.t_dev)[0] + a.k + j == 0;
+        s_now = R(((D4)a.tfac)[a.k + j + 1]);
+        s_old = R(((D4)a.tfac)[a.k + j + (first ? 1 : 0)]);
+        common(a);
+    }
+    // any time t (the batched form, whose instances run any number of steps in one launch)
+    __device__ __forceinline__ static NodeConst at(const StepArgs& a, int64_t t) {
+        NodeConst c;
+        c.first = (t == 0);
+        c.s_now = R(time_factor(a.period_T, t));
+        c.s_old = c.first ? c.s_now : R(time_factor(a.period_T, t - 1));
+        c.common(a);
+        return c;
+    }
+    __device__ __forceinline__ void common(const StepArgs& a) {
         eps = R(a.eps);
         delta = R(a.delta);
-        psi_scale = R(a.eps * 0.69314718055994530942);  // eps ln 2: psi = eps ln2 (log2 a - log2 b)
-        s_scale = R(1.0 / (a.eps * (1.0 + 2.0 * a.delta) * (1.0 + 2.0 * a.delta)));
-        omega = R(1.0 / a.tau);
-        kforce = R(1.0 - 0.5 / a.tau);
-        keep = R(1.0 - 1.0 / a.tau);
+        psi_scale = R(a.psi_scale);
+        s_scale = R(a.s_scale);
+        omega = R(a.omega);
+        kforce = R(a.kforce);
+        keep = R(a.keep);
     }
 };
 
@@ -598,7 +623,7 @@ __host__ __device__ constexpr int block_threads() {
     return BX + 64;
 }
 
-// One step on the tile of column block `bxi` and strip `syi` at time t.  The
+// One step on the tile of column block `bxi` and strip `syi`.  The
 // strip is marched upward, or downward when `down` is set (the kernel flips
 // odd strips so that two strips sharing a boundary read its halo rows at
 // about the same time, while they are still in cache).
@@ -610,7 +635,7 @@ __host__ __device__ constexpr int block_threads() {
 // the memory operations in flight exactly and keeps PF rows of loads
 // outstanding across the row's arithmetic.
 template <typename R, int ST, int MODEL, int BX, int PF>
-__device__ __forceinline__ void step_tile_lds(const StepArgs& a, int bxi, int syi, int64_t t, bool down,
+__device__ __forceinline__ void step_tile_lds(const StepArgs& a, int bxi, int syi, bool down,
                                               TileLds<R, BX>& lds) {
     auto& ring = lds.ring;
     auto& sring = lds.sring;
@@ -645,7 +670,7 @@ __device__ __forceinline__ void step_tile_lds(const StepArgs& a, int bxi, int sy
     const Io<R, ST> io(a);
     lds_barrier();  // the LDS may still be read by a previous tile of this block
 
-    const NodeConst<R> kc(a, t);
+    const NodeConst<R> kc(a, 0);
     const R Axl = act ? R(a.vtab[x]) : R(0);
     const R Bxl = act ? R(a.vtab[a.nx + x]) : R(0);
 
@@ -780,7 +805,7 @@ __global__ __launch_bounds__(block_threads<BX>()) void step_kernel_lds(StepArgs 
     const int per = ntile / a.n_xcd, extra = ntile % a.n_xcd;
     const int tile = xcd * per + min(xcd, extra) + k;
     const int bxi = tile % a.nbx, syi = tile / a.nbx;
-    step_tile_lds<R, ST, MODEL, BX, PF>(a, bxi, syi, a.t_dev[0] + a.k, (syi & 1) != 0, lds);
+    step_tile_lds<R, ST, MODEL, BX, PF>(a, bxi, syi, (syi & 1) != 0, lds);
 }
 
 // ---- learned closure: BF16 MFMA inference ------------------------------------
@@ -1087,8 +1112,8 @@ __host__ __device__ constexpr int stepS_threads() {
 }
 
 // COH: storage read and written with device-scope accesses (IoCoherent,
-// IoCoherentShifted: the batched form).  CL: the
-// learned closure (FP32 plain storage).
+// IoCoherentShifted: the batched form, at time t; else t is not used).  CL:
+// the learned closure (FP32 plain storage).
 template <int MODEL, int BX, int S, int ST, bool COH = false, bool CL = false>
 __device__ __forceinline__ void stepS_tile_lds(const StepArgs& a, int x0, int w, int ys, int hh, int64_t t,
                                                bool down, TileSLds<BX, S, CL>& lds) {
@@ -1159,9 +1184,12 @@ __device__ __forceinline__ void stepS_tile_lds(const StepArgs& a, int x0, int w,
     // one-step kernels round it on the device
     const float Ax = a.vtabf[gcol];
     const float Bx = down ? -a.vtabf[a.nx + gcol] : a.vtabf[a.nx + gcol];
-    NodeConst<float> kcs[S];  // stage k at time t + k
+    NodeConst<float> kcs[S];  // stage k, step k of the launch (the batched form: time t + k)
 #pragma unroll
-    for (int k = 0; k < S; ++k) kcs[k] = NodeConst<float>(a, t + k);
+    for (int k = 0; k < S; ++k) {
+        if constexpr (COH) kcs[k] = NodeConst<float>::at(a, t + k);
+        else kcs[k] = NodeConst<float>(a, k);
+    }
     // pulled populations and phi of stage k, ping-pong by iteration parity:
     // the pull of iteration it fills half it & 1, the update of iteration
     // it + UL reads it (with UL = 2 through fh, which keeps the pull of two
@@ -1430,8 +1458,7 @@ __global__ __launch_bounds__((stepS_threads<BX, S>())) void stepS_kernel_lds(Ste
     const int tile = xcd_tile(blockIdx.x, ntile, a.n_xcd);
     const int bxi = tile % a.nbx, syi = tile / a.nbx;
     const int x0 = bxi * BX, ys = syi * a.strip_h;
-    stepS_tile_lds<MODEL, BX, S, ST>(a, x0, min(BX, a.nx - x0), ys, min(a.strip_h, a.ny - ys), a.t_dev[0] + a.k,
-                                     (syi & 1) != 0, lds);
+    stepS_tile_lds<MODEL, BX, S, ST>(a, x0, min(BX, a.nx - x0), ys, min(a.strip_h, a.ny - ys), 0, (syi & 1) != 0, lds);
 }
 
 // The S-step kernel with the learned closure (FP32 storage, improved model).
@@ -1444,8 +1471,7 @@ stepS_kernel_cl(StepArgs a) {
     const int bxi = tile % a.nbx, syi = tile / a.nbx;
     const int x0 = bxi * BX, ys = syi * a.strip_h;
     stepS_tile_lds<MODEL_IMPROVED, BX, S, ST_PLAIN, false, true>(a, x0, min(BX, a.nx - x0), ys,
-                                                                 min(a.strip_h, a.ny - ys), a.t_dev[0] + a.k,
-                                                                 (syi & 1) != 0, lds);
+                                                                 min(a.strip_h, a.ny - ys), 0, (syi & 1) != 0, lds);
 }
 
 // ---------------------------------------------------------------------------
@@ -1503,7 +1529,7 @@ struct WaveGeom {
 };
 
 template <typename R, int ST, int MODEL, int DIR>
-__device__ __forceinline__ void step_wave_dir(const StepArgs& a, int bxi, int syi, int64_t t) {
+__device__ __forceinline__ void step_wave_dir(const StepArgs& a, int bxi, int syi) {
     using G = WaveGeom;
     constexpr int D = G::kDelay;
     const int l = threadIdx.x % kWave;
@@ -1516,7 +1542,7 @@ __device__ __forceinline__ void step_wave_dir(const StepArgs& a, int bxi, int sy
     const int x = x0 - G::kHalo + l;                     // column this lane updates (upd_lane)
     const Io<R, ST> io(a);
 
-    const NodeConst<R> kc(a, t);
+    const NodeConst<R> kc(a, 0);
     const R Axl = upd_lane ? R(a.vtab[x]) : R(0);
     const R Bxl = upd_lane ? R(a.vtab[a.nx + x]) : R(0);
 
@@ -1614,15 +1640,15 @@ __device__ __forceinline__ void step_wave_dir(const StepArgs& a, int bxi, int sy
 }
 
 // One step on the tile of column block `bxi` and strip `syi` (a.strip_h rows)
-// at time t, by the calling wavefront.  Odd strips march downward so that
+// by the calling wavefront.  Odd strips march downward so that
 // two strips sharing a boundary read its halo rows at about the same time,
 // while they are still in cache.
 template <typename R, int ST, int MODEL>
-__device__ __forceinline__ void step_wave(const StepArgs& a, int bxi, int syi, int64_t t) {
+__device__ __forceinline__ void step_wave(const StepArgs& a, int bxi, int syi) {
     if (syi & 1)
-        step_wave_dir<R, ST, MODEL, -1>(a, bxi, syi, t);
+        step_wave_dir<R, ST, MODEL, -1>(a, bxi, syi);
     else
-        step_wave_dir<R, ST, MODEL, 1>(a, bxi, syi, t);
+        step_wave_dir<R, ST, MODEL, 1>(a, bxi, syi);
 }
 
 
@@ -1634,7 +1660,7 @@ __global__ __launch_bounds__(WPB * kWave) void step_kernel(StepArgs a) {
     const int tile = xcd_tile(blockIdx.x, nbb * a.nby, a.n_xcd);
     const int bxi = (tile % nbb) * WPB + (int)(threadIdx.x / kWave), syi = tile / nbb;
     if (bxi >= a.nbx) return;  // whole wavefront idle
-    step_wave<R, ST, MODEL>(a, bxi, syi, a.t_dev[0] + a.k);
+    step_wave<R, ST, MODEL>(a, bxi, syi);
 }
 
 // ---- learned closure: band list and correction pass -------------------------
@@ -1916,12 +1942,25 @@ __global__ __launch_bounds__(kRedThreads) void reduce_rows_kernel(const R* __res
     }
 }
 
-static __global__ void advance_kernel(int64_t* t_dev, int64_t n) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) t_dev[0] += n;
+// The step counter and the time factors of the next kTimeFactors steps from
+// it, tfac[j] = s(t - 1 + j), by one block of kTimeThreads threads.
+constexpr int kTimeThreads = 320;
+static_assert(kTimeThreads > kTimeFactors, "one factor per thread");
+__device__ __forceinline__ void fill_factors(int64_t* t_dev, double* tfac, double period, int64_t t) {
+    if (threadIdx.x == 0) t_dev[0] = t;
+    if (threadIdx.x <= kTimeFactors) tfac[threadIdx.x] = time_factor(period, t - 1 + (int64_t)threadIdx.x);
 }
 
-static __global__ void set_time_kernel(int64_t* t_dev, int64_t t) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) t_dev[0] = t;
+static __global__ __launch_bounds__(kTimeThreads) void advance_kernel(int64_t* t_dev, double* tfac, double period,
+                                                                      int64_t n) {
+    const int64_t t = t_dev[0] + n;
+    __syncthreads();  // every thread has read the counter
+    fill_factors(t_dev, tfac, period, t);
+}
+
+static __global__ __launch_bounds__(kTimeThreads) void set_time_kernel(int64_t* t_dev, double* tfac, double period,
+                                                                       int64_t t) {
+    fill_factors(t_dev, tfac, period, t);
 }
 
 // Copy of the stored state with the step kernel's tiling and access order
