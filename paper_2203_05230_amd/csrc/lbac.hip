@@ -12,6 +12,7 @@
 #include <vector>
 
 #include "lbac_internal.hpp"
+#include "lbac_patch.hpp"
 
 using namespace lbac;
 using namespace lbac_host;
@@ -135,6 +136,10 @@ double time_period(const lbac_params& p) {
 }
 
 }  // namespace
+
+float lbac_host::state_bytes(const lbac_ctx* h) {
+    return (float)(h->nplanes * h->elem_bytes + (h->storage == ST_PLAIN ? 0 : 4));
+}
 
 StepArgs lbac_host::make_args(const lbac_ctx* h, int src, int32_t k) {
     StepArgs a{};
@@ -279,6 +284,9 @@ bool stepS_allowed(const lbac_ctx* h) {
     return !h->closure || h->p.model == LBAC_MODEL_IMPROVED;
 }
 
+// Tile width of the one-step kernels by default: full-width blocks when the grid allows.
+int default_bx(int nx) { return nx >= 256 ? 256 : (nx >= 128 ? 128 : 64); }
+
 // Steps one launch takes: S with the S-step variants, else 1.
 int launch_steps_of(const lbac_ctx* h) {
     if (!stepS_allowed(h)) return 1;
@@ -376,35 +384,105 @@ hipError_t launch_stepS(const lbac_ctx* h, int src, int32_t k, int S) {
     }
 }
 
+// One launch of a run: the patch kernels, an S-step launch or a one-step launch.
+struct Launch {
+    bool patch;
+    PatchPlan p;
+    int S;
+};
+
+// The default shape of the strip kernels, for grids the patch kernels leave to
+// them, and an estimate of its time per step in microseconds (as PatchPlan's).
+//
+// Three steps per launch (FP32 storage): 224 columns and the strip height
+// whose tiles fill whole rounds of the 768 workgroups the device keeps
+// resident best, ceil(tiles / 768) (strip + 14) rows: 28 rows at 2048^2, 48 at
+// 3001 x 2210, 40 at 8192^2 (29.8, 44.6 and 355 us per step; strips of 40 took
+// 37 and 46 on the first two, the best of 60 shapes 29.3 and 42.7).
+//
+// One step: strips of such a height that about 1024 tiles, four per CU, share
+// the device: 256-column tiles at 16-bit storage ran at 17.9, 27.0, 38.6, 74
+// and 155 us per step at 1024^2, 1536^2, 2048^2, 3001 x 2210 and 4096^2
+// (strips of 4, 12, 16, 24, 64), the best of 54 shapes to 2%, against 60 us
+// and more below 2048^2 at strips of 64.
+float default_strips(const lbac_ctx* h, bool three, int& variant, int& bx, int& strip_h) {
+    const int nx = h->p.nx, ny = h->p.ny;
+    const float mnodes = 1e-6f * (float)((int64_t)nx * ny);
+    if (three) {
+        variant = LBAC_KERNEL_FUSED3;
+        bx = 224;
+        const int64_t nbx = (nx + bx - 1) / bx;
+        int64_t best = INT64_MAX;
+        for (int sh = 24; sh <= 64; sh += 4) {
+            const int64_t c = (nbx * ((ny + sh - 1) / sh) + 767) / 768 * (sh + 14);
+            if (c < best) {
+                best = c;
+                strip_h = std::min(sh, ny);
+            }
+        }
+        return h->closure ? 120.f + 13.f * mnodes : 0.7f * (float)best;
+    }
+    variant = LBAC_KERNEL_BLOCK;
+    bx = default_bx(nx);
+    const int64_t nbx = (nx + bx - 1) / bx;
+    strip_h = (int)std::min<int64_t>(ny, std::max<int64_t>(4, std::min<int64_t>(64, nbx * ny / 1024)));
+    // the state read and written at 4.6 TB/s; the closure's passes about half as much again
+    return (h->closure ? 30.f : 8.f) + (h->closure ? 1.5f : 1.f) * mnodes * 2.f * state_bytes(h) / 4.6f;
+}
+
+// The next launch of a run with `left` steps to go: the shape that was set,
+// or, where nobody set one, the faster of the patch kernels and the strip
+// kernels.  Results do not depend on the choice (16-bit storage takes one
+// step per launch here, as its rounding depends on the steps of a launch).
+Launch plan_launch(lbac_ctx* h, int64_t left) {
+    if (h->shape_set) {
+        const int S = launch_steps_of(h);
+        return {false, {}, S > 1 && left >= S ? S : 1};
+    }
+    const bool three = h->p.precision == LBAC_F32 && stepS_allowed(h) && left >= 3;
+    const float strips = default_strips(h, three, h->variant, h->bx, h->strip_h);
+    // (the closure with the conventional model: one-step launches only)
+    if (!h->closure || h->p.model == LBAC_MODEL_IMPROVED) {
+        const PatchPlan p = plan_patch(h, left);
+        if (p.shape >= 0 && p.us < strips) return {true, p, p.S};
+    }
+    return {false, {}, three ? 3 : 1};
+}
+
+hipError_t do_launch(const lbac_ctx* h, const Launch& l, int src, int32_t k) {
+    if (l.patch) return launch_patch(h, src, k, l.p);
+    return l.S > 1 ? launch_stepS(h, src, k, l.S) : launch_step(h, src, k);
+}
+
 void launch_set_time(const lbac_ctx* h, int64_t t) {
     hipLaunchKernelGGL(set_time_kernel, dim3(1), dim3(kTimeThreads), 0, h->stream, h->t_dev, h->tfac,
                        time_period(h->p), t);
 }
 
-// Queues `n` steps from pop[src], S steps per launch where the variant
-// allows and single steps for the rest, and the advance of the step counter.
-// The counter (and the table of time factors with it) moves after every
+// Queues `n` steps from pop[src], several per launch where the plan allows and
+// single steps for the rest, and the advance of the step counter.  The
+// counter (and the table of time factors with it) moves after every
 // kTimeFactors steps at the latest.  *flips gets the number of launches
 // (buffer swaps).
-hipError_t launch_steps(const lbac_ctx* h, int src, int64_t n, int64_t* flips) {
+hipError_t launch_steps(lbac_ctx* h, int src, int64_t n, int64_t* flips) {
     int64_t f = 0;
     hipError_t e = hipSuccess;
-    const int S = launch_steps_of(h);
     int32_t k = 0;  // steps queued since the counter moved
+    auto advance = [&]() {
+        hipLaunchKernelGGL(advance_kernel, dim3(1), dim3(kTimeThreads), 0, h->stream, h->t_dev, h->tfac,
+                           time_period(h->p), (int64_t)k);
+        k = 0;
+        return hipGetLastError();
+    };
     for (int64_t left = n; left > 0 && e == hipSuccess;) {
-        const int cur = src ^ (int)(f & 1);
-        const int s = S > 1 && left >= S ? S : 1;
-        e = s > 1 ? launch_stepS(h, cur, k, s) : launch_step(h, cur, k);
-        k += s;
-        left -= s;
+        const Launch l = plan_launch(h, left);
+        if (k + l.S > kTimeFactors) e = advance();
+        if (e == hipSuccess) e = do_launch(h, l, src ^ (int)(f & 1), k);
+        k += l.S;
+        left -= l.S;
         ++f;
-        if (e == hipSuccess && (left == 0 || k + std::min<int64_t>(S, left) > kTimeFactors)) {
-            hipLaunchKernelGGL(advance_kernel, dim3(1), dim3(kTimeThreads), 0, h->stream, h->t_dev, h->tfac,
-                               time_period(h->p), (int64_t)k);
-            e = hipGetLastError();
-            k = 0;
-        }
     }
+    if (e == hipSuccess && k > 0) e = advance();
     *flips = f;
     return e;
 }
@@ -525,8 +603,7 @@ int lbac_host::create(const lbac_params* p, const double* phi0, bool phi0_on_dev
         if ((h->pitch / unit) % 2 == 0) h->pitch += unit;
     }
     h->plane_stride = (int64_t)h->pitch * p->ny + kPlanePadBytes / h->elem_bytes;
-    // default launch shape: full-width blocks when the grid allows, strips of 64 rows
-    h->bx = p->nx >= 256 ? 256 : (p->nx >= 128 ? 128 : 64);
+    h->bx = default_bx(p->nx);
     h->strip_h = std::min(64, p->ny);
     const size_t pop_bytes = (size_t)h->plane_stride * h->nplanes * h->elem_bytes;
     const size_t phis_bytes = ((size_t)h->pitch * p->ny + 64) * sizeof(float);
@@ -805,15 +882,18 @@ int lbac_set_launch(lbac_ctx* h, int32_t variant, int32_t bx, int32_t strip_h) {
     h->variant = variant;
     h->bx = bx;
     h->strip_h = std::min(strip_h, h->p.ny);
+    h->shape_set = true;
     drop_graphs(h);
     return LBAC_OK;
 }
 
 int lbac_get_launch(lbac_ctx* h, int32_t* variant, int32_t* bx, int32_t* strip_h) {
     if (!h) return LBAC_EINVAL;
-    if (variant) *variant = h->variant;
-    if (bx) *bx = h->bx;
-    if (strip_h) *strip_h = h->strip_h;
+    // a context whose shape nobody set reports the shape of creation, which
+    // lbac_set_launch accepts
+    if (variant) *variant = h->shape_set ? h->variant : LBAC_KERNEL_BLOCK;
+    if (bx) *bx = h->shape_set ? h->bx : default_bx(h->p.nx);
+    if (strip_h) *strip_h = h->shape_set ? h->strip_h : std::min(64, h->p.ny);
     return LBAC_OK;
 }
 
@@ -837,9 +917,21 @@ int lbac_autotune(lbac_ctx* h, int32_t steps, double* us_per_step) {
     HIPCHK(h, hipEventCreate(&e0));
     HIPCHK(h, hipEventCreate(&e1));
     const int keep_bx = h->bx, keep_h = h->strip_h, keep_v = h->variant;
+    const bool keep_set = h->shape_set;
     int best_bx = keep_bx, best_h = keep_h, best_v = keep_v;
     float best = 1e30f;
     hipError_t e = hipSuccess;
+    // mean ms per step of one(), which takes S steps per launch
+    auto time_ms = [&](auto&& one, int S) {
+        for (int w = 0; w < 2 && e == hipSuccess; ++w) e = one();
+        if (e == hipSuccess) e = hipEventRecord(e0, h->stream);
+        for (int s = 0; s < steps && e == hipSuccess; ++s) e = one();
+        if (e == hipSuccess) e = hipEventRecord(e1, h->stream);
+        if (e == hipSuccess) e = hipEventSynchronize(e1);
+        float ms = 0.f;
+        if (e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
+        return ms / (float)S;
+    };
     const int last_var = stepS_allowed(h) ? LBAC_KERNEL_FUSED3 : LBAC_KERNEL_BLOCK_DEEP;
     for (int var = LBAC_KERNEL_BLOCK; var <= last_var && e == hipSuccess; ++var)
     for (int bx : bxs) {
@@ -855,15 +947,8 @@ int lbac_autotune(lbac_ctx* h, int32_t steps, double* us_per_step) {
             // is untouched; an S-step launch counts as S steps
             const int S = launch_steps_of(h);
             auto one = [&]() { return S > 1 ? launch_stepS(h, h->cur, 0, S) : launch_step(h, h->cur, 0); };
-            for (int w = 0; w < 2 && e == hipSuccess; ++w) e = one();
-            if (e == hipSuccess) e = hipEventRecord(e0, h->stream);
-            for (int s = 0; s < steps && e == hipSuccess; ++s) e = one();
-            if (e == hipSuccess) e = hipEventRecord(e1, h->stream);
-            if (e == hipSuccess) e = hipEventSynchronize(e1);
-            float ms = 0.f;
-            if (e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
+            const float ms = time_ms(one, S);
             if (e != hipSuccess) break;
-            ms /= (float)S;
             if (ms < best) {
                 best = ms;
                 best_v = var;
@@ -873,13 +958,26 @@ int lbac_autotune(lbac_ctx* h, int32_t steps, double* us_per_step) {
         }
         if (e != hipSuccess) break;
     }
+    // the launches a context makes whose shape nobody set (the patch kernels on small grids)
+    bool set = true;
+    if (e == hipSuccess) {
+        h->shape_set = false;
+        const Launch l = plan_launch(h, INT32_MAX);
+        const float ms = time_ms([&]() { return do_launch(h, l, h->cur, 0); }, l.S);
+        if (e == hipSuccess && ms < best) {
+            best = ms;
+            set = false;
+        }
+    }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
+    h->shape_set = set;
     h->variant = best_v;
     h->bx = best_bx;
     h->strip_h = best_h;
     drop_graphs(h);
     if (e != hipSuccess) {
+        h->shape_set = keep_set;
         h->variant = keep_v;
         h->bx = keep_bx;
         h->strip_h = keep_h;
@@ -983,7 +1081,7 @@ int lbac_bytes_per_node(lbac_ctx* h, double* bytes) {
 
 int lbac_steps_per_launch(lbac_ctx* h, int32_t* steps) {
     if (!h || !steps) return LBAC_EINVAL;
-    *steps = launch_steps_of(h);
+    *steps = plan_launch(h, INT32_MAX).S;
     return LBAC_OK;
 }
 

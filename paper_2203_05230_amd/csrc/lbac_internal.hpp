@@ -56,6 +56,7 @@ struct lbac_ctx {
     int64_t t = 0;
     int variant = LBAC_KERNEL_BLOCK;
     int bx = 256, strip_h = 64;
+    bool shape_set = false;  // launch shape set by the caller or the autotuner (else plan_launch chooses per run)
     int graph_chunk = 0;
     hipGraphExec_t gexec[2] = {nullptr, nullptr};
     int gexec_chunk[2] = {0, 0};
@@ -81,6 +82,17 @@ int fail(lbac_ctx* h, int code, const std::string& msg);
 void* dev_alloc(lbac_ctx* h, size_t bytes);
 void dev_free(lbac_ctx* h, void* ptr);
 lbac::StepArgs make_args(const lbac_ctx* h, int src, int32_t k);
+
+// A launch of the patch kernels: which shape, its steps, and the time per
+// step that ranks it (microseconds); shape < 0: none.
+struct PatchPlan {
+    int shape, S;
+    float us;
+};
+float state_bytes(const lbac_ctx* h);  // stored bytes per node
+PatchPlan plan_patch(const lbac_ctx* h, int64_t left);  // the best shape of at most `left` steps
+hipError_t launch_patch(const lbac_ctx* h, int src, int32_t k, const PatchPlan& p);
+
 int create(const lbac_params* p, const double* phi0, bool phi0_on_device, lbac_ctx** out);
 void destroy(lbac_ctx* h);
 

@@ -16,6 +16,9 @@
 // the strip kernels, so the results are the same bit for bit.
 #pragma once
 
+#include <algorithm>
+
+#include "lbac_internal.hpp"
 #include "lbac_kernels.hpp"
 
 namespace lbac {
@@ -41,7 +44,7 @@ struct PatchLds<float, S, PW, PH, true> {
     float ps[N];
     float phr[N];             // phi (the network's input)
     int tab[16][kWave];       // per wavefront: its band nodes
-    uint16_t w[kClWN];        // the network, packed
+    alignas(16) uint16_t w[kClWN];  // the network, packed
     float b[kClBN];
 };
 
@@ -192,3 +195,144 @@ __global__ __launch_bounds__(NT) void patch_kernel(StepArgs a) {
 }
 
 }  // namespace lbac
+
+// ---------------------------------------------------------------------------
+// host side: the shapes that are built, the rule that chooses one, the launches
+
+namespace {
+
+using namespace lbac;
+
+// A shape: S steps of patches of pw x ph nodes.  first, more: microseconds of
+// a launch of at most 256 patches (one per CU) and of every further 256,
+// fitted to launches back to back on an MI355X.  They rank the shapes against
+// each other and against the strip kernels.
+struct Shape {
+    int S, pw, ph;
+    float first, more;
+};
+
+// FP32: measured at 64^2 to 4096^2 (for example 1.24 us per step with six
+// steps of 8 x 8 at 64^2, 1.62 with four of 16 x 16 at 256^2, 2.93 with four
+// of 32 x 16 at 512^2, 8.9 with three of 52 x 20 at 1024^2; the best of the
+// strip shapes take 6.9, 7.4, 8.1 and 12.6 us there).
+constexpr Shape kF32[] = {{6, 8, 8, 7.5f, 3.7f},   {4, 16, 16, 6.4f, 2.8f}, {6, 24, 24, 14.3f, 11.4f},
+                          {4, 32, 16, 7.8f, 4.1f}, {3, 52, 20, 8.3f, 5.2f}, {2, 24, 24, 5.4f, 2.2f},
+                          {1, 28, 28, 5.0f, 2.1f}};
+// FP64 (for example 2.34 us per step with four steps of 8 x 8 at 64^2, 3.3
+// with four of 16 x 16 at 200^2, 31 and 436 with three of 52 x 20 at 1024^2
+// and 4096^2; the best one-step strips 7.2, 9.8, 37 and 522 us).
+constexpr Shape kF64[] = {{4, 8, 8, 10.f, 6.5f},    {4, 16, 16, 13.3f, 10.6f}, {3, 20, 20, 11.1f, 9.1f},
+                          {3, 52, 20, 19.f, 20.f}, {2, 24, 24, 9.9f, 8.3f},   {1, 28, 28, 6.6f, 6.f}};
+// 16-bit storage: one step, since a launch rounds once (5.2, 7.1, 11.3 and
+// 16.0 us at 256^2, 512^2, 768^2 and 1024^2; strips 7.9, 9.6, 13.9 and 16.9).
+constexpr Shape kF16[] = {{1, 28, 28, 5.2f, 2.1f}};
+// FP32 with the closure, a disk's edge in the field (7.3, 8.7, 14.8 and 89 us
+// per step at 128^2, 200^2, 512^2 and 2048^2; the best of five multi-step
+// strip shapes 50, 57, 67 and 165).
+constexpr Shape kCl[] = {{4, 8, 8, 29.f, 9.f}, {3, 14, 14, 26.f, 5.f}, {2, 20, 20, 19.5f, 5.6f}, {2, 52, 20, 28.f, 9.f},
+                         {1, 26, 26, 12.f, 3.6f}};
+
+template <typename R, int ST, int MODEL, int S, int PW, int PH, int NT, bool CL = false>
+hipError_t go(StepArgs a, hipStream_t s) {
+    a.nbx = (a.nx + PW - 1) / PW;
+    a.nby = (a.ny + PH - 1) / PH;
+    a.n_xcd = lbac_host::kXcds;
+    hipLaunchKernelGGL((patch_kernel<R, ST, MODEL, S, PW, PH, NT, CL>), dim3(a.nbx * a.nby), dim3(NT), 0, s, a);
+    return hipGetLastError();
+}
+
+template <int MODEL>
+hipError_t go_f32(int shape, const StepArgs& a, hipStream_t s) {
+    switch (shape) {
+    case 0:
+        return go<float, ST_PLAIN, MODEL, 6, 8, 8, 1024>(a, s);
+    case 1:
+        return go<float, ST_PLAIN, MODEL, 4, 16, 16, 1024>(a, s);
+    case 2:
+        return go<float, ST_PLAIN, MODEL, 6, 24, 24, 768>(a, s);
+    case 3:
+        return go<float, ST_PLAIN, MODEL, 4, 32, 16, 768>(a, s);
+    case 4:
+        return go<float, ST_PLAIN, MODEL, 3, 52, 20, 1024>(a, s);
+    case 5:
+        return go<float, ST_PLAIN, MODEL, 2, 24, 24, 1024>(a, s);
+    default:
+        return go<float, ST_PLAIN, MODEL, 1, 28, 28, 1024>(a, s);
+    }
+}
+
+template <int MODEL>
+hipError_t go_f64(int shape, const StepArgs& a, hipStream_t s) {
+    switch (shape) {
+    case 0:
+        return go<double, ST_PLAIN, MODEL, 4, 8, 8, 576>(a, s);
+    case 1:
+        return go<double, ST_PLAIN, MODEL, 4, 16, 16, 1024>(a, s);
+    case 2:
+        return go<double, ST_PLAIN, MODEL, 3, 20, 20, 1024>(a, s);
+    case 3:
+        return go<double, ST_PLAIN, MODEL, 3, 52, 20, 1024>(a, s);
+    case 4:
+        return go<double, ST_PLAIN, MODEL, 2, 24, 24, 1024>(a, s);
+    default:
+        return go<double, ST_PLAIN, MODEL, 1, 28, 28, 1024>(a, s);
+    }
+}
+
+hipError_t go_cl(int shape, const StepArgs& a, hipStream_t s) {
+    switch (shape) {
+    case 0:
+        return go<float, ST_PLAIN, MODEL_IMPROVED, 4, 8, 8, 1024, true>(a, s);
+    case 1:
+        return go<float, ST_PLAIN, MODEL_IMPROVED, 3, 14, 14, 1024, true>(a, s);
+    case 2:
+        return go<float, ST_PLAIN, MODEL_IMPROVED, 2, 20, 20, 1024, true>(a, s);
+    case 3:
+        return go<float, ST_PLAIN, MODEL_IMPROVED, 2, 52, 20, 1024, true>(a, s);
+    default:
+        return go<float, ST_PLAIN, MODEL_IMPROVED, 1, 26, 26, 1024, true>(a, s);
+    }
+}
+
+const Shape* shapes_of(const lbac_ctx* h, int& n) {
+    if (h->closure) return n = 5, kCl;
+    if (h->storage != ST_PLAIN) return n = 1, kF16;
+    if (h->p.precision == LBAC_F64) return n = 6, kF64;
+    return n = 7, kF32;
+}
+
+}  // namespace
+
+lbac_host::PatchPlan lbac_host::plan_patch(const lbac_ctx* h, int64_t left) {
+    PatchPlan best{-1, 0, 0.f};
+    int n = 0;
+    const Shape* t = shapes_of(h, n);
+    // the state read and written once per launch at 4 TB/s bounds short launches on large grids
+    const float mem = 2.5e-7f * (float)((int64_t)h->p.nx * h->p.ny) * 2.f * state_bytes(h);
+    for (int i = 0; i < n; ++i) {
+        if (t[i].S > left) continue;
+        const int64_t tiles = (int64_t)((h->p.nx + t[i].pw - 1) / t[i].pw) * ((h->p.ny + t[i].ph - 1) / t[i].ph);
+        const float us = std::max(mem, t[i].first + (float)((tiles + 255) / 256 - 1) * t[i].more) / (float)t[i].S;
+        if (best.shape < 0 || us < best.us) best = {i, t[i].S, us};
+    }
+    return best;
+}
+
+hipError_t lbac_host::launch_patch(const lbac_ctx* h, int src, int32_t k, const PatchPlan& p) {
+    const StepArgs a = make_args(h, src, k);
+    const bool conv = h->p.model == LBAC_MODEL_CONVENTIONAL;
+    if (h->closure) return go_cl(p.shape, a, h->stream);
+    switch (h->p.precision) {
+    case LBAC_F64:
+        return conv ? go_f64<MODEL_CONVENTIONAL>(p.shape, a, h->stream) : go_f64<MODEL_IMPROVED>(p.shape, a, h->stream);
+    case LBAC_F32:
+        return conv ? go_f32<MODEL_CONVENTIONAL>(p.shape, a, h->stream) : go_f32<MODEL_IMPROVED>(p.shape, a, h->stream);
+    case LBAC_F32_F16STORE:
+        return conv ? go<float, ST_F16, MODEL_CONVENTIONAL, 1, 28, 28, 1024>(a, h->stream)
+                    : go<float, ST_F16, MODEL_IMPROVED, 1, 28, 28, 1024>(a, h->stream);
+    default:
+        return conv ? go<float, ST_BF16, MODEL_CONVENTIONAL, 1, 28, 28, 1024>(a, h->stream)
+                    : go<float, ST_BF16, MODEL_IMPROVED, 1, 28, 28, 1024>(a, h->stream);
+    }
+}

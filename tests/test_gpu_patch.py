@@ -1,0 +1,106 @@
+"""The patch kernels (the launches of a context whose shape nobody set, on
+grids whose strips cannot fill the device) against the one-step strip kernels:
+bit for bit, in every shape the rule chooses between and for every remainder
+of a step count, on sizes at and off the patches' edges."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+from paper_2203_05230_amd import closure as driver  # noqa: E402
+from paper_2203_05230_amd import lbac, workloads as W  # noqa: E402
+
+
+def say(*a):
+    print(*a, flush=True)
+
+
+def sims(nx, ny, precision, model="improved", closure=False, vel="vortex"):
+    case = dict(nx=nx, ny=ny, eps=0.8, tau=0.7, vel=vel, U=0.03, period_T=37.0, ux=0.04, uy=-0.03, precision=precision,
+                model=model)
+    rng = np.random.default_rng(nx * 1000 + ny)
+    phi0 = W.circle(nx, 0.8, R_frac=0.3, yc_frac=0.5, ny=ny) * (1.0 - 1e-3 * rng.random((ny, nx)))
+    out = []
+    for _ in range(2):
+        s = lbac.Simulation(case, phi0)
+        if closure:
+            s.set_closure(driver.init_weights(5, out_scale=0.05), 0.02)
+        out.append(s)
+    out[1].set_launch(64, 8, 0)  # one-step strips
+    return out
+
+
+def check(a, b, steps):
+    for n in steps:
+        a.step(n)
+        b.step(n)
+        assert a.time() == b.time()
+        assert np.array_equal(a.phi(), b.phi()), n
+    a.close()
+    b.close()
+
+
+# FP32 shapes by size: 8x8, 16x16, 24x24, 32x16, 52x20; FP64: 8x8, 16x16,
+# 20x20, 24x24, 52x20; sizes on the patches' edges, one off them, smaller than
+# a grown patch, and degenerate
+@pytest.mark.parametrize("nx,ny", [(1, 1), (1, 70), (33, 1), (5, 3), (31, 32), (64, 64), (129, 127), (200, 203), (256, 256),
+                                   (303, 290), (384, 385), (512, 500), (1040, 1000)])
+@pytest.mark.parametrize("precision", ["f32", "f64", "f32_f16store", "f32_bf16store"])
+def test_patches_equal_strips(nx, ny, precision):
+    say("case: patches", nx, ny, precision)
+    a, b = sims(nx, ny, precision)
+    check(a, b, (1, 2, 3, 4, 5, 13))
+
+
+@pytest.mark.parametrize("precision", ["f32", "f64", "f32_f16store"])
+def test_patches_equal_strips_conventional_model(precision):
+    say("case: patches, conventional model", precision)
+    for nx, ny in ((70, 61), (530, 410)):
+        a, b = sims(nx, ny, precision, model="conventional", vel="uniform")
+        check(a, b, (3, 14))
+
+
+# closure shapes by size: 8x8, 14x14, 20x20, 52x20
+@pytest.mark.parametrize("nx,ny", [(9, 7), (96, 101), (200, 190), (400, 420), (1000, 700)])
+def test_patches_equal_strips_with_the_closure(nx, ny):
+    say("case: patches with the closure", nx, ny)
+    a, b = sims(nx, ny, "f32", closure=True)
+    check(a, b, (1, 2, 3, 9))
+
+
+@pytest.mark.parametrize("precision", ["f32", "f64"])
+def test_long_runs_and_graphs(precision):
+    """Runs past the table of time factors (256 steps), in pieces, from graphs, and after a restored state."""
+    say("case: patches, long runs", precision)
+    a, b = sims(75, 66, precision)
+    a.step(700)
+    for n in (255, 1, 256, 188):
+        b.step(n)
+    assert np.array_equal(a.phi(), b.phi())
+    blob = a.get_state()
+    a.set_graph_chunk(300)
+    b.set_state(blob)
+    a.step(650)
+    b.step(650)
+    assert a.time() == b.time() == 1350 and np.array_equal(a.phi(), b.phi())
+    a.close()
+    b.close()
+
+
+def test_autotune_keeps_the_faster_and_the_state():
+    say("case: autotune on a small grid")
+    a, b = sims(96, 96, "f32")
+    a.step(7)
+    b.step(7)
+    us = a.autotune(3)
+    assert us > 0 and a.time() == 7
+    a.step(20)
+    b.step(20)
+    assert np.array_equal(a.phi(), b.phi())
+    bx, strip, variant = a.get_launch()
+    a.set_launch(bx, strip, variant)  # a reported shape can be set
+    a.step(5)
+    b.step(5)
+    assert np.array_equal(a.phi(), b.phi())
+    a.close()
+    b.close()
