@@ -154,6 +154,7 @@ StepArgs lbac_host::make_args(const lbac_ctx* h, int src, int32_t k) {
     a.strip_h = h->strip_h;
     a.vtab = h->vtab;
     a.vtabf = h->vtabf;
+    a.vrowf = h->vtabf + 2 * h->p.nx + 2 * h->p.ny;
     a.t_dev = h->t_dev;
     a.tfac = h->tfac;
     a.k = k;
@@ -322,41 +323,21 @@ hipError_t launch_stepS_cl(StepArgs a, int bx, hipStream_t s) {
     }
 }
 
-// One S-step launch with tile width BX.
-template <int MODEL, int S, int ST, int BX>
-hipError_t launch_stepS_shape(StepArgs a, hipStream_t s) {
-    a.nbx = (a.nx + BX - 1) / BX;
-    const dim3 grid(a.nbx * a.nby);
-    hipLaunchKernelGGL((stepS_kernel_lds<MODEL, BX, S, ST>), grid, dim3(stepS_threads<BX, S>()), 0, s, a);
-    return hipGetLastError();
-}
-
+// One S-step launch with tiles of bx columns, in strips of whole periods of the
+// kernel's march, which runs whole periods (the multiple nearest to the height
+// asked for).
 template <int MODEL, int S, int ST>
 hipError_t launch_stepS_m(StepArgs a, int bx, hipStream_t s) {
+    using L = TileSRows<S>;
+    constexpr int Q = L::kPeriod;
+    a.strip_h = std::max(Q, (a.strip_h + Q / 2) / Q * Q);
     a.nby = (a.ny + a.strip_h - 1) / a.strip_h;
     a.n_xcd = kXcds;
-    switch (bx) {
-    case 64:
-        return launch_stepS_shape<MODEL, S, ST, 64>(a, s);
-    case 96:
-        return launch_stepS_shape<MODEL, S, ST, 96>(a, s);
-    case 128:
-        return launch_stepS_shape<MODEL, S, ST, 128>(a, s);
-    case 160:
-        return launch_stepS_shape<MODEL, S, ST, 160>(a, s);
-    case 192:
-        return launch_stepS_shape<MODEL, S, ST, 192>(a, s);
-    case 224:
-        return launch_stepS_shape<MODEL, S, ST, 224>(a, s);
-    case 240:
-        return launch_stepS_shape<MODEL, S, ST, 240>(a, s);
-    case 288:
-        return launch_stepS_shape<MODEL, S, ST, 288>(a, s);
-    case 320:
-        return launch_stepS_shape<MODEL, S, ST, 320>(a, s);
-    default:
-        return launch_stepS_shape<MODEL, S, ST, 256>(a, s);
-    }
+    a.tile_w = bx;
+    a.nbx = (a.nx + bx - 1) / bx;
+    const dim3 grid(a.nbx * a.nby), block((bx + 4 * S + 63) / 64 * 64);
+    hipLaunchKernelGGL((stepS_kernel_lds<MODEL, S, ST>), grid, block, L::bytes(bx), s, a);
+    return hipGetLastError();
 }
 
 template <int ST>
@@ -618,8 +599,10 @@ int lbac_host::create(const lbac_params* p, const double* phi0, bool phi0_on_dev
     std::vector<double> tab;
     build_velocity(h->p, tab);
     h->vtab = (double*)dev_alloc(h, tab.size() * sizeof(double));
-    h->vtabf = (float*)dev_alloc(h, tab.size() * sizeof(float));
     std::vector<float> tabf(tab.begin(), tab.end());
+    for (int j = 0; j < p->ny; ++j)  // the row factors again, as pairs
+        for (int c = 0; c < 2; ++c) tabf.push_back(tabf[2 * (size_t)p->nx + (size_t)c * p->ny + j]);
+    h->vtabf = (float*)dev_alloc(h, tabf.size() * sizeof(float));
     h->t_dev = (int64_t*)dev_alloc(h, 64);
     h->tfac = (double*)dev_alloc(h, (kTimeFactors + 1) * sizeof(double));
     h->rows = dev_alloc(h, 10 * sizeof(double) * (size_t)p->ny);  // five compensated pairs per row

@@ -88,7 +88,13 @@ bool build_items(const std::vector<Geometry>& geo, int strip_h, std::vector<Item
         // the pipeline's fill, so a ragged last strip is avoided
         const int nby = std::max(1, std::min((int)std::lround((double)ny / strip_h), ny / kBatchMinStrip));
         const int nbx = (int)ct.size();
-        auto strip_y0 = [&](int j) { return (int)((int64_t)j * ny / nby); };
+        // cut at multiples of the march's period where strips are long enough
+        // (the kernel runs whole periods of rows)
+        constexpr int Q = TileSRows<kBatchS>::kPeriod;
+        auto strip_y0 = [&](int j) {
+            const int y = (int)((int64_t)j * ny / nby);
+            return j == nby || ny < 2 * Q * nby ? y : (y + Q / 2) / Q * Q;
+        };
         std::vector<int> tile_of_col(nx), strip_of_row(ny);
         for (int i = 0; i < nbx; ++i)
             for (int c = ct[i].first; c < ct[i].first + ct[i].second; ++c) tile_of_col[c] = i;

@@ -195,7 +195,7 @@ __global__ __launch_bounds__(kBatchThreads) __attribute__((amdgpu_waves_per_eu(3
     using C4 = const __attribute__((address_space(4))) BatchDev;
     using I4 = const __attribute__((address_space(4))) BatchItem;
     using N4 = const __attribute__((address_space(4))) BatchInst;
-    __shared__ TileSLds<kBatchTile, S> lds;
+    __shared__ float lds[TileSRows<S>::bytes(kBatchTile) / sizeof(float)];
     __shared__ int64_t slot;
     for (;;) {
         // an opaque zero, so that the block is read again per slot instead
@@ -237,7 +237,7 @@ __global__ __launch_bounds__(kBatchThreads) __attribute__((amdgpu_waves_per_eu(3
         const int64_t gp = S == 1 ? nfull + p : p;  // pass index within the run
         const StepArgs a = insts[2 * inst + (int)(gp & 1)].a;
         const int64_t t = a.t_dev[0] + (dry ? 0 : (S == 1 ? nfull * kBatchS + p : (int64_t)p * kBatchS));
-        stepS_tile_lds<MODEL, kBatchTile, S, ST, true>(a, item.x0, item.w, item.ys, item.hh, t, item.down != 0, lds);
+        stepS_tile_lds<MODEL, S, ST, true>(a, item.x0, item.w, kBatchTile, item.ys, item.hh, t, item.down != 0, lds);
         // publish: every wavefront waits until its device-scope stores have
         // completed (vmcnt counts stores on this architecture), then the
         // counter moves; no writeback of the whole L2 is needed

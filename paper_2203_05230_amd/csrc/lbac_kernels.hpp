@@ -32,6 +32,7 @@
 #include <stdint.h>
 
 #include <type_traits>
+#include <utility>
 
 namespace lbac {
 
@@ -64,8 +65,10 @@ struct StepArgs {
     int32_t pitch;          // elements between rows
     int32_t nx, ny;
     int32_t strip_h;        // rows per block
+    int32_t tile_w;         // columns per block (multi-step kernel)
     const double* vtab;     // Ax[nx], Bx[nx], Ay[ny], By[ny]: u = s(t) Ax Ay, v = s(t) Bx By
     const float* vtabf;     // the same table rounded to FP32
+    const float* vrowf;     // its row factors as pairs (Ay, By)
     const int64_t* t_dev;   // step count at the start of this launch sequence
     const double* tfac;     // s(t_dev[0] - 1 + j), j = 0 .. kTimeFactors (see fill_factors)
     int32_t k;              // this launch is step t_dev[0] + k
@@ -264,6 +267,12 @@ __device__ __forceinline__ double row_factor(const double* vtab, int64_t i) {
 __device__ __forceinline__ float row_factor(const float* vtabf, int64_t i) {
     return ((const __attribute__((address_space(4))) float*)vtabf)[i];
 }
+// both FP32 factors of row y, one scalar load
+__device__ __forceinline__ float2 row_pair(const float* vrowf, int y) {
+    typedef float f2 __attribute__((ext_vector_type(2)));
+    const f2 v = ((const __attribute__((address_space(4))) f2*)vrowf)[y];
+    return make_float2(v.x, v.y);
+}
 
 // Steps one fill of the time-factor table serves.
 constexpr int kTimeFactors = 256;
@@ -314,6 +323,17 @@ __device__ __forceinline__ R normal_source(R phi, const NodeConst<R>& k) {
     return k.psi_scale * (Math<R>::log2(pc + k.delta) - Math<R>::log2(R(1) - pc + k.delta));
 }
 
+// The same, keeping a b = (phi_c + delta)(1 - phi_c + delta) for the sharpening
+// magnitude of the node (not formed for the conventional model).
+template <typename R, int MODEL>
+__device__ __forceinline__ R normal_source(R phi, const NodeConst<R>& k, R& ab) {
+    if (MODEL == MODEL_CONVENTIONAL) return phi;
+    const R pc = clip01(phi);
+    const R a = pc + k.delta, b = R(1) - pc + k.delta;
+    ab = a * b;
+    return k.psi_scale * (Math<R>::log2(a) - Math<R>::log2(b));
+}
+
 // Isotropic gradient grad chi = sum_i w_i c_i chi(x + c_i) / c_s^2 from the
 // eight neighbours of a node.
 template <typename R>
@@ -326,21 +346,28 @@ __device__ __forceinline__ void iso_gradient(R pE, R pW, R pN, R pS, R pNE, R pN
 // n = grad psi / (|grad psi| + delta) (Eq. (13)) and S the sharpening
 // magnitude (Eq. (6) in the algebraic form below, or phi (1 - phi)/eps for
 // the conventional model).  u, v at t; uo, vo at t - 1; phio = phi at t - 1.
+// ab: (phi_c + delta)(1 - phi_c + delta) as normal_source formed it (improved
+// model).
 template <typename R, int MODEL>
-__device__ __forceinline__ void flux_bracket(R gx, R gy, R phi, R phio, R u, R v, R uo, R vo, const NodeConst<R>& k,
-                                             R& Gx, R& Gy) {
+__device__ __forceinline__ void flux_bracket(R gx, R gy, R phi, R ab, R phio, R u, R v, R uo, R vo,
+                                             const NodeConst<R>& k, R& Gx, R& Gy) {
     const R inv = Math<R>::rcp(Math<R>::sqrt(fmaR(gx, gx, gy * gy)) + k.delta);
     R S;
     if (MODEL == MODEL_CONVENTIONAL) {
         S = phi * (R(1) - phi) / k.eps;
     } else {
         // (1 - tanh^2(psi/(2 eps)))/(4 eps) = a b / (eps (a + b)^2), a = phi_c + delta, b = 1 - phi_c + delta
-        const R pc = clip01(phi);
-        S = (pc + k.delta) * (R(1) - pc + k.delta) * k.s_scale;
+        S = ab * k.s_scale;
     }
     const R Sn = R(1.0 / 3.0) * S * inv;
     Gx = fmaR(Sn, gx, fmaR(phi, u, -(phio * uo)));
     Gy = fmaR(Sn, gy, fmaR(phi, v, -(phio * vo)));
+}
+template <typename R, int MODEL>
+__device__ __forceinline__ void flux_bracket(R gx, R gy, R phi, R phio, R u, R v, R uo, R vo, const NodeConst<R>& k,
+                                             R& Gx, R& Gy) {
+    const R pc = clip01(phi);
+    flux_bracket<R, MODEL>(gx, gy, phi, (pc + k.delta) * (R(1) - pc + k.delta), phio, u, v, uo, vo, k, Gx, Gy);
 }
 
 // Eq. (9)-(11): f*_i = (1 - 1/tau) f_i + w_i [phi/tau + 3 c_i.(phi u/tau + (1 - 1/(2 tau)) G)].
@@ -498,6 +525,78 @@ struct Io<float, ST_F16> : IoShifted<__half> {
 template <>
 struct Io<float, ST_BF16> : IoShifted<__hip_bfloat16> {
     using IoShifted<__hip_bfloat16>::IoShifted;
+};
+
+// Storage access of the multi-step kernel: every plane through a buffer
+// resource shared by several, the plane chosen by the scalar offset
+// (population q's plane m(q), q or its mirror image), the same offsets for
+// both buffers.  FP32: planes 0..4 and 5..8, which the mirror keeps apart, so
+// that a resource spans at most five planes of 2^27 padded nodes (2.7 GB):
+// 25 scalar registers where a base pointer per load and a resource per store
+// take 58, which had spilled into vector lanes.  16-bit: the eight g planes
+// (2.2 GB at most), and the phi* plane.  A resource's range is 3 GiB; lanes
+// with nothing to store pass that as their offset and are dropped.
+constexpr uint32_t kRowsRange = 0xC0000000u;
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_rsrc(const void* base) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, (int)kRowsRange, 0x00020000);
+}
+
+template <int ST>
+struct IoRows {
+    static constexpr bool kShifted = true;
+    using H = typename std::conditional<ST == ST_F16, __half, __hip_bfloat16>::type;
+    __amdgpu_buffer_rsrc_t sg, dg, sp, dp;
+    uint32_t pb[9];
+    __device__ __forceinline__ IoRows(const StepArgs& a, bool mirror)
+        : sg(rows_rsrc(a.src)), dg(rows_rsrc(a.dst)), sp(rows_rsrc(a.src_phi)), dp(rows_rsrc(a.dst_phi)) {
+        pb[0] = 0;
+#pragma unroll
+        for (int q = 1; q < 9; ++q) pb[q] = (uint32_t)((mirror ? mirror_q(q) : q) - 1) * (uint32_t)a.plane_stride * 2u;
+    }
+    // v[0] = phi*, v[i] = w_i phi* + g_i (see StoreShifted)
+    __device__ __forceinline__ void load(uint32_t off, float (&v)[9]) const {
+        const float ph = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(sp, (int)(off * 4u), 0, 0));
+        v[0] = ph;
+#pragma unroll
+        for (int q = 1; q < 9; ++q) {
+            const unsigned short g = __builtin_amdgcn_raw_buffer_load_b16(sg, (int)(off * 2u), (int)pb[q], 0);
+            v[q] = __builtin_fmaf(wq<float>(q), ph, h2f<H>(__builtin_bit_cast(H, g)));
+        }
+    }
+    __device__ __forceinline__ void store_nt(bool on, uint32_t off, const float (&v)[9], float phi) const {
+        const uint32_t b2 = on ? off * 2u : kRowsRange, b4 = on ? off * 4u : kRowsRange;
+#pragma unroll
+        for (int q = 1; q < 9; ++q)
+            __builtin_amdgcn_raw_buffer_store_b16(
+                __builtin_bit_cast(unsigned short, f2h<H>(__builtin_fmaf(-wq<float>(q), phi, v[q]))), dg, (int)b2,
+                (int)pb[q], 2);
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(phi), dp, (int)b4, 0, 2);
+    }
+};
+
+template <>
+struct IoRows<ST_PLAIN> {
+    static constexpr bool kShifted = false;
+    __amdgpu_buffer_rsrc_t s0, s1, d0, d1;
+    uint32_t pb[9];
+    __device__ __forceinline__ IoRows(const StepArgs& a, bool mirror)
+        : s0(rows_rsrc(a.src)), s1(rows_rsrc(static_cast<const float*>(a.src) + 5 * a.plane_stride)), d0(rows_rsrc(a.dst)),
+          d1(rows_rsrc(static_cast<float*>(a.dst) + 5 * a.plane_stride)) {
+#pragma unroll
+        for (int q = 0; q < 9; ++q)
+            pb[q] = (uint32_t)((mirror ? mirror_q(q) : q) - (q < 5 ? 0 : 5)) * (uint32_t)a.plane_stride * 4u;
+    }
+    __device__ __forceinline__ void load(uint32_t off, float (&v)[9]) const {
+#pragma unroll
+        for (int q = 0; q < 9; ++q)
+            v[q] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(q < 5 ? s0 : s1, (int)(off * 4u), (int)pb[q], 0));
+    }
+    __device__ __forceinline__ void store_nt(bool on, uint32_t off, const float (&v)[9], float /*phi*/) const {
+        const uint32_t b = on ? off * 4u : kRowsRange;
+#pragma unroll
+        for (int q = 0; q < 9; ++q)
+            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v[q]), q < 5 ? d0 : d1, (int)b, (int)pb[q], 2);
+    }
 };
 
 // FP32 plain storage read and written with device-scope accesses (the
@@ -1087,20 +1186,16 @@ struct StepSGeom {
     static constexpr int NP = UL + 3;          // depth of the phi(t - 1) history
 };
 
-template <int BX, int S, bool CL>
-struct TileSLdsBase {
-    static constexpr int W = StepSGeom<BX, S, CL>::W;
+// LDS of the S-step tile with the closure: a row per value.
+template <int BX, int S>
+struct TileSLds {
+    static constexpr int W = StepSGeom<BX, S, true>::W;
     float ro[S][3][2][W];                          // input of stage k: old pair, three rows
     float rm[S][2][2][W];                          // populations 1 and 3, two rows
     float rn[S][2][W];                             // new pair, one row
-    float ps[S][StepSGeom<BX, S, CL>::NPS][W];     // psi of stage k on its last rows
-};
-template <int BX, int S, bool CL = false>
-struct TileSLds : TileSLdsBase<BX, S, CL> {};
-template <int BX, int S>
-struct TileSLds<BX, S, true> : TileSLdsBase<BX, S, true> {
-    float phr[S][5][TileSLdsBase<BX, S, true>::W];  // phi of stage k on its last five rows
-    int tab[(BX + 6 * S + 63) / 64][S * 64];         // per wavefront: the band nodes of an iteration
+    float ps[S][StepSGeom<BX, S, true>::NPS][W];   // psi of stage k on its last rows
+    float phr[S][5][W];                            // phi of stage k on its last five rows
+    int tab[(BX + 6 * S + 63) / 64][S * 64];       // per wavefront: the band nodes of an iteration
 };
 
 // Threads of an S-step tile of at most BX columns: the BX + 2H columns of the
@@ -1111,33 +1206,59 @@ __host__ __device__ constexpr int stepS_threads() {
     return (BX + 2 * StepSGeom<BX, S, CL>::H + 63) / 64 * 64;
 }
 
-// COH: storage read and written with device-scope accesses (IoCoherent,
-// IoCoherentShifted: the batched form, at time t; else t is not used).  CL:
-// the learned closure (FP32 plain storage).
-template <int MODEL, int BX, int S, int ST, bool COH = false, bool CL = false>
-__device__ __forceinline__ void stepS_tile_lds(const StepArgs& a, int x0, int w, int ys, int hh, int64_t t,
-                                               bool down, TileSLds<BX, S, CL>& lds) {
-    static_assert(!CL || (ST == ST_PLAIN && !COH), "the closure runs with FP32 plain storage");
-    using G = StepSGeom<BX, S, CL>;
-    constexpr int H = G::H, UL = G::UL, LG = G::LG, PER = G::PER, D = G::D, W = G::W, NPS = G::NPS;
-    using IoCoh = typename std::conditional<
-        ST == ST_PLAIN, IoCoherent,
-        IoCoherentShifted<typename std::conditional<ST == ST_F16, __half, __hip_bfloat16>::type>>::type;
-    using IoT = typename std::conditional<COH, IoCoh, Io<float, ST>>::type;
-    // Thread layout.  The tile's first hd columns (its head: the columns up to
-    // the first 128-byte line boundary of the storage, when x0 is not on one
-    // and the layout below still fits; else hd = 0) and the C = 64 * c
-    // columns after them that whole wavefronts own go to wavefronts 0 .. c - 1
-    // in segments of 64 columns, each starting on a line (so every wavefront
-    // loads and stores whole lines); wavefront c, the halo wavefront, takes the
-    // H left halo columns, the head, the tile's remaining w - hd - C columns
-    // and the right halo (c is the largest count for which that fits in 64
-    // lanes, else one more, whose last columns then belong to the right halo);
-    // later wavefronts (a tile narrower than BX) only take part in the
-    // barriers.  Threads whose column lies past the right halo
-    // duplicate its last column: they load what its owner loads, write their
-    // LDS values to the padding column and store nothing.  cxo: column
-    // relative to x0 (-H .. w + H - 1); act: owns tile column x0 + cxo.
+// LDS of the S-step tile: per column the values its neighbours read, all
+// together, N of them (odd, so that the same value of neighbouring columns
+// falls in different banks).  Everything a thread reads then lies within
+// three columns, in reach of a two-value LDS read's short offsets from one
+// address register; a row per value (the layout before) took an address
+// register for each pair, about thirty in all.
+template <int S>
+struct TileSRows {
+    // columns held for tiles of at most bx: the grown tile, one on each side
+    // (so that reads east and west stay inside), the last one also taking the
+    // writes of threads past the grown tile
+    static constexpr __device__ __host__ int columns(int bx) { return bx + 4 * S + 2; }
+    // Rows in the longer rings, and iterations after which every ring is back
+    // at its first place.  Three rows are enough; at S = 2, where LDS allows,
+    // four make the period four, so that strips of 8 rows are whole periods.
+    static constexpr int R = S == 2 ? 4 : 3, kPeriod = S == 2 ? 4 : 6;
+    static constexpr int K = 3 * R + 6;  // values per stage
+    static constexpr int N = (K * S) | 1;
+    // of stage k: the input's old pair (R rows), populations 1 and 3 (two
+    // rows), the new pair (one row), psi on its last R rows
+    static constexpr __device__ __host__ int ro(int k, int row, int p) { return K * k + 2 * row + p; }
+    static constexpr __device__ __host__ int rm(int k, int row, int p) { return K * k + 2 * R + 2 * row + p; }
+    static constexpr __device__ __host__ int rn(int k, int p) { return K * k + 2 * R + 4 + p; }
+    static constexpr __device__ __host__ int ps(int k, int row) { return K * k + 2 * R + 6 + row; }
+    static constexpr __device__ __host__ int bytes(int bx) { return columns(bx) * N * (int)sizeof(float); }
+};
+
+// Calls f(integral_constant<int, I>) for I = 0 .. n - 1 (n the sequence's length).
+template <typename F, int... I>
+__device__ __forceinline__ void unrolled(F&& f, std::integer_sequence<int, I...>) {
+    (f(std::integral_constant<int, I>{}), ...);
+}
+
+// Thread layout of a tile of w columns at x0.  The tile's first hd columns (its
+// head: the columns up to the first 128-byte line boundary of the storage,
+// when x0 is not on one and the layout below still fits; else hd = 0) and the
+// C = 64 * c columns after them that whole wavefronts own go to wavefronts
+// 0 .. c - 1 in segments of 64 columns, each starting on a line (so every
+// wavefront loads and stores whole lines); wavefront c, the halo wavefront,
+// takes the H left halo columns, the head, the tile's remaining w - hd - C
+// columns and the right halo (c is the largest count for which that fits in
+// 64 lanes, else one more, whose last columns then belong to the right halo);
+// later wavefronts (a tile narrower than the launch's widest) only take part
+// in the barriers.  Threads whose column lies past the right halo duplicate
+// its last column: they load what its owner loads, write their LDS values to
+// the padding column and store nothing.  cxo: column relative to x0
+// (-H .. w + H - 1); act: owns tile column x0 + cxo.
+struct StepSThread {
+    int cxo;
+    bool dup, act, idle;  // idle: the wavefront has no column (uniform)
+};
+template <int ST>
+__device__ __forceinline__ StepSThread stepS_thread(int x0, int w, int H) {
     const int l = threadIdx.x;
     const int wv = __builtin_amdgcn_readfirstlane(l) / kWave;  // wavefront index (uniform)
     constexpr int LC = ST == ST_PLAIN ? 32 : 64;  // columns per 128-byte line of the storage
@@ -1148,9 +1269,57 @@ __device__ __forceinline__ void stepS_tile_lds(const StepArgs& a, int x0, int w,
     const int hw = C / kWave;  // the halo wavefront
     const int hl = l - C;      // lane in the halo wavefront
     const int craw = wv < hw ? hd + l : (hl < H + hd ? hl - H : C + hl - H);
-    const bool dup = craw > w + H - 1;
-    const int cxo = min(craw, w + H - 1);
-    const bool act = cxo >= 0 && cxo < w && !dup;
+    StepSThread r;
+    r.dup = craw > w + H - 1;
+    r.cxo = min(craw, w + H - 1);
+    r.act = r.cxo >= 0 && r.cxo < w && !r.dup;
+    r.idle = wv > hw;
+    return r;
+}
+
+// A row index that walks the periodic rows one at a time.
+struct RowWalk {
+    int y, dir, ny;
+    __device__ __forceinline__ RowWalk(int y0, bool down, int n) : y(wrap_idx(y0, n)), dir(down ? -1 : 1), ny(n) {}
+    __device__ __forceinline__ void next() {
+        y += dir;
+        y = y == ny ? 0 : (y < 0 ? ny - 1 : y);
+    }
+};
+
+// COH: storage read and written with device-scope accesses (IoCoherent,
+// IoCoherentShifted: the batched form, at time t; else t is not used).
+//
+// The march is written out by its place in the period of the rings (U), so
+// that every ring slot, in LDS and in registers, is a constant: the S-step
+// kernel is bound by its instruction stream, at three wavefronts per SIMD by
+// the scalar one and its waits too.  The first F iterations fill the pipeline:
+// they are written out one by one, each with only the stages that have input,
+// and store nothing; the loop after them runs every stage, without a branch.
+// Per row at S = 3: 278 vector and 44 scalar instructions, 33 LDS accesses and
+// 13 waits, 144 registers.  (Before: one loop of two iterations with the slots
+// computed from the iteration number, a branch around every stage, histories
+// aged by moves, rows wrapped by division, an LDS row per value: about 350,
+// 230, 51 and 30, 167 registers.)  8192^2 FP32 in 224 x 40 tiles: 355 -> 341
+// us per step, where a launch now moves the state at the rate of a plain copy;
+// 3000 x 1500: 37.5 -> 26.9; 1000 x 1400, two steps per launch on 160 x 8
+// tiles: 21.1 -> 16.1 (FP16 storage 21.4 -> 14.1).
+//
+// lds: TileSRows<S>::bytes(bx) bytes, bx >= w the widest tile of the launch.
+template <int MODEL, int S, int ST, bool COH = false>
+__device__ __forceinline__ void stepS_tile_lds(const StepArgs& a, int x0, int w, int bx, int ys, int hh, int64_t t,
+                                               bool down, float* lds) {
+    using G = StepSGeom<64, S, false>;
+    using L = TileSRows<S>;
+    constexpr int H = G::H, PER = G::PER, R = L::R, Q = L::kPeriod;
+    constexpr int F = PER * (S - 1) + 4;  // iterations before the first stored row
+    static_assert(G::UL == 1 && F == H + G::D, "rows: the strip's, its halo's and the pipeline's");
+    using IoCoh = typename std::conditional<
+        ST == ST_PLAIN, IoCoherent,
+        IoCoherentShifted<typename std::conditional<ST == ST_F16, __half, __hip_bfloat16>::type>>::type;
+    using IoT = typename std::conditional<COH, IoCoh, IoRows<ST>>::type;
+    const StepSThread th = stepS_thread<ST>(x0, w, H);
+    const int cxo = th.cxo;
     // Stage k forms phi/psi validly on the columns (and rows) up to
     // RC (S - k) - 1 beyond the tile and updates up to RC (S - 1 - k) beyond
     // it.  Every thread runs every stage (branching on these ranges would only
@@ -1158,8 +1327,13 @@ __device__ __forceinline__ void stepS_tile_lds(const StepArgs& a, int x0, int w,
     // outside them a thread forms values from rows or columns that are not
     // valid yet, which no valid value reads.
     const int gcol = wrap_idx(x0 + cxo, a.nx);
-    const int j = cxo + H + 1;        // LDS column read
-    const int jw = dup ? W - 1 : j;   // LDS column written
+    const int j = cxo + H + 1;  // LDS column
+    // LDS addresses of the column west of the own one, where reads start, and
+    // of the column written
+    typedef __attribute__((address_space(3))) float LdsFloat;
+    const uint32_t lds_b = (uint32_t)(uintptr_t)(LdsFloat*)lds;
+    uint32_t west_b = lds_b + (uint32_t)((j - 1) * L::N * 4);
+    uint32_t own_b = lds_b + (uint32_t)((th.dup ? L::columns(bx) - 1 : j) * L::N * 4);
     // A strip marched downward is computed in the mirrored frame y -> -y:
     // populations are read from and written to the planes of their mirror
     // images and the y velocity changes sign, so the march always runs
@@ -1170,10 +1344,9 @@ __device__ __forceinline__ void stepS_tile_lds(const StepArgs& a, int x0, int w,
     const IoT io(a, down);
     lds_barrier();  // the LDS may still be read by a previous tile of this block
 
-    const int iters = hh + H + D;
-    if (wv > hw) {
-        // no column in this wavefront: the loop's two barriers per iteration only
-        for (int it = 0; it < iters; ++it) {
+    if (th.idle) {
+        // no column in this wavefront: the march's two barriers per iteration only
+        for (int it = F + (hh + Q - 1) / Q * Q; it > 0; --it) {
             lds_barrier();
             lds_barrier();
         }
@@ -1190,27 +1363,274 @@ __device__ __forceinline__ void stepS_tile_lds(const StepArgs& a, int x0, int w,
         if constexpr (COH) kcs[k] = NodeConst<float>::at(a, t + k);
         else kcs[k] = NodeConst<float>(a, k);
     }
+    // pulled populations, phi and the sharpening's a b of stage k by iteration
+    // parity: the pull of iteration it fills half it % 2, the update of
+    // iteration it + 1 reads it
+    float fp[S][2][9], ph[S][2], ab[S][2];
+    // Histories, rings by iteration.  P: the sum of the stage's input
+    // populations at the own node (phi(t + k - 1) as the one-step kernel forms
+    // it); z0, zo, zn: the own column's c_x = 0 inputs (population 0, the
+    // old-row one, the new-row one).  An update of stage k - 1 writes stage
+    // k's place of the same iteration, which stage k has read by then (its
+    // pull before the barrier, its update first: the updates run from the
+    // last stage to the first).
+    float P[S][R], z0[S][R], zo[S][R], zn[S];
+    // shifted storage: the own column's populations 4, 7 and 8 of stage 0's last
+    // two input rows (the rings keep them only where another column pulls them)
+    float o4[2], o7[2], o8[2];
+    constexpr bool kSh = IoT::kShifted;
+
+    // lattice rows: the next one to load (the last input row, hh + 2H - 1, is
+    // repeated past the end; what it forms is not used), stage k's updated one,
+    // and the stored one's offset
+    RowWalk rl(down ? ys + hh + H - 1 : ys - H, down, a.ny);
+    int loads_left = hh + 2 * H - 1;
+    auto load = [&](float(&nv)[9]) __attribute__((always_inline)) {
+        io.load((uint32_t)rl.y * (uint32_t)a.pitch + (uint32_t)gcol, nv);
+        if (loads_left > 0) rl.next();
+        --loads_left;
+    };
+    // (stage k updates, at iteration it, the row 3 k + 2 behind the one loaded for it)
+    auto first_row = [&](int k) {
+        const int behind = 3 * k + 2;
+        return down ? ys + hh + H - 1 + behind : ys - H - behind;
+    };
+    int yk[S];
+#pragma unroll
+    for (int k = 0; k < S; ++k) yk[k] = wrap_idx(first_row(k), a.ny);
+    const int dir = down ? -1 : 1;
+    const int spitch = dir * a.pitch;
+    int srow = (down ? ys + hh - 1 : ys) * a.pitch + x0 + cxo;  // element offset of the next stored node
+
+    // a stage's input into its ring and histories (v: populations at the own column)
+    auto put = [&](int k, auto U_, const float(&v)[9]) __attribute__((always_inline)) {
+        constexpr int U = decltype(U_)::value;
+        LdsFloat* own_w = (LdsFloat*)own_b;
+        // phi at t + k - 1: the sum of the stage's input values (phi* itself
+        // for stage 0's shifted input)
+        P[k][U % R] = kSh && k == 0 ? v[0] : sum9(v);
+        if (kSh && k == 0) {
+            o4[U % 2] = v[4];
+            o7[U % 2] = v[7];
+            o8[U % 2] = v[8];
+        }
+        own_w[L::ro(k, U % R, 0)] = v[5];
+        own_w[L::ro(k, U % R, 1)] = v[6];
+        own_w[L::rm(k, U % 2, 0)] = v[1];
+        own_w[L::rm(k, U % 2, 1)] = v[3];
+        own_w[L::rn(k, 0)] = v[8];
+        own_w[L::rn(k, 1)] = v[7];
+        z0[k][U % R] = v[0];
+        zo[k][U % R] = v[2];
+        zn[k] = v[4];
+    };
+    // place of the row `age` iterations old in a ring of R
+    constexpr auto at = [](int u, int age) { return (u + 2 * R - age) % R; };
+    int left = hh;  // rows to store
+    // An iteration at place U of the period; IT: which one of the pipeline's
+    // fill, or -1 (all stages run; past the strip's last row nothing is stored).
+    auto body = [&](float(&nv)[9], auto U_, auto IT_) __attribute__((always_inline)) {
+        constexpr int U = decltype(U_)::value;
+        constexpr int IT = decltype(IT_)::value;  // the fill's iteration, or -1: all stages run
+        constexpr int B = U % 2;
+        // (instructions stay in their iteration and stage: mixed across them
+        // they hold up to 168 registers instead of 136)
+        // opaque here, so that every LDS address is formed from these two
+        // registers with an immediate offset (hoisted out of the loop as
+        // invariants the addresses took dozens of registers)
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("" : "+v"(west_b), "+v"(own_b));
+        const LdsFloat* west = (const LdsFloat*)west_b;
+        LdsFloat* own_w = (LdsFloat*)own_b;
+        // the row factors of the rows the stages update (consumed after the barriers)
+        float2 rf[S];
+#pragma unroll
+        for (int k = 0; k < S; ++k)
+            if (IT < 0 || IT >= PER * k + 4) rf[k] = row_pair(a.vrowf, yk[k]);
+        // ---- the row loaded two iterations ago into stage 0's ring
+        put(0, U_, nv);
+        load(nv);
+        lds_barrier();
+
+        // ---- phi (Eq. (12)) and psi (Eq. (13)) of every stage.  Stage 0 reads
+        // rows entered 0 (new pair), 1 (populations 1, 3) and 2 (old pair)
+        // iterations ago; a later stage's input rows were written 1, 2 and 3
+        // iterations ago.  Every stage's reads go out first, so that one LDS
+        // latency is waited for and not S.
+        constexpr bool own_row = kSh && (IT < 0 || IT >= 2);
+        float own[9];
+#pragma unroll
+        for (int k = 0; k < S; ++k) {
+            if (IT >= 0 && IT < PER * k + 2) continue;
+            const int so = at(U, k == 0 ? 2 : 3);
+            const int sm = k == 0 ? B ^ 1 : B;
+            float(&f)[9] = fp[k][B];
+            f[0] = z0[k][at(U, k == 0 ? 1 : 2)];
+            f[1] = west[L::rm(k, sm, 0)];
+            f[2] = zo[k][so];
+            f[3] = west[2 * L::N + L::rm(k, sm, 1)];
+            f[4] = zn[k];
+            f[5] = west[L::ro(k, so, 0)];
+            f[6] = west[2 * L::N + L::ro(k, so, 1)];
+            f[7] = west[2 * L::N + L::rn(k, 1)];
+            f[8] = west[L::rn(k, 0)];
+            if (own_row && k == 0) {
+                // the own column's values of the centre row: populations 1, 3
+                // and 5, 6 from the rings, 2 (and phi* in z0) from the
+                // histories, 4, 7, 8 from o4, o7, o8
+                own[0] = 0.f;
+                own[1] = west[L::N + L::rm(0, sm, 0)];
+                own[3] = west[L::N + L::rm(0, sm, 1)];
+                own[5] = west[L::N + L::ro(0, at(U, 1), 0)];
+                own[6] = west[L::N + L::ro(0, at(U, 1), 1)];
+                own[2] = zo[0][at(U, 1)];
+                own[4] = o4[B ^ 1];
+                own[7] = o7[B ^ 1];
+                own[8] = o8[B ^ 1];
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int k = 0; k < S; ++k) {
+            if (IT >= 0 && IT < PER * k + 2) continue;
+            const float(&f)[9] = fp[k][B];
+            float s;
+            if constexpr (own_row) s = k == 0 ? shifted_phi(f[0], f, own) : sum9(f);  // (the collision forms the rest population itself)
+            else s = sum9(f);
+            ph[k][B] = s;
+            own_w[L::ps(k, U % R)] = normal_source<float, MODEL>(s, kcs[k], ab[k][B]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        lds_barrier();
+
+        // ---- updates: stage k on the row 3 k + 2 behind the loaded one, at t + k;
+        // the last stage into HBM.  The psi of every stage is read first.
+        float gx[S], gy[S], pn[S][8];
+#pragma unroll
+        for (int k = S - 1; k >= 0; --k) {
+            if (IT >= 0 && IT < PER * k + 4) continue;
+            const int c0 = L::ps(k, at(U, 1)), cm = L::ps(k, at(U, 2)), cp = L::ps(k, U % R);
+            constexpr int C = L::N, E = 2 * L::N;  // own and east column
+            pn[k][0] = west[E + c0];
+            pn[k][1] = west[c0];
+            pn[k][2] = west[C + cp];
+            pn[k][3] = west[C + cm];
+            pn[k][4] = west[E + cp];
+            pn[k][5] = west[cp];
+            pn[k][6] = west[E + cm];
+            pn[k][7] = west[cm];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int k = S - 1; k >= 0; --k) {
+            if (IT < 0 || IT >= PER * k + 4) {
+                const NodeConst<float>& kc = kcs[k];
+                float Gx, Gy, ob[9];
+                iso_gradient(pn[k][0], pn[k][1], pn[k][2], pn[k][3], pn[k][4], pn[k][5], pn[k][6], pn[k][7], gx[k], gy[k]);
+                const float phi = ph[k][B ^ 1];
+                const float uxr = Ax * rf[k].x, uyr = Bx * rf[k].y;
+                const float phio = P[k][at(U, k == 0 ? 2 : 3)];
+                // (only the first stage can be the run's first step)
+                flux_bracket<float, MODEL>(gx[k], gy[k], phi, ab[k][B ^ 1], k == 0 && kc.first ? phi : phio,
+                                           kc.s_now * uxr, kc.s_now * uyr, kc.s_old * uxr, kc.s_old * uyr, kc, Gx, Gy);
+                collide(fp[k][B ^ 1], phi, kc.s_now * uxr, kc.s_now * uyr, Gx, Gy, kc, ob);
+                if (k < S - 1) {
+                    put(k < S - 1 ? k + 1 : 0, U_, ob);
+                } else {
+                    // non-temporal: a stored row is not read again in this
+                    // launch, while the 2H rows each strip shares with its
+                    // neighbours are (1.5% faster at 8192^2 than plain stores)
+                    io.store_nt(th.act && left > 0, (uint32_t)srow, ob, phi);
+                    srow += spitch;
+                    --left;
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            yk[k] += dir;
+            yk[k] = yk[k] == a.ny ? 0 : (yk[k] < 0 ? a.ny - 1 : yk[k]);
+        }
+    };
+    // two rows of loads in flight: row r + 2 is loaded while row r is processed,
+    // into the register set row r came in
+    float nv[2][9];
+    load(nv[0]);
+    load(nv[1]);
+    unrolled([&](auto I) __attribute__((always_inline)) {
+        body(nv[decltype(I)::value % 2], std::integral_constant<int, decltype(I)::value % Q>{}, I);
+    }, std::make_integer_sequence<int, F>{});
+    // whole periods: a loop left in the middle, or rows after it, would carry
+    // every value through merges
+    do {
+        unrolled([&](auto I) __attribute__((always_inline)) {
+            constexpr int N = F + decltype(I)::value;
+            body(nv[N % 2], std::integral_constant<int, N % Q>{}, std::integral_constant<int, -1>{});
+        }, std::make_integer_sequence<int, Q>{});
+    } while (left > 0);
+}
+
+// The S-step tile with the learned closure (FP32 plain storage, improved
+// model): the march in a loop of two iterations, the rings' places computed
+// from the iteration number (their periods, 3, 4 and 5 rows, have no short
+// common one).
+template <int BX, int S>
+__device__ __forceinline__ void stepS_tile_cl(const StepArgs& a, int x0, int w, int ys, int hh, bool down,
+                                              TileSLds<BX, S>& lds) {
+    using G = StepSGeom<BX, S, true>;
+    constexpr int H = G::H, UL = G::UL, LG = G::LG, PER = G::PER, D = G::D, W = G::W, NPS = G::NPS;
+    const StepSThread th = stepS_thread<ST_PLAIN>(x0, w, H);
+    const int l = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(l) / kWave, cxo = th.cxo;
+    const bool dup = th.dup, act = th.act;
+    // Stage k forms phi/psi validly on the columns (and rows) up to
+    // RC (S - k) - 1 beyond the tile and updates up to RC (S - 1 - k) beyond
+    // it.  Every thread runs every stage (branching on these ranges would only
+    // hold per-lane masks, since every wavefront has lanes inside them):
+    // outside them a thread forms values from rows or columns that are not
+    // valid yet, which no valid value reads.
+    const int gcol = wrap_idx(x0 + cxo, a.nx);
+    const int j = cxo + H + 1;        // LDS column read
+    const int jw = dup ? W - 1 : j;   // LDS column written
+    // A strip marched downward is computed in the mirrored frame y -> -y:
+    // populations are read from and written to the planes of their mirror
+    // images and the y velocity changes sign, so the march always runs
+    // toward +y in the frame the stages see and no value depends on the
+    // direction.  Every node helper rounds mirror-symmetrically (sums in
+    // mirror-invariant order, y components that only change sign), so the
+    // results equal the lattice-frame computation bit for bit.
+    const IoRows<ST_PLAIN> io(a, down);
+    lds_barrier();  // the LDS may still be read by a previous tile of this block
+
+    const int iters = hh + H + D;
+    if (th.idle) {
+        // no column in this wavefront: the loop's two barriers per iteration only
+        for (int it = 0; it < iters; ++it) {
+            lds_barrier();
+            lds_barrier();
+        }
+        return;
+    }
+
+    // FP32 velocity factors: the FP64 table rounded once on the host, as the
+    // one-step kernels round it on the device
+    const float Ax = a.vtabf[gcol];
+    const float Bx = down ? -a.vtabf[a.nx + gcol] : a.vtabf[a.nx + gcol];
+    NodeConst<float> kcs[S];  // stage k, step k of the launch
+#pragma unroll
+    for (int k = 0; k < S; ++k) kcs[k] = NodeConst<float>(a, k);
     // pulled populations and phi of stage k, ping-pong by iteration parity:
     // the pull of iteration it fills half it & 1, the update of iteration
     // it + UL reads it (with UL = 2 through fh, which keeps the pull of two
     // iterations ago before the half is refilled)
-    float fp[S][2][9], ph[S][2], ob[9];
-    float fh[CL ? S : 1][9];
-    float phl = 0.f;  // phi of the last stage's updated node (the shifted store's phi*)
+    float fp[S][2][9], ob[9];
+    float fh[S][9];
     // Histories, index = age in iterations (0: this iteration).  P[k]: the sum
     // of stage k's input populations at the own node (phi(t + k - 1) as the
     // one-step kernel forms it); z0, zo, zn: the own column's c_x = 0 inputs
     // of stage k (population 0, the old-row one, the new-row one).
     float P[S][G::NP], z0[S][4], zo[S][4], zn[S][4];
-    // shifted storage: the own column's populations 7 and 8 of stage 0's last
-    // two input rows (the rings keep them only where another column pulls them)
-    float o7[2] = {0.f, 0.f}, o8[2] = {0.f, 0.f};
-    constexpr bool kSh = IoT::kShifted;
 #pragma unroll
     for (int k = 0; k < S; ++k) {
 #pragma unroll
         for (int b = 0; b < 2; ++b) {
-            ph[k][b] = 0.f;
 #pragma unroll
             for (int q = 0; q < 9; ++q) fp[k][b][q] = 0.f;
         }
@@ -1220,7 +1640,7 @@ __device__ __forceinline__ void stepS_tile_lds(const StepArgs& a, int x0, int w,
         for (int d = 0; d < 4; ++d) z0[k][d] = zo[k][d] = zn[k][d] = 0.f;
     }
 #pragma unroll
-    for (int k = 0; k < (CL ? S : 1); ++k)
+    for (int k = 0; k < S; ++k)
 #pragma unroll
         for (int q = 0; q < 9; ++q) fh[k][q] = 0.f;
 #pragma unroll
@@ -1233,13 +1653,7 @@ __device__ __forceinline__ void stepS_tile_lds(const StepArgs& a, int x0, int w,
     auto row_of = [&](int it) { return (uint32_t)wrap_idx(raw_row(min(it, hh + 2 * H - 1)), a.ny); };
     // a stage's input into its ring and histories (v: populations at the own column)
     auto put = [&](int k, int s3, int s2, const float(&v)[9]) __attribute__((always_inline)) {
-        // phi at t + k - 1: the sum of the stage's input values (phi* itself
-        // for stage 0's shifted input)
-        P[k][0] = kSh && k == 0 ? v[0] : sum9(v);
-        if (kSh && k == 0) {
-            o7[0] = v[7];
-            o8[0] = v[8];
-        }
+        P[k][0] = sum9(v);  // phi at t + k - 1
         lds.ro[k][s3][0][jw] = v[5];
         lds.ro[k][s3][1][jw] = v[6];
         lds.rm[k][s2][0][jw] = v[1];
@@ -1254,7 +1668,7 @@ __device__ __forceinline__ void stepS_tile_lds(const StepArgs& a, int x0, int w,
         constexpr int B = decltype(parity)::value;  // it & 1
         const int Rr = raw_row(it);
         const int s3 = it % 3, s2 = B;
-        const int sps = CL ? it % NPS : s3;  // psi slot of this iteration's phi row
+        const int sps = it % NPS;  // psi slot of this iteration's phi row
         // ---- row R into stage 0's ring
         put(0, s3, s2, nv);
         io.load(row_of(it + 2) * (uint32_t)a.pitch + (uint32_t)gcol, nv);
@@ -1267,10 +1681,8 @@ __device__ __forceinline__ void stepS_tile_lds(const StepArgs& a, int x0, int w,
 #pragma unroll
         for (int k = 0; k < S; ++k) {
             const int lag = k == 0 ? 0 : 1;
-            if constexpr (CL) {
 #pragma unroll
-                for (int q = 0; q < 9; ++q) fh[k][q] = fp[k][B][q];
-            }
+            for (int q = 0; q < 9; ++q) fh[k][q] = fp[k][B][q];
             if (it >= PER * k + 2) {
                 const int so = (it + 1 + 2 * lag) % 3;  // old pair: it - 2 - lag
                 const int sm = B ^ 1 ^ lag;             // populations 1, 3: it - 1 - lag
@@ -1284,28 +1696,9 @@ __device__ __forceinline__ void stepS_tile_lds(const StepArgs& a, int x0, int w,
                 f[6] = lds.ro[k][so][1][j + 1];
                 f[7] = lds.rn[k][1][j + 1];
                 f[8] = lds.rn[k][0][j - 1];
-                float s;
-                if (kSh && k == 0) {
-                    // the own column's values of the centre row: populations 1, 3
-                    // and 5, 6 from the rings, 2, 4 (and phi* in z0) from the
-                    // histories, 7, 8 from o7, o8
-                    float own[9];
-                    own[0] = 0.f;
-                    own[1] = lds.rm[0][sm][0][j];
-                    own[3] = lds.rm[0][sm][1][j];
-                    own[5] = lds.ro[0][(it + 2) % 3][0][j];
-                    own[6] = lds.ro[0][(it + 2) % 3][1][j];
-                    own[2] = zo[0][1];
-                    own[4] = zn[0][1];
-                    own[7] = o7[1];
-                    own[8] = o8[1];
-                    s = shifted_phi(z0[0][1], f, own);  // the collision forms the rest population itself
-                } else {
-                    s = sum9(f);
-                }
-                ph[k][B] = s;
-                lds.ps[k][sps][jw] = normal_source<float, MODEL>(s, kcs[k]);
-                if constexpr (CL) lds.phr[k][it % 5][jw] = s;
+                const float s = sum9(f);
+                lds.ps[k][sps][jw] = normal_source<float, MODEL_IMPROVED>(s, kcs[k]);
+                lds.phr[k][it % 5][jw] = s;
             }
         }
         lds_barrier();
@@ -1332,32 +1725,25 @@ __device__ __forceinline__ void stepS_tile_lds(const StepArgs& a, int x0, int w,
                 float gx, gy, Gx, Gy;
                 iso_gradient(ps[c0][j + 1], ps[c0][j - 1], ps[cp][j], ps[cm][j], ps[cp][j + 1], ps[cp][j - 1],
                              ps[cm][j + 1], ps[cm][j - 1], gx, gy);
-                float phi;
-                if constexpr (CL) phi = lds.phr[k][(it + 3) % 5][j];  // phi row it - 2
-                else phi = ph[k][B ^ 1];
+                const float phi = lds.phr[k][(it + 3) % 5][j];  // phi row it - 2
                 const float uxr = Ax * row_factor(a.vtabf, 2 * a.nx + y);
                 const float uyr = Bx * row_factor(a.vtabf, 2 * a.nx + a.ny + y);
                 const float phio = P[k][(k == 0 ? 1 : 2) + UL];
-                flux_bracket<float, MODEL>(gx, gy, phi, kc.first ? phi : phio, kc.s_now * uxr, kc.s_now * uyr,
+                flux_bracket<float, MODEL_IMPROVED>(gx, gy, phi, kc.first ? phi : phio, kc.s_now * uxr, kc.s_now * uyr,
                                            kc.s_old * uxr, kc.s_old * uyr, kc, Gx, Gy);
-                if constexpr (CL) {
-                    collide(fh[k], phi, kc.s_now * uxr, kc.s_now * uyr, Gx, Gy, kc, ob);
-                    // interface-band nodes among those stage k must update (the
-                    // condition of the one-step path's band mask); their
-                    // correction is added after the last stage (below)
-                    const int reach = G::RC * (S - 1 - k);
-                    const int rel = it - H - (LG * k + 1 + UL);  // row relative to the strip, march frame
-                    const bool need = !dup && cxo >= -reach && cxo < w + reach && rel >= -reach && rel < hh + reach;
-                    const float pc = clip01(phi);
-                    bms[k] = __ballot(need && pc > a.cl_theta && pc < 1.0f - a.cl_theta);
-                } else {
-                    collide(fp[k][B ^ 1], phi, kc.s_now * uxr, kc.s_now * uyr, Gx, Gy, kc, ob);
-                }
+                collide(fh[k], phi, kc.s_now * uxr, kc.s_now * uyr, Gx, Gy, kc, ob);
+                // interface-band nodes among those stage k must update (the
+                // condition of the one-step path's band mask); their
+                // correction is added after the last stage (below)
+                const int reach = G::RC * (S - 1 - k);
+                const int rel = it - H - (LG * k + 1 + UL);  // row relative to the strip, march frame
+                const bool need = !dup && cxo >= -reach && cxo < w + reach && rel >= -reach && rel < hh + reach;
+                const float pc = clip01(phi);
+                bms[k] = __ballot(need && pc > a.cl_theta && pc < 1.0f - a.cl_theta);
                 if (!last) put(k + 1, s3, s2, ob);
-                else phl = phi;
             }
         }
-        if constexpr (CL) {
+        {
             // The network on every stage's band nodes of this wavefront, packed
             // into one list (stage by stage, lanes in order), from stage k's
             // phi ring (rows it - 4 .. it; the updated row is it - 2), and its
@@ -1424,10 +1810,8 @@ __device__ __forceinline__ void stepS_tile_lds(const StepArgs& a, int x0, int w,
         // non-temporal: a stored row is not read again in this launch, while
         // the 2H rows each strip shares with its neighbours are (1.5% faster
         // at 8192^2 than plain stores)
-        io.store_nt(st, (uint32_t)yl * (uint32_t)a.pitch + (uint32_t)(x0 + cxo), ob, phl);
+        io.store_nt(st, (uint32_t)yl * (uint32_t)a.pitch + (uint32_t)(x0 + cxo), ob, 0.f);
         // ---- age the histories by one iteration
-        o7[1] = o7[0];
-        o8[1] = o8[0];
 #pragma unroll
         for (int k = 0; k < S; ++k) {
 #pragma unroll
@@ -1451,27 +1835,32 @@ __device__ __forceinline__ void stepS_tile_lds(const StepArgs& a, int x0, int w,
     }
 }
 
-template <int MODEL, int BX, int S, int ST>
-__global__ __launch_bounds__((stepS_threads<BX, S>())) void stepS_kernel_lds(StepArgs a) {
-    __shared__ TileSLds<BX, S> lds;
+// Tiles of a.tile_w <= 320 columns; LDS by the launch, so that narrow tiles do
+// not hold the widest one's.  Three wavefronts per SIMD at S = 3 (168
+// registers), four at S = 2 (128).
+constexpr int kStepSMaxBx = 320;
+template <int MODEL, int S, int ST>
+__global__ __launch_bounds__((stepS_threads<kStepSMaxBx, S>())) __attribute__((amdgpu_waves_per_eu(S == 2 ? 4 : 3))) void
+stepS_kernel_lds(StepArgs a) {
+    extern __shared__ float stepS_lds[];
     const int ntile = a.nbx * a.nby;
     const int tile = xcd_tile(blockIdx.x, ntile, a.n_xcd);
     const int bxi = tile % a.nbx, syi = tile / a.nbx;
-    const int x0 = bxi * BX, ys = syi * a.strip_h;
-    stepS_tile_lds<MODEL, BX, S, ST>(a, x0, min(BX, a.nx - x0), ys, min(a.strip_h, a.ny - ys), 0, (syi & 1) != 0, lds);
+    const int x0 = bxi * a.tile_w, ys = syi * a.strip_h;
+    stepS_tile_lds<MODEL, S, ST>(a, x0, min(a.tile_w, a.nx - x0), a.tile_w, ys, min(a.strip_h, a.ny - ys), 0,
+                                 (syi & 1) != 0, stepS_lds);
 }
 
 // The S-step kernel with the learned closure (FP32 storage, improved model).
 template <int BX, int S>
 __global__ __launch_bounds__((stepS_threads<BX, S, true>())) __attribute__((amdgpu_waves_per_eu(2, 2))) void
 stepS_kernel_cl(StepArgs a) {
-    __shared__ TileSLds<BX, S, true> lds;
+    __shared__ TileSLds<BX, S> lds;
     const int ntile = a.nbx * a.nby;
     const int tile = xcd_tile(blockIdx.x, ntile, a.n_xcd);
     const int bxi = tile % a.nbx, syi = tile / a.nbx;
     const int x0 = bxi * BX, ys = syi * a.strip_h;
-    stepS_tile_lds<MODEL_IMPROVED, BX, S, ST_PLAIN, false, true>(a, x0, min(BX, a.nx - x0), ys,
-                                                                 min(a.strip_h, a.ny - ys), 0, (syi & 1) != 0, lds);
+    stepS_tile_cl<BX, S>(a, x0, min(BX, a.nx - x0), ys, min(a.strip_h, a.ny - ys), (syi & 1) != 0, lds);
 }
 
 // ---------------------------------------------------------------------------
