@@ -112,8 +112,8 @@ int lbac_init_device(const lbac_params* p, const double* phi0_device, lbac_ctx**
 /* Releases every resource of the context (NULL is allowed). */
 int lbac_free(lbac_ctx* h);
 
-/* Advances n >= 0 steps of Eq. (9) (one fused collide-and-stream kernel per
- * step) on the context's stream; t += n.  Asynchronous: a device error may
+/* Advances n >= 0 steps of Eq. (9) (fused collide-and-stream kernels of one
+ * or several steps each) on the context's stream; t += n.  Asynchronous: a device error may
  * surface here or at the next synchronising call. */
 int lbac_step(lbac_ctx* h, int64_t n);
 
@@ -151,15 +151,19 @@ int lbac_set_state(lbac_ctx* h, const void* buf, size_t bytes);
  * LBAC_KERNEL_FUSED2 and LBAC_KERNEL_FUSED3 (FP32 collision: LBAC_F32 or a
  * 16-bit storage): one launch takes S = 2 or 3 steps, the populations
  * between them kept in LDS (the block layout; step k of S is computed on the
- * tile grown by RC (S - 1 - k) columns and rows on each side, RC = 2, or 3
- * with the closure, whose network reads a 5x5 neighbourhood), so HBM is read
+ * tile grown by 2 (S - 1 - k) columns and rows on each side), so HBM is read
  * and written once per S steps; their tiles are bx = 64, 96, 128, ..., 320
- * columns (any multiple of 32 in that range, and 240; with the closure 128,
- * 160, 192 or 224, another width running those launches at 224), the block
- * being the bx + 2 RC S grown columns rounded up to whole wavefronts; a step count
+ * columns (any multiple of 32 in that range, and 240), the block being the
+ * bx + 4 S grown columns rounded up to whole wavefronts, and their strips
+ * strip_h rounded to the nearest whole period of the march (4 rows at S = 2,
+ * 6 at S = 3, at least one); a step count
  * that is not a multiple of S ends with one-step launches (bx 256 where bx
  * is not 64, 128 or 256).  With the closure and the conventional model every
  * step is a one-step launch.  strip_h: rows each tile marches (>= 1).
+ * Until a shape is set, or chosen by lbac_autotune, launches follow the
+ * grid's size: patches of nodes advanced several steps in LDS where the grid
+ * is too small to fill the GPU with strips, else strips; lbac_get_launch then
+ * reports the one-step shape the context was created with.
  * Results do not depend on the shape or variant (bitwise; the 16-bit
  * storage forms round once per launch, so there they depend on S only).
  * LBAC_EINVAL for unsupported values. */
@@ -173,7 +177,8 @@ int lbac_get_launch(lbac_ctx* h, int32_t* variant, int32_t* bx, int32_t* strip_h
 
 /* Times every supported launch shape (variant; bx; strip_h among the
  * multiples of 8 up to 256, 512 and ceil(ny / k) for k = 1..32) over `steps`
- * launches each (state is left unchanged) and keeps the fastest per step;
+ * launches each (state is left unchanged), and what launches do with no shape
+ * set, and keeps the fastest per step;
  * *us_per_step (may be NULL) gets its time per step. */
 int lbac_autotune(lbac_ctx* h, int32_t steps, double* us_per_step);
 
@@ -189,13 +194,14 @@ int lbac_set_graph_chunk(lbac_ctx* h, int32_t chunk);
  * correction c that is added to the sharpening flux S n of Eq. (11).  The
  * collision is linear in G, so the correction changes a band node's
  * post-collision populations by (1 - 1/(2 tau)) w_i (c_i . c).  With
- * LBAC_KERNEL_FUSED2 / _FUSED3 (improved model) the multi-step kernel
- * evaluates the network inside each of its steps, on the band nodes of the
- * rows it updates, from the phi rows it keeps in LDS.  One-step launches run
- * the block-variant step kernel (which records the band), a scan that lists
- * the band nodes and a pass that adds the correction at those nodes.  Both
- * give the same results bit for bit.  Needs device memory for nx * ny list
- * entries.
+ * LBAC_KERNEL_FUSED2 / _FUSED3 (improved model) a launch takes its steps
+ * without the network and marks the patches of nodes whose result it can
+ * change; those are then recomputed with the network, several steps at a
+ * time in LDS, from the launch's input, which the step leaves in place.
+ * One-step launches run the block-variant step kernel (which records the
+ * band), a scan that lists the band nodes and a pass that adds the correction
+ * at those nodes.  Both give the same results bit for bit.  Needs device
+ * memory for nx * ny list entries.
  * params == NULL switches the closure off.  LBAC_EINVAL for another
  * precision, a batch instance, theta outside [0, 0.5) or non-finite
  * parameters. */

@@ -71,6 +71,7 @@ void release(lbac_ctx* h) {
     dev_free(h, h->cl_mask);
     dev_free(h, h->cl_list);
     dev_free(h, h->cl_count);
+    dev_free(h, h->cl_flags);
     if (h->host5) (void)hipHostFree(h->host5);
     if (h->own_stream && h->stream) (void)hipStreamDestroy(h->stream);
 }
@@ -172,6 +173,13 @@ StepArgs lbac_host::make_args(const lbac_ctx* h, int src, int32_t k) {
     a.cl_theta = h->cl_theta;
     a.cl_mask = h->closure ? h->cl_mask : nullptr;
     a.cl_words = h->cl_words;
+    if (h->closure) {
+        // a b at theta less far more than the FP32 rounding of phi, delta and the product
+        a.cl_ab = (float)((h->cl_theta + a.delta) * (1.0 - h->cl_theta + a.delta) * (1.0 - 1e-5)) - 1e-7f;
+        a.cl_flags = h->cl_flags;
+        a.cl_list = h->cl_list;
+        a.cl_count = h->cl_count;
+    }
     return a;
 }
 
@@ -294,39 +302,10 @@ int launch_steps_of(const lbac_ctx* h) {
     return h->variant == LBAC_KERNEL_FUSED2 ? 2 : (h->variant == LBAC_KERNEL_FUSED3 ? 3 : 1);
 }
 
-// Tile widths of the S-step kernels with the closure; another width set by
-// lbac_set_launch runs these launches at 224 columns (the results do not
-// depend on the tile width).
-int closure_stepS_bx(int bx) { return bx == 128 || bx == 160 || bx == 192 || bx == 224 ? bx : 224; }
-
-template <int S, int BX>
-hipError_t launch_stepS_cl_shape(StepArgs a, hipStream_t s) {
-    a.nbx = (a.nx + BX - 1) / BX;
-    const dim3 grid(a.nbx * a.nby);
-    hipLaunchKernelGGL((stepS_kernel_cl<BX, S>), grid, dim3(stepS_threads<BX, S, true>()), 0, s, a);
-    return hipGetLastError();
-}
-
-template <int S>
-hipError_t launch_stepS_cl(StepArgs a, int bx, hipStream_t s) {
-    a.nby = (a.ny + a.strip_h - 1) / a.strip_h;
-    a.n_xcd = kXcds;
-    switch (closure_stepS_bx(bx)) {
-    case 128:
-        return launch_stepS_cl_shape<S, 128>(a, s);
-    case 160:
-        return launch_stepS_cl_shape<S, 160>(a, s);
-    case 192:
-        return launch_stepS_cl_shape<S, 192>(a, s);
-    default:
-        return launch_stepS_cl_shape<S, 224>(a, s);
-    }
-}
-
 // One S-step launch with tiles of bx columns, in strips of whole periods of the
 // kernel's march, which runs whole periods (the multiple nearest to the height
 // asked for).
-template <int MODEL, int S, int ST>
+template <int MODEL, int S, int ST, bool BAND = false>
 hipError_t launch_stepS_m(StepArgs a, int bx, hipStream_t s) {
     using L = TileSRows<S>;
     constexpr int Q = L::kPeriod;
@@ -336,7 +315,7 @@ hipError_t launch_stepS_m(StepArgs a, int bx, hipStream_t s) {
     a.tile_w = bx;
     a.nbx = (a.nx + bx - 1) / bx;
     const dim3 grid(a.nbx * a.nby), block((bx + 4 * S + 63) / 64 * 64);
-    hipLaunchKernelGGL((stepS_kernel_lds<MODEL, S, ST>), grid, block, L::bytes(bx), s, a);
+    hipLaunchKernelGGL((stepS_kernel_lds<MODEL, S, ST, BAND>), grid, block, L::bytes(bx), s, a);
     return hipGetLastError();
 }
 
@@ -353,8 +332,7 @@ hipError_t launch_stepS_st(const lbac_ctx* h, const StepArgs& a, int S) {
 // Steps k .. k + S - 1 of the current run in one launch, from pop[src] into pop[1 - src].
 hipError_t launch_stepS(const lbac_ctx* h, int src, int32_t k, int S) {
     const StepArgs a = make_args(h, src, k);
-    if (h->closure)
-        return S == 3 ? launch_stepS_cl<3>(a, h->bx, h->stream) : launch_stepS_cl<2>(a, h->bx, h->stream);
+    if (h->closure) return launch_split(h, a, S);
     switch (h->p.precision) {
     case LBAC_F32_F16STORE:
         return launch_stepS_st<ST_F16>(h, a, S);
@@ -375,11 +353,14 @@ struct Launch {
 // The default shape of the strip kernels, for grids the patch kernels leave to
 // them, and an estimate of its time per step in microseconds (as PatchPlan's).
 //
-// Three steps per launch (FP32 storage): 224 columns and the strip height
-// whose tiles fill whole rounds of the 768 workgroups the device keeps
-// resident best, ceil(tiles / 768) (strip + 14) rows: 28 rows at 2048^2, 48 at
-// 3001 x 2210, 40 at 8192^2 (29.8, 44.6 and 355 us per step; strips of 40 took
-// 37 and 46 on the first two, the best of 60 shapes 29.3 and 42.7).
+// Three steps per launch (FP32 storage): 224 columns and the strip height of
+// the least estimate.  A strip costs its rows and the pipeline's 14, each 0.35
+// us where every CU has one tile at most, 0.455 with two, 0.65 with three (the
+// device's 768 at once), beyond that 0.62 per round of 768, a started round
+// counting half; never less than the state read and written once at 4.76 TB/s.
+// Measured with the chosen strips: 17.5 us per step at 1536^2 (24 rows), 25.4
+// at 2048^2 (42; 30 rows 27.2, 48 27.3), 37.8 at 3001 x 2210 (42), 93.5 at
+// 4096^2 and 341 at 8192^2 (42); the best of 72 shapes 16.5, 25.4, 36.6, 91.4.
 //
 // One step: strips of such a height that about 1024 tiles, four per CU, share
 // the device: 256-column tiles at 16-bit storage ran at 17.9, 27.0, 38.6, 74
@@ -393,15 +374,19 @@ float default_strips(const lbac_ctx* h, bool three, int& variant, int& bx, int& 
         variant = LBAC_KERNEL_FUSED3;
         bx = 224;
         const int64_t nbx = (nx + bx - 1) / bx;
-        int64_t best = INT64_MAX;
-        for (int sh = 24; sh <= 64; sh += 4) {
-            const int64_t c = (nbx * ((ny + sh - 1) / sh) + 767) / 768 * (sh + 14);
-            if (c < best) {
-                best = c;
+        float best = 1e30f;
+        for (int sh : {42, 36, 48, 30, 54, 24, 60, 18, 12}) {
+            const int64_t tiles = nbx * ((ny + sh - 1) / sh), rounds = (tiles + 767) / 768;
+            const float row = tiles <= 256 ? 0.35f : (tiles <= 512 ? 0.455f : (tiles <= 768 ? 0.65f
+                              : 0.31f * ((float)tiles / 768.f + (float)rounds)));
+            const float us = std::max(row * (float)(sh + 14), 5.04f * mnodes);
+            if (us < best) {
+                best = us;
                 strip_h = std::min(sh, ny);
             }
         }
-        return h->closure ? 120.f + 13.f * mnodes : 0.7f * (float)best;
+        // with the closure: the marks, their list, and the marked patches of an interface across the grid
+        return h->closure ? best + 15.f + 3.f * std::sqrt(mnodes) : best;
     }
     variant = LBAC_KERNEL_BLOCK;
     bx = default_bx(nx);
@@ -535,6 +520,11 @@ int validate(const lbac_params* p, std::string& why) {
 }
 
 }  // namespace
+
+hipError_t lbac_host::launch_stepS_band(int S, StepArgs a, int bx, hipStream_t s) {
+    return S == 3 ? launch_stepS_m<MODEL_IMPROVED, 3, ST_PLAIN, true>(a, bx, s)
+                  : launch_stepS_m<MODEL_IMPROVED, 2, ST_PLAIN, true>(a, bx, s);
+}
 
 int lbac_host::create(const lbac_params* p, const double* phi0, bool phi0_on_device, lbac_ctx** out) {
     if (!out) return LBAC_EINVAL;
@@ -921,7 +911,6 @@ int lbac_autotune(lbac_ctx* h, int32_t steps, double* us_per_step) {
         const int S = var == LBAC_KERNEL_FUSED2 ? 2 : (var == LBAC_KERNEL_FUSED3 ? 3 : 1);
         if (bx > 64 && bx / 2 >= h->p.nx) continue;
         if (S == 1 ? !one_step_bx(bx) : !stepS_bx(bx)) continue;
-        if (S > 1 && h->closure && closure_stepS_bx(bx) != bx) continue;
         for (int sh : hs) {
             h->variant = var;
             h->bx = bx;
@@ -999,8 +988,11 @@ int lbac_set_closure(lbac_ctx* h, const float* params, float theta) {
         h->cl_mask = (uint64_t*)dev_alloc(h, sizeof(uint64_t) * (size_t)h->cl_words * h->p.ny);
         h->cl_list = (int32_t*)dev_alloc(h, sizeof(int32_t) * (size_t)h->p.nx * h->p.ny);
         h->cl_count = (uint32_t*)dev_alloc(h, 256);
-        if (!h->cl_param || !h->cl_w || !h->cl_b || !h->cl_mask || !h->cl_list || !h->cl_count)
+        const size_t marks = (mark_count(h->p.nx, h->p.ny) + 7) / 8 * 8;
+        h->cl_flags = (uint8_t*)dev_alloc(h, marks);
+        if (!h->cl_param || !h->cl_w || !h->cl_b || !h->cl_mask || !h->cl_list || !h->cl_count || !h->cl_flags)
             return fail(h, LBAC_ENOMEM, "closure buffers");
+        HIPCHK(h, hipMemsetAsync(h->cl_flags, 0, marks, h->stream));
     }
     HIPCHK(h, hipMemcpyAsync(h->cl_param, params, sizeof(float) * LBAC_MLP_NPARAM, hipMemcpyHostToDevice, h->stream));
     hipLaunchKernelGGL(closure_pack_kernel, dim3((64 * 64 + 255) / 256), dim3(256), 0, h->stream, h->cl_param, h->cl_w,

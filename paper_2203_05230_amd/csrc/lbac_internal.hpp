@@ -70,8 +70,9 @@ struct lbac_ctx {
     uint16_t* cl_w = nullptr;    // packed BF16 weights
     float* cl_b = nullptr;       // padded biases
     uint64_t* cl_mask = nullptr;  // band masks written by the step kernel
-    int32_t* cl_list = nullptr;   // band node list (up to nx * ny entries)
+    int32_t* cl_list = nullptr;   // band node list (up to nx * ny entries), or the marked patches
     uint32_t* cl_count = nullptr; // entries in cl_list
+    uint8_t* cl_flags = nullptr;  // marks of the two-pass launches, a byte per patch, zero between launches
     int32_t cl_words = 0;         // mask words per row
     std::string err;
 };
@@ -92,6 +93,11 @@ struct PatchPlan {
 float state_bytes(const lbac_ctx* h);  // stored bytes per node
 PatchPlan plan_patch(const lbac_ctx* h, int64_t left);  // the best shape of at most `left` steps
 hipError_t launch_patch(const lbac_ctx* h, int src, int32_t k, const PatchPlan& p);
+
+// The closure's two-pass launches (strips, then the marked patches with the network).
+hipError_t launch_split(const lbac_ctx* h, const lbac::StepArgs& a, int S);
+hipError_t launch_stepS_band(int S, lbac::StepArgs a, int bx, hipStream_t s);  // the strips, marking
+size_t mark_count(int nx, int ny);                                             // marks at most
 
 int create(const lbac_params* p, const double* phi0, bool phi0_on_device, lbac_ctx** out);
 void destroy(lbac_ctx* h);

@@ -84,6 +84,11 @@ struct StepArgs {
     const float* cl_b;      // learned closure: biases b1[64], b2[64], b3[32] (rows >= 2 zero)
     float cl_theta;         // closure band: theta < clip(phi) < 1 - theta
     uint64_t* cl_mask;      // closure: band mask, one 64-bit word per 64 columns of a row, or null
+    float cl_ab;            // closure: (phi_c + delta)(1 - phi_c + delta) above this wherever phi is in the band
+    uint8_t* cl_flags;      // closure: a mark per patch of the two-pass launch, cl_npx patches to a row
+    int32_t cl_npx;
+    const int32_t* cl_list; // closure: the marked patches
+    uint32_t* cl_count;     // entries in cl_list
     int32_t cl_words;       // words per row of cl_mask
 };
 
@@ -926,8 +931,8 @@ __global__ __launch_bounds__(block_threads<BX>()) void step_kernel_lds(StepArgs 
 // [row 16][8], W3 [ks 2][g 4][row 16][8] (rows 2..15 zero).  Each output
 // column depends on its own sample only, so a node's correction is the same
 // whichever nodes share its wavefront.  The small tiles keep the registers
-// the network needs (about forty) low enough for it to run inside the
-// multi-step kernel's loop.
+// the network needs (about forty) low enough for it to run inside the patch
+// kernel.
 constexpr int kClW1 = 0, kClW2 = kClW1 + 64 * 32, kClW3 = kClW2 + 64 * 64, kClWN = kClW3 + 16 * 64;
 constexpr int kClB1 = 0, kClB2 = 64, kClB3 = 128, kClBN = 160;
 
@@ -943,12 +948,9 @@ struct ClosureLds {
     uint16_t x[kClWaves][kWave * 32];  // each wavefront's stencils, one row of 32 BF16 per sample
 };
 
-__device__ __forceinline__ uint16_t bf16_bits(float f) {
-    // round to nearest even (inputs are finite)
-    uint32_t u = __builtin_bit_cast(uint32_t, f);
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return (uint16_t)(u >> 16);
-}
+// BF16 by rounding to nearest even: gfx950's own conversion (two values to an
+// instruction; four integer instructions each otherwise)
+__device__ __forceinline__ uint16_t bf16_bits(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
 
 // tanh form of GELU, tanh(u) = 1 - 2 / (exp(2u) + 1) with the hardware exp2
 __device__ __forceinline__ float gelu_fast(float x) {
@@ -1055,42 +1057,6 @@ __device__ __forceinline__ void closure_correct(float (&f)[9], float phi, float 
     f[0] = phi - sum_moving(f);
 }
 
-// The network on up to 64 listed nodes whose inputs lie in rings of five phi
-// rows in LDS (the S-step kernel with the closure): entry s of `tab`
-// (s < count) names a node by its ring (high 16 bits: which of the rings,
-// `ring_stride` floats apart) and its column in the ring rows (low 16 bits);
-// ring row (base + d) % 5 holds phi of the row d rows ahead of the nodes' row
-// in the frame the rings are filled in (mirror: the lattice's y axis
-// reversed).  Lane s returns the correction (cx, cy) of node s.
-__device__ __forceinline__ float2 closure_mlp_list(const uint16_t* w, const float* b, const float* rings,
-                                                   int ring_stride, int row_len, int base, bool mirror,
-                                                   const int* tab, int count) {
-    const int lane = threadIdx.x % kWave, hf = lane / 16;
-    auto xfrag = [&](int nt) {
-        const int s = 16 * nt + lane % 16;
-        const bool on = s < count;
-        const int ent = on ? tab[s] : 0;
-        const float* ring = rings + (ent >> 16) * ring_stride;
-        const int jc = ent & 0xffff;
-        u16x8_t v;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const int kk = 8 * hf + e;
-            float x = 0.f;
-            if (on && kk < 25) {
-                const int dy = kk / 5 - 2, dx = kk % 5 - 2;
-                x = ring[((base + (mirror ? -dy : dy)) % 5) * row_len + jc + dx];
-            }
-            v[e] = bf16_bits(x);
-        }
-        return __builtin_bit_cast(bf16x8_t, v);
-    };
-    const uint64_t want = count >= 64 ? ~0ull : (1ull << count) - 1ull;
-    float2 c;
-    closure_mlp(w, b, xfrag, want, c.x, c.y);
-    return c;
-}
-
 // Stages the packed closure weights into LDS (all threads of the block).
 __device__ __forceinline__ void closure_stage(const StepArgs& a, ClosureLds& L) {
     const uint32_t* src = reinterpret_cast<const uint32_t*>(a.cl_w);
@@ -1149,19 +1115,13 @@ static __global__ void closure_pack_kernel(const float* __restrict__ p, uint16_t
 // intermediate steps keep them in FP32 in LDS), so that form rounds to its
 // storage precision once per launch.
 //
-// With the learned closure (CL; FP32 storage) a stage also evaluates the
-// network on the interface-band nodes of the row it updates and adds its
-// correction to their post-collision populations exactly as the one-step
-// path's correction pass does, so the results are again those of S one-step
-// launches bit for bit.  The network reads the 5x5 neighbourhood of phi, so
-// a stage reaches RC = 3 columns and rows, keeps its last five phi rows in
-// LDS, and updates a row UL = 2 rows behind the one it forms phi on (the
-// plain stages: UL = 1).
+// With the learned closure (FP32 storage) the launch also marks where the
+// network has work (BAND below), and patches there are recomputed with it.
 //
 // Rows at iteration it (dir = +1 up the strip, -1 down it): row R enters
-// stage 0's ring; stage k forms phi and psi on R - (LG k + 1) dir and updates
-// R - (LG k + 1 + UL) dir, LG = UL + 2.  Two LDS barriers per iteration, as
-// in the one-step kernel.
+// stage 0's ring; stage k forms phi and psi on R - (3 k + 1) dir and updates
+// R - (3 k + 2) dir.  Two LDS barriers per iteration, as in the one-step
+// kernel.
 //
 // Rings.  A pull f_i(x, c) = f*_i(x - c_i) needs another thread's column only
 // for the six populations with c_x != 0, and each of those only from one
@@ -1169,41 +1129,21 @@ static __global__ void closure_pack_kernel(const float* __restrict__ p, uint16_t
 // direction (the "old" pair 5, 6; the march runs toward +y in the frame the
 // stages see) or the row ahead (the "new" pair 8, 7).  So the rings hold,
 // per pair, as many rows as the pull is late; the three populations with
-// c_x = 0 stay in the thread's registers.  Pairs are stored c_x = +1 first.  Index j <-> column
-// x0 - H - 1 + j; indices 0 and W - 1 are padding, so that every thread's
-// reads at j - 1 and j + 1 stay inside its row, and W - 1 also takes the
-// writes of threads past the grown tile.
-template <int BX, int S, bool CL>
+// c_x = 0 stay in the thread's registers.  Pairs are stored c_x = +1 first.
+template <int S>
 struct StepSGeom {
-    static constexpr int RC = CL ? 3 : 2;      // columns and rows one stage reaches
-    static constexpr int H = RC * S;           // halo columns (and shared rows) on each side
-    static constexpr int UL = CL ? 2 : 1;      // rows from a stage's phi row back to the row it updates
-    static constexpr int LG = UL + 2;          // rows between consecutive stages
-    static constexpr int PER = 3 + 2 * UL;     // iterations between consecutive stages' first values
-    static constexpr int D = LG * (S - 1) + 1 + UL;  // rows from the loaded row back to the stored one
-    static constexpr int W = BX + 2 * H + 2;   // LDS row length
-    static constexpr int NPS = UL + 2;         // psi rows kept per stage
-    static constexpr int NP = UL + 3;          // depth of the phi(t - 1) history
-};
-
-// LDS of the S-step tile with the closure: a row per value.
-template <int BX, int S>
-struct TileSLds {
-    static constexpr int W = StepSGeom<BX, S, true>::W;
-    float ro[S][3][2][W];                          // input of stage k: old pair, three rows
-    float rm[S][2][2][W];                          // populations 1 and 3, two rows
-    float rn[S][2][W];                             // new pair, one row
-    float ps[S][StepSGeom<BX, S, true>::NPS][W];   // psi of stage k on its last rows
-    float phr[S][5][W];                            // phi of stage k on its last five rows
-    int tab[(BX + 6 * S + 63) / 64][S * 64];       // per wavefront: the band nodes of an iteration
+    static constexpr int H = 2 * S;              // halo columns (and shared rows) on each side
+    static constexpr int PER = 5;                // iterations between consecutive stages' first values
+    static constexpr int F = PER * (S - 1) + 4;  // iterations before the first stored row
+    static_assert(F == H + 3 * (S - 1) + 2, "the halo's rows and the pipeline's depth");
 };
 
 // Threads of an S-step tile of at most BX columns: the BX + 2H columns of the
 // grown tile rounded up to whole wavefronts (enough for the layout below at
 // every tile width up to BX).
-template <int BX, int S, bool CL = false>
+template <int BX, int S>
 __host__ __device__ constexpr int stepS_threads() {
-    return (BX + 2 * StepSGeom<BX, S, CL>::H + 63) / 64 * 64;
+    return (BX + 2 * StepSGeom<S>::H + 63) / 64 * 64;
 }
 
 // LDS of the S-step tile: per column the values its neighbours read, all
@@ -1306,14 +1246,26 @@ struct RowWalk {
 // tiles: 21.1 -> 16.1 (FP16 storage 21.4 -> 14.1).
 //
 // lds: TileSRows<S>::bytes(bx) bytes, bx >= w the widest tile of the launch.
-template <int MODEL, int S, int ST, bool COH = false>
+//
+// BAND (the learned closure): marks the patches of kMarkW x kMarkH<S> nodes
+// whose result the network may change.  A correction at a node of stage k
+// reaches the result up to 2 (S - 1 - k) <= 4 nodes away (each later step's
+// pull and psi gradient), and the nodes it brings into or out of the band lie
+// within that reach too; so the patches within 4 nodes of a node whose
+// uncorrected phi is in the band, at the stage that updates it, cover every
+// difference.  The band test is a bound on a b = (phi_c + delta)(1 - phi_c +
+// delta), which is monotonic towards phi_c = 1/2 (a.cl_ab, slightly below its
+// value at theta): one compare per node and stage.
+constexpr int kMarkW = 16;
+template <int S>
+constexpr int kMarkH = S == 3 ? 12 : 24;  // (a patch grown by 3 S nodes has at most 1024)
+template <int MODEL, int S, int ST, bool COH = false, bool BAND = false>
 __device__ __forceinline__ void stepS_tile_lds(const StepArgs& a, int x0, int w, int bx, int ys, int hh, int64_t t,
                                                bool down, float* lds) {
-    using G = StepSGeom<64, S, false>;
+    using G = StepSGeom<S>;
     using L = TileSRows<S>;
-    constexpr int H = G::H, PER = G::PER, R = L::R, Q = L::kPeriod;
-    constexpr int F = PER * (S - 1) + 4;  // iterations before the first stored row
-    static_assert(G::UL == 1 && F == H + G::D, "rows: the strip's, its halo's and the pipeline's");
+    constexpr int H = G::H, PER = G::PER, F = G::F, R = L::R, Q = L::kPeriod;
+    static_assert(!BAND || (ST == ST_PLAIN && !COH), "the closure runs with FP32 plain storage");
     using IoCoh = typename std::conditional<
         ST == ST_PLAIN, IoCoherent,
         IoCoherentShifted<typename std::conditional<ST == ST_F16, __half, __hip_bfloat16>::type>>::type;
@@ -1426,6 +1378,23 @@ __device__ __forceinline__ void stepS_tile_lds(const StepArgs& a, int x0, int w,
     };
     // place of the row `age` iterations old in a ring of R
     constexpr auto at = [](int u, int age) { return (u + 2 * R - age) % R; };
+    // BAND: the largest a b of stage k's updates in this period, and the
+    // periods (bit 0: the fill; the last bit: every later one) where it passed
+    float abmax[S];
+    uint32_t seen[S], bit = 1;
+#pragma unroll
+    for (int k = 0; k < S; ++k) {
+        abmax[k] = 0.f;
+        seen[k] = 0;
+    }
+    auto look = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < S; ++k) {
+            seen[k] |= abmax[k] > a.cl_ab ? bit : 0u;
+            abmax[k] = 0.f;
+        }
+        if (bit < 0x80000000u) bit <<= 1;
+    };
     int left = hh;  // rows to store
     // An iteration at place U of the period; IT: which one of the pipeline's
     // fill, or -1 (all stages run; past the strip's last row nothing is stored).
@@ -1528,6 +1497,7 @@ __device__ __forceinline__ void stepS_tile_lds(const StepArgs& a, int x0, int w,
                 float Gx, Gy, ob[9];
                 iso_gradient(pn[k][0], pn[k][1], pn[k][2], pn[k][3], pn[k][4], pn[k][5], pn[k][6], pn[k][7], gx[k], gy[k]);
                 const float phi = ph[k][B ^ 1];
+                if constexpr (BAND) abmax[k] = __builtin_fmaxf(abmax[k], ab[k][B ^ 1]);
                 const float uxr = Ax * rf[k].x, uyr = Bx * rf[k].y;
                 const float phio = P[k][at(U, k == 0 ? 2 : 3)];
                 // (only the first stage can be the run's first step)
@@ -1558,6 +1528,7 @@ __device__ __forceinline__ void stepS_tile_lds(const StepArgs& a, int x0, int w,
     unrolled([&](auto I) __attribute__((always_inline)) {
         body(nv[decltype(I)::value % 2], std::integral_constant<int, decltype(I)::value % Q>{}, I);
     }, std::make_integer_sequence<int, F>{});
+    if constexpr (BAND) look();
     // whole periods: a loop left in the middle, or rows after it, would carry
     // every value through merges
     do {
@@ -1565,273 +1536,49 @@ __device__ __forceinline__ void stepS_tile_lds(const StepArgs& a, int x0, int w,
             constexpr int N = F + decltype(I)::value;
             body(nv[N % 2], std::integral_constant<int, N % Q>{}, std::integral_constant<int, -1>{});
         }, std::make_integer_sequence<int, Q>{});
+        if constexpr (BAND) look();
     } while (left > 0);
-}
-
-// The S-step tile with the learned closure (FP32 plain storage, improved
-// model): the march in a loop of two iterations, the rings' places computed
-// from the iteration number (their periods, 3, 4 and 5 rows, have no short
-// common one).
-template <int BX, int S>
-__device__ __forceinline__ void stepS_tile_cl(const StepArgs& a, int x0, int w, int ys, int hh, bool down,
-                                              TileSLds<BX, S>& lds) {
-    using G = StepSGeom<BX, S, true>;
-    constexpr int H = G::H, UL = G::UL, LG = G::LG, PER = G::PER, D = G::D, W = G::W, NPS = G::NPS;
-    const StepSThread th = stepS_thread<ST_PLAIN>(x0, w, H);
-    const int l = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(l) / kWave, cxo = th.cxo;
-    const bool dup = th.dup, act = th.act;
-    // Stage k forms phi/psi validly on the columns (and rows) up to
-    // RC (S - k) - 1 beyond the tile and updates up to RC (S - 1 - k) beyond
-    // it.  Every thread runs every stage (branching on these ranges would only
-    // hold per-lane masks, since every wavefront has lanes inside them):
-    // outside them a thread forms values from rows or columns that are not
-    // valid yet, which no valid value reads.
-    const int gcol = wrap_idx(x0 + cxo, a.nx);
-    const int j = cxo + H + 1;        // LDS column read
-    const int jw = dup ? W - 1 : j;   // LDS column written
-    // A strip marched downward is computed in the mirrored frame y -> -y:
-    // populations are read from and written to the planes of their mirror
-    // images and the y velocity changes sign, so the march always runs
-    // toward +y in the frame the stages see and no value depends on the
-    // direction.  Every node helper rounds mirror-symmetrically (sums in
-    // mirror-invariant order, y components that only change sign), so the
-    // results equal the lattice-frame computation bit for bit.
-    const IoRows<ST_PLAIN> io(a, down);
-    lds_barrier();  // the LDS may still be read by a previous tile of this block
-
-    const int iters = hh + H + D;
-    if (th.idle) {
-        // no column in this wavefront: the loop's two barriers per iteration only
-        for (int it = 0; it < iters; ++it) {
-            lds_barrier();
-            lds_barrier();
+    if constexpr (BAND) {
+        // the marks, after the march (a branch inside it cost registers it has not)
+        // the patches columns gcol - 4 .. gcol + 4 fall in, periodic: three at
+        // most (the last patch of a row may be narrow)
+        auto step = [](int p, int n, int size) {  // from position p (in [0, n)) to the next patch's first
+            return min(size - p % size, n - p);
+        };
+        int px[3], dx = -4;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            const int q = wrap_idx(gcol + dx, a.nx);
+            px[i] = q / kMarkW;
+            dx = min(dx + step(q, a.nx, kMarkW), 4);
         }
-        return;
-    }
-
-    // FP32 velocity factors: the FP64 table rounded once on the host, as the
-    // one-step kernels round it on the device
-    const float Ax = a.vtabf[gcol];
-    const float Bx = down ? -a.vtabf[a.nx + gcol] : a.vtabf[a.nx + gcol];
-    NodeConst<float> kcs[S];  // stage k, step k of the launch
-#pragma unroll
-    for (int k = 0; k < S; ++k) kcs[k] = NodeConst<float>(a, k);
-    // pulled populations and phi of stage k, ping-pong by iteration parity:
-    // the pull of iteration it fills half it & 1, the update of iteration
-    // it + UL reads it (with UL = 2 through fh, which keeps the pull of two
-    // iterations ago before the half is refilled)
-    float fp[S][2][9], ob[9];
-    float fh[S][9];
-    // Histories, index = age in iterations (0: this iteration).  P[k]: the sum
-    // of stage k's input populations at the own node (phi(t + k - 1) as the
-    // one-step kernel forms it); z0, zo, zn: the own column's c_x = 0 inputs
-    // of stage k (population 0, the old-row one, the new-row one).
-    float P[S][G::NP], z0[S][4], zo[S][4], zn[S][4];
-#pragma unroll
-    for (int k = 0; k < S; ++k) {
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-#pragma unroll
-            for (int q = 0; q < 9; ++q) fp[k][b][q] = 0.f;
-        }
-#pragma unroll
-        for (int d = 0; d < G::NP; ++d) P[k][d] = 0.f;
-#pragma unroll
-        for (int d = 0; d < 4; ++d) z0[k][d] = zo[k][d] = zn[k][d] = 0.f;
-    }
-#pragma unroll
-    for (int k = 0; k < S; ++k)
-#pragma unroll
-        for (int q = 0; q < 9; ++q) fh[k][q] = 0.f;
-#pragma unroll
-    for (int q = 0; q < 9; ++q) ob[q] = 0.f;
-
-    const int dir = down ? -1 : 1;
-    auto raw_row = [&](int it) { return down ? ys + hh + H - 1 - it : ys - H + it; };
-    // lattice row loaded at iteration it (iterations past the last input row
-    // repeat it; what they form is not used)
-    auto row_of = [&](int it) { return (uint32_t)wrap_idx(raw_row(min(it, hh + 2 * H - 1)), a.ny); };
-    // a stage's input into its ring and histories (v: populations at the own column)
-    auto put = [&](int k, int s3, int s2, const float(&v)[9]) __attribute__((always_inline)) {
-        P[k][0] = sum9(v);  // phi at t + k - 1
-        lds.ro[k][s3][0][jw] = v[5];
-        lds.ro[k][s3][1][jw] = v[6];
-        lds.rm[k][s2][0][jw] = v[1];
-        lds.rm[k][s2][1][jw] = v[3];
-        lds.rn[k][0][jw] = v[8];
-        lds.rn[k][1][jw] = v[7];
-        z0[k][0] = v[0];
-        zo[k][0] = v[2];
-        zn[k][0] = v[4];
-    };
-    auto body = [&](const int it, float(&nv)[9], auto parity) __attribute__((always_inline)) {
-        constexpr int B = decltype(parity)::value;  // it & 1
-        const int Rr = raw_row(it);
-        const int s3 = it % 3, s2 = B;
-        const int sps = it % NPS;  // psi slot of this iteration's phi row
-        // ---- row R into stage 0's ring
-        put(0, s3, s2, nv);
-        io.load(row_of(it + 2) * (uint32_t)a.pitch + (uint32_t)gcol, nv);
-        lds_barrier();
-
-        // ---- phi (Eq. (12)) and psi (Eq. (13)) of every stage.  Stage 0 reads
-        // rows entered 0 (new pair), 1 (populations 1, 3) and 2 (old pair)
-        // iterations ago; a later stage's input rows were written 1, 2 and 3
-        // iterations ago.
+        const bool narrow = a.nx < 16;  // (then every patch column)
 #pragma unroll
         for (int k = 0; k < S; ++k) {
-            const int lag = k == 0 ? 0 : 1;
-#pragma unroll
-            for (int q = 0; q < 9; ++q) fh[k][q] = fp[k][B][q];
-            if (it >= PER * k + 2) {
-                const int so = (it + 1 + 2 * lag) % 3;  // old pair: it - 2 - lag
-                const int sm = B ^ 1 ^ lag;             // populations 1, 3: it - 1 - lag
-                float(&f)[9] = fp[k][B];
-                f[0] = z0[k][1 + lag];
-                f[1] = lds.rm[k][sm][0][j - 1];
-                f[2] = zo[k][2 + lag];
-                f[3] = lds.rm[k][sm][1][j + 1];
-                f[4] = zn[k][lag];
-                f[5] = lds.ro[k][so][0][j - 1];
-                f[6] = lds.ro[k][so][1][j + 1];
-                f[7] = lds.rn[k][1][j + 1];
-                f[8] = lds.rn[k][0][j - 1];
-                const float s = sum9(f);
-                lds.ps[k][sps][jw] = normal_source<float, MODEL_IMPROVED>(s, kcs[k]);
-                lds.phr[k][it % 5][jw] = s;
-            }
-        }
-        lds_barrier();
-
-        // psi rows around an updated row: the centre row is UL rows behind this
-        // iteration's phi row, and the row ahead of it (+y in the stages'
-        // frame) one row nearer
-        const int c0 = (it + NPS - UL) % NPS;
-        const int cm = (it + NPS - UL - 1) % NPS;
-        const int cp = (it + (NPS - UL + 1) % NPS) % NPS;
-        // ---- updates: stage k on row R - (LG k + 1 + UL) dir at t + k; the last stage into HBM
-        const bool st = act && it >= PER * (S - 1) + 2 + 2 * UL;
-        const int yl = min(max(Rr - D * dir, 0), a.ny - 1);
-        uint64_t bms[S];  // closure: band nodes of stage k's updated row (one bit per lane)
-#pragma unroll
-        for (int k = 0; k < S; ++k) bms[k] = 0;
-#pragma unroll
-        for (int k = 0; k < S; ++k) {
-            const bool last = k == S - 1;
-            if (it >= PER * k + 2 + 2 * UL) {
-                const NodeConst<float>& kc = kcs[k];
-                const int y = last ? yl : wrap_idx(Rr - (LG * k + 1 + UL) * dir, a.ny);
-                const float(&ps)[NPS][W] = lds.ps[k];
-                float gx, gy, Gx, Gy;
-                iso_gradient(ps[c0][j + 1], ps[c0][j - 1], ps[cp][j], ps[cm][j], ps[cp][j + 1], ps[cp][j - 1],
-                             ps[cm][j + 1], ps[cm][j - 1], gx, gy);
-                const float phi = lds.phr[k][(it + 3) % 5][j];  // phi row it - 2
-                const float uxr = Ax * row_factor(a.vtabf, 2 * a.nx + y);
-                const float uyr = Bx * row_factor(a.vtabf, 2 * a.nx + a.ny + y);
-                const float phio = P[k][(k == 0 ? 1 : 2) + UL];
-                flux_bracket<float, MODEL_IMPROVED>(gx, gy, phi, kc.first ? phi : phio, kc.s_now * uxr, kc.s_now * uyr,
-                                           kc.s_old * uxr, kc.s_old * uyr, kc, Gx, Gy);
-                collide(fh[k], phi, kc.s_now * uxr, kc.s_now * uyr, Gx, Gy, kc, ob);
-                // interface-band nodes among those stage k must update (the
-                // condition of the one-step path's band mask); their
-                // correction is added after the last stage (below)
-                const int reach = G::RC * (S - 1 - k);
-                const int rel = it - H - (LG * k + 1 + UL);  // row relative to the strip, march frame
-                const bool need = !dup && cxo >= -reach && cxo < w + reach && rel >= -reach && rel < hh + reach;
-                const float pc = clip01(phi);
-                bms[k] = __ballot(need && pc > a.cl_theta && pc < 1.0f - a.cl_theta);
-                if (!last) put(k + 1, s3, s2, ob);
-            }
-        }
-        {
-            // The network on every stage's band nodes of this wavefront, packed
-            // into one list (stage by stage, lanes in order), from stage k's
-            // phi ring (rows it - 4 .. it; the updated row is it - 2), and its
-            // correction added to the node's post-collision populations: for
-            // the last stage in ob before the store, for an earlier one where
-            // put() left them (the next stage's rings and own-column
-            // histories), which nothing reads before the next iteration.
-            const int lane = l % kWave;
-            const uint64_t below = (1ull << lane) - 1ull;
-            int slot[S], count = 0;
-#pragma unroll
-            for (int k = 0; k < S; ++k) {
-                slot[k] = count + __popcll(bms[k] & below);
-                count += __popcll(bms[k]);
-            }
-            if (count) {
-                int* tab = lds.tab[wv];
-#pragma unroll
-                for (int k = 0; k < S; ++k)
-                    if ((bms[k] >> lane) & 1ull) tab[slot[k]] = (k << 16) | j;
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
-                for (int first = 0; first < count; first += kWave) {
-                    const float2 c = closure_mlp_list(a.cl_w, a.cl_b, &lds.phr[0][0][0], 5 * W, W, it + 3, down,
-                                                      tab + first, count - first);
-#pragma unroll
-                    for (int k = 0; k < S; ++k) {
-                        const int src = slot[k] - first;
-                        const float cx = __shfl(c.x, src & (kWave - 1), kWave);
-                        const float cy = __shfl(c.y, src & (kWave - 1), kWave);
-                        if (!((bms[k] >> lane) & 1ull) || src < 0 || src >= kWave) continue;
-                        const float phi = lds.phr[k][(it + 3) % 5][j];
-                        if (k == S - 1) {
-                            closure_correct(ob, phi, kcs[k].kforce, cx, cy, down);
-                        } else {
-                            const int n = k == S - 1 ? 0 : k + 1;  // (k + 1 without the out-of-range index)
-                            float f[9];
-                            f[1] = lds.rm[n][s2][0][jw];
-                            f[3] = lds.rm[n][s2][1][jw];
-                            f[5] = lds.ro[n][s3][0][jw];
-                            f[6] = lds.ro[n][s3][1][jw];
-                            f[8] = lds.rn[n][0][jw];
-                            f[7] = lds.rn[n][1][jw];
-                            f[2] = zo[n][0];
-                            f[4] = zn[n][0];
-                            closure_correct(f, phi, kcs[k].kforce, cx, cy, down);
-                            lds.rm[n][s2][0][jw] = f[1];
-                            lds.rm[n][s2][1][jw] = f[3];
-                            lds.ro[n][s3][0][jw] = f[5];
-                            lds.ro[n][s3][1][jw] = f[6];
-                            lds.rn[n][0][jw] = f[8];
-                            lds.rn[n][1][jw] = f[7];
-                            z0[n][0] = f[0];
-                            zo[n][0] = f[2];
-                            zn[n][0] = f[4];
-                            P[n][0] = sum9(f);
-                        }
+            const int reach = 2 * (S - 1 - k);
+            if (th.dup || cxo < -reach || cxo >= w + reach) seen[k] = 0;
+            // periods in turn, the rows the wavefront's: only the lanes differ
+            for (int g = 0; g < 32; ++g) {
+                const bool on = (seen[k] >> g) & 1u;
+                if (__ballot(on) == 0) continue;
+                // the period's rows, counted along the march from the strip's
+                // first (stage k is 3 (S - 1 - k) rows ahead of the stored one)
+                const int r0 = g == 0 ? -reach : Q * (g - 1) + 3 * (S - 1 - k);
+                const int r1 = g == 0 ? 3 * (S - 1 - k) - 1 : (g < 31 ? r0 + Q - 1 : hh + reach - 1);
+                const int ylo = (down ? ys + hh - 1 - r1 : ys + r0) - 4, yhi = ylo + (r1 - r0) + 8;
+                for (int y = ylo; y <= yhi;) {
+                    const int q = wrap_idx(y, a.ny);
+                    uint8_t* row = a.cl_flags + (q / kMarkH<S>) * a.cl_npx;
+                    if (on) {
+                        row[px[0]] = 1;
+                        row[px[1]] = 1;
+                        row[px[2]] = 1;
+                        if (narrow) row[0] = 1;
                     }
+                    y += step(q, a.ny, kMarkH<S>);
                 }
-                __builtin_amdgcn_wave_barrier();  // the list is rewritten next iteration
             }
         }
-        // non-temporal: a stored row is not read again in this launch, while
-        // the 2H rows each strip shares with its neighbours are (1.5% faster
-        // at 8192^2 than plain stores)
-        io.store_nt(st, (uint32_t)yl * (uint32_t)a.pitch + (uint32_t)(x0 + cxo), ob, 0.f);
-        // ---- age the histories by one iteration
-#pragma unroll
-        for (int k = 0; k < S; ++k) {
-#pragma unroll
-            for (int d = G::NP - 1; d > 0; --d) P[k][d] = P[k][d - 1];
-#pragma unroll
-            for (int d = 3; d > 0; --d) {
-                z0[k][d] = z0[k][d - 1];
-                zo[k][d] = zo[k][d - 1];
-                zn[k][d] = zn[k][d - 1];
-            }
-        }
-    };
-    // two rows of loads in flight: row r + 2 is loaded while row r is processed,
-    // into the register set row r came in
-    float na[9], nb[9];
-    io.load(row_of(0) * (uint32_t)a.pitch + (uint32_t)gcol, na);
-    io.load(row_of(1) * (uint32_t)a.pitch + (uint32_t)gcol, nb);
-    for (int it = 0; it < iters; it += 2) {
-        body(it, na, std::integral_constant<int, 0>{});
-        if (it + 1 < iters) body(it + 1, nb, std::integral_constant<int, 1>{});
     }
 }
 
@@ -1839,7 +1586,7 @@ __device__ __forceinline__ void stepS_tile_cl(const StepArgs& a, int x0, int w, 
 // not hold the widest one's.  Three wavefronts per SIMD at S = 3 (168
 // registers), four at S = 2 (128).
 constexpr int kStepSMaxBx = 320;
-template <int MODEL, int S, int ST>
+template <int MODEL, int S, int ST, bool BAND = false>
 __global__ __launch_bounds__((stepS_threads<kStepSMaxBx, S>())) __attribute__((amdgpu_waves_per_eu(S == 2 ? 4 : 3))) void
 stepS_kernel_lds(StepArgs a) {
     extern __shared__ float stepS_lds[];
@@ -1847,20 +1594,23 @@ stepS_kernel_lds(StepArgs a) {
     const int tile = xcd_tile(blockIdx.x, ntile, a.n_xcd);
     const int bxi = tile % a.nbx, syi = tile / a.nbx;
     const int x0 = bxi * a.tile_w, ys = syi * a.strip_h;
-    stepS_tile_lds<MODEL, S, ST>(a, x0, min(a.tile_w, a.nx - x0), a.tile_w, ys, min(a.strip_h, a.ny - ys), 0,
+    if (BAND && blockIdx.x == 0 && threadIdx.x == 0) a.cl_count[0] = 0;  // (the patch list starts empty)
+    stepS_tile_lds<MODEL, S, ST, false, BAND>(a, x0, min(a.tile_w, a.nx - x0), a.tile_w, ys, min(a.strip_h, a.ny - ys), 0,
                                  (syi & 1) != 0, stepS_lds);
 }
 
-// The S-step kernel with the learned closure (FP32 storage, improved model).
-template <int BX, int S>
-__global__ __launch_bounds__((stepS_threads<BX, S, true>())) __attribute__((amdgpu_waves_per_eu(2, 2))) void
-stepS_kernel_cl(StepArgs a) {
-    __shared__ TileSLds<BX, S> lds;
-    const int ntile = a.nbx * a.nby;
-    const int tile = xcd_tile(blockIdx.x, ntile, a.n_xcd);
-    const int bxi = tile % a.nbx, syi = tile / a.nbx;
-    const int x0 = bxi * BX, ys = syi * a.strip_h;
-    stepS_tile_cl<BX, S>(a, x0, min(BX, a.nx - x0), ys, min(a.strip_h, a.ny - ys), (syi & 1) != 0, lds);
+// The marked patches as a list (in any order: each is recomputed by itself),
+// and the marks cleared for the next launch.
+static __global__ __launch_bounds__(256) void closure_list_kernel(uint8_t* __restrict__ flags, int n,
+                                                                  int32_t* __restrict__ list,
+                                                                  uint32_t* __restrict__ count) {
+    const int i0 = (blockIdx.x * 256 + threadIdx.x) * 8;  // the flags are padded to whole words
+    if (i0 >= n) return;
+    uint64_t f = *reinterpret_cast<const uint64_t*>(flags + i0);
+    if (!f) return;
+    *reinterpret_cast<uint64_t*>(flags + i0) = 0;
+    uint32_t k = atomicAdd(count, (uint32_t)__popcll(f));
+    for (; f; f &= f - 1) list[k++] = i0 + (__ffsll((unsigned long long)f) - 1) / 8;
 }
 
 // ---------------------------------------------------------------------------

@@ -43,7 +43,9 @@ struct PatchLds<float, S, PW, PH, true> {
     float f[8][N];
     float ps[N];
     float phr[N];             // phi (the network's input)
-    int tab[16][kWave];       // per wavefront: its band nodes
+    int tab[N];               // the band nodes of the step's update, in any order
+    float cor[N][2];          // their corrections
+    uint32_t count[S];        // how many, per step
     alignas(16) uint16_t w[kClWN];  // the network, packed
     float b[kClBN];
 };
@@ -57,16 +59,13 @@ __device__ __forceinline__ int wrap_near(int a, int n, bool near) {
 
 // NT threads, NPT nodes per thread (node i of thread l: l + i NT of the grown
 // patch, row by row, so that neighbouring lanes hold neighbouring columns).
-template <typename R, int ST, int MODEL, int S, int PW, int PH, int NT, bool CL>
-__global__ __launch_bounds__(NT) void patch_kernel(StepArgs a) {
+template <typename R, int ST, int MODEL, int S, int PW, int PH, int NT, bool CL, bool LOOP = false>
+__device__ __forceinline__ void patch_steps(const StepArgs& a, int x0, int y0, PatchLds<R, S, PW, PH, CL>& lds) {
     static_assert(!CL || (sizeof(R) == 4 && ST == ST_PLAIN && MODEL == MODEL_IMPROVED), "closure: FP32 plain storage");
     static_assert(ST == ST_PLAIN || S == 1, "16-bit storage is rounded once per launch: one step");
     using G = PatchGeom<S, PW, PH, CL>;
     constexpr int RC = G::RC, H = G::H, GW = G::GW, GH = G::GH, N = G::N;
     constexpr int NPT = (N + NT - 1) / NT;
-    __shared__ PatchLds<R, S, PW, PH, CL> lds;
-    const int tile = xcd_tile(blockIdx.x, a.nbx * a.nby, a.n_xcd);
-    const int x0 = (tile % a.nbx) * PW, y0 = (tile / a.nbx) * PH;
     const int l = threadIdx.x;
     const bool nearx = a.nx >= GW, neary = a.ny >= GH;
     const Io<R, ST> io(a);
@@ -96,10 +95,7 @@ __global__ __launch_bounds__(NT) void patch_kernel(StepArgs a) {
         }
     }
     if constexpr (CL) {
-        const uint32_t* src = reinterpret_cast<const uint32_t*>(a.cl_w);
-        uint32_t* dst = reinterpret_cast<uint32_t*>(lds.w);
-        for (int i = l; i < kClWN / 2; i += NT) dst[i] = src[i];
-        for (int i = l; i < kClBN; i += NT) lds.b[i] = a.cl_b[i];
+        if (l < S) lds.count[l] = 0;
     }
     R rest[NPT], P[NPT];
 #pragma unroll
@@ -112,8 +108,13 @@ __global__ __launch_bounds__(NT) void patch_kernel(StepArgs a) {
         rest[i] = v[i][0];
         P[i] = Io<R, ST>::kShifted ? v[i][0] : sum9(v[i]);
     }
-#pragma unroll
+    // (LOOP: the steps stay a loop, and the lane index opaque: what they share,
+    // addresses above all, held across them takes more registers than two
+    // blocks of the list kernel have)
+#pragma unroll(LOOP ? 1 : S)
     for (int k = 0; k < S; ++k) {
+        int l = threadIdx.x;
+        if constexpr (LOOP) asm volatile("" : "+v"(l));
         const NodeConst<R> kc(a, k);
         R fp[NPT][9], phi[NPT];
         lds_barrier();
@@ -137,11 +138,14 @@ __global__ __launch_bounds__(NT) void patch_kernel(StepArgs a) {
         lds_barrier();
         // ---- update
         const int mb = RC * (S - 1 - k);
+        int slot[NPT];  // closure: the node's place in the list of band nodes, or -1
 #pragma unroll
         for (int i = 0; i < NPT; ++i) {
             const int n = l + i * NT;
             const bool in = n < N && lx[i] >= -mb && lx[i] < PW + mb && ly[i] >= -mb && ly[i] < PH + mb;
+            const bool mine = in && x0 + lx[i] < a.nx && y0 + ly[i] < a.ny;  // the last step stores it
             R out[9];
+            slot[i] = -1;
             if (in) {
                 R gx, gy, Gx, Gy;
                 const R* p = &lds.ps[n];
@@ -152,45 +156,109 @@ __global__ __launch_bounds__(NT) void patch_kernel(StepArgs a) {
                 collide(fp[i], phi[i], kc.s_now * uxr, kc.s_now * uyr, Gx, Gy, kc, out);
             }
             if constexpr (CL) {
-                // the network on the wavefront's band nodes, packed into a list
                 const float pc = clip01(phi[i]);
                 const bool band = in && pc > a.cl_theta && pc < 1.0f - a.cl_theta;
                 const uint64_t m = __ballot(band);
                 if (m) {
-                    const int lane = l % kWave, slot = __popcll(m & ((1ull << lane) - 1ull)), count = __popcll(m);
-                    int* tab = lds.tab[l / kWave];
-                    if (band) tab[slot] = n;
-                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
-                    __builtin_amdgcn_wave_barrier();
-                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
-                    auto xfrag = [&](int nt) {
-                        const int s = 16 * nt + lane % 16, g = lane / 16;
-                        const bool on = s < count;
-                        const int c = on ? tab[s] : 0;
-                        u16x8_t x;
-#pragma unroll
-                        for (int e = 0; e < 8; ++e) {
-                            const int kk = 8 * g + e;
-                            x[e] = on && kk < 25 ? bf16_bits(lds.phr[c + (kk / 5 - 2) * GW + kk % 5 - 2]) : (uint16_t)0;
-                        }
-                        return __builtin_bit_cast(bf16x8_t, x);
-                    };
-                    float ccx, ccy;
-                    closure_mlp(lds.w, lds.b, xfrag, count >= 64 ? ~0ull : (1ull << count) - 1ull, ccx, ccy);
-                    const float vx = __shfl(ccx, slot & (kWave - 1), kWave), vy = __shfl(ccy, slot & (kWave - 1), kWave);
-                    if (band) closure_correct(out, phi[i], kc.kforce, vx, vy, false);
-                    __builtin_amdgcn_wave_barrier();  // the list is rewritten by the next step
+                    const int lane = l % kWave;
+                    uint32_t base = 0;
+                    if (lane == 0) base = atomicAdd(&lds.count[k], (uint32_t)__popcll(m));
+                    base = __builtin_amdgcn_readfirstlane(base);
+                    if (band) {
+                        slot[i] = (int)base + __popcll(m & ((1ull << lane) - 1ull));
+                        lds.tab[slot[i]] = n;
+                    }
                 }
             }
-            if (k == S - 1) {
-                io.store(in && x0 + lx[i] < a.nx && y0 + ly[i] < a.ny, off[i], out, phi[i]);
-            } else if (in) {
+            // (a band node goes through LDS on the last step too: its
+            // correction is added below, and the network has the registers
+            // to itself)
+            const bool later = CL && slot[i] >= 0;
+            if (k == S - 1) io.store(mine && !later, off[i], out, phi[i]);
+            if (in && (k < S - 1 || later)) {
 #pragma unroll
                 for (int q = 1; q < 9; ++q) lds.f[q - 1][n] = out[q];
                 rest[i] = out[0];
                 P[i] = sum9(out);
             }
         }
+        if constexpr (CL) {
+            // The network on the block's band nodes, 16 to a wavefront at a
+            // time: a wavefront's own few would each take a whole 16-sample
+            // pass (5 us per step at 16 wavefronts per block; packed, 2 to 3)
+            lds_barrier();
+            const int count = (int)lds.count[k], lane = l % kWave;
+            for (int s0 = l / kWave * 16; s0 < count; s0 += NT / kWave * 16) {
+                const int s = s0 + lane % 16, g = lane / 16;
+                const bool on = s < count;
+                const int c = on ? lds.tab[s] : 0;
+                auto xfrag = [&](int) {
+                    u16x8_t x;
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        const int kk = 8 * g + e;
+                        x[e] = on && kk < 25 ? bf16_bits(lds.phr[c + (kk / 5 - 2) * GW + kk % 5 - 2]) : (uint16_t)0;
+                    }
+                    return __builtin_bit_cast(bf16x8_t, x);
+                };
+                float ccx, ccy;
+                closure_mlp(lds.w, lds.b, xfrag, 0xffffull, ccx, ccy);
+                if (g == 0 && on) {
+                    lds.cor[s][0] = ccx;
+                    lds.cor[s][1] = ccy;
+                }
+            }
+            if (count) lds_barrier();  // (the same count on every wavefront)
+#pragma unroll
+            for (int i = 0; i < NPT; ++i) {
+                const int n = l + i * NT;
+                if (slot[i] < 0) continue;
+                float f[9];
+#pragma unroll
+                for (int q = 1; q < 9; ++q) f[q] = lds.f[q - 1][n];
+                closure_correct(f, phi[i], kc.kforce, lds.cor[slot[i]][0], lds.cor[slot[i]][1], false);
+                if (k == S - 1) {
+                    io.store(x0 + lx[i] < a.nx && y0 + ly[i] < a.ny, off[i], f, phi[i]);
+                } else {
+#pragma unroll
+                    for (int q = 1; q < 9; ++q) lds.f[q - 1][n] = f[q];
+                    rest[i] = f[0];
+                    P[i] = sum9(f);
+                }
+            }
+        }
+    }
+}
+
+// The closure's network into LDS (seen after the next barrier).
+template <int NT, typename Lds>
+__device__ __forceinline__ void patch_network(const StepArgs& a, Lds& lds) {
+    const uint32_t* src = reinterpret_cast<const uint32_t*>(a.cl_w);
+    uint32_t* dst = reinterpret_cast<uint32_t*>(lds.w);
+    for (int i = threadIdx.x; i < kClWN / 2; i += NT) dst[i] = src[i];
+    for (int i = threadIdx.x; i < kClBN; i += NT) lds.b[i] = a.cl_b[i];
+}
+
+// Every patch of the grid, one per block.
+template <typename R, int ST, int MODEL, int S, int PW, int PH, int NT, bool CL>
+__global__ __launch_bounds__(NT) void patch_kernel(StepArgs a) {
+    __shared__ PatchLds<R, S, PW, PH, CL> lds;
+    const int tile = xcd_tile(blockIdx.x, a.nbx * a.nby, a.n_xcd);
+    if constexpr (CL) patch_network<NT>(a, lds);
+    patch_steps<R, ST, MODEL, S, PW, PH, NT, CL>(a, (tile % a.nbx) * PW, (tile / a.nbx) * PH, lds);
+}
+
+// The listed patches (closure), each block several in turn.
+template <int S, int PW, int PH, int NT>
+__global__ __launch_bounds__(NT) void patch_list_kernel(StepArgs a) {
+    __shared__ PatchLds<float, S, PW, PH, true> lds;
+    patch_network<NT>(a, lds);
+    const int n = (int)a.cl_count[0];
+    for (int i = blockIdx.x; i < n; i += gridDim.x) {
+        const int tile = a.cl_list[i];
+        patch_steps<float, ST_PLAIN, MODEL_IMPROVED, S, PW, PH, NT, true, true>(a, (tile % a.cl_npx) * PW, (tile / a.cl_npx) * PH,
+                                                                          lds);
+        lds_barrier();  // the LDS is filled again by the next patch
     }
 }
 
@@ -227,11 +295,11 @@ constexpr Shape kF64[] = {{4, 8, 8, 10.f, 6.5f},    {4, 16, 16, 13.3f, 10.6f}, {
 // 16-bit storage: one step, since a launch rounds once (5.2, 7.1, 11.3 and
 // 16.0 us at 256^2, 512^2, 768^2 and 1024^2; strips 7.9, 9.6, 13.9 and 16.9).
 constexpr Shape kF16[] = {{1, 28, 28, 5.2f, 2.1f}};
-// FP32 with the closure, a disk's edge in the field (7.3, 8.7, 14.8 and 89 us
-// per step at 128^2, 200^2, 512^2 and 2048^2; the best of five multi-step
-// strip shapes 50, 57, 67 and 165).
-constexpr Shape kCl[] = {{4, 8, 8, 29.f, 9.f}, {3, 14, 14, 26.f, 5.f}, {2, 20, 20, 19.5f, 5.6f}, {2, 52, 20, 28.f, 9.f},
-                         {1, 26, 26, 12.f, 3.6f}};
+// FP32 with the closure, a disk's edge in the field (5.7, 14.3, 26 and 43 us
+// per step at 128^2, 512^2, 1024^2 and 1536^2; the two-pass launches at their
+// best 17.8, 17.7, 21.7 and 32).
+constexpr Shape kCl[] = {{4, 8, 8, 23.f, 9.f}, {3, 14, 14, 20.f, 5.f}, {2, 20, 20, 15.f, 6.5f}, {2, 52, 20, 24.f, 8.5f},
+                         {1, 26, 26, 10.f, 3.4f}};
 
 template <typename R, int ST, int MODEL, int S, int PW, int PH, int NT, bool CL = false>
 hipError_t go(StepArgs a, hipStream_t s) {
@@ -295,6 +363,27 @@ hipError_t go_cl(int shape, const StepArgs& a, hipStream_t s) {
     }
 }
 
+// The closure in two passes over large grids: the plain S-step strips, which
+// mark the patches near the interface band, then the marked patches again
+// with the network, from the same input.  The band is thin (0.1% of the nodes
+// of the benchmark's disk at 8192^2), so nearly all of the grid runs at the
+// plain kernel's speed; before, every tile ran a kernel with the network
+// inside, at two wavefronts per SIMD.
+constexpr int kMarkBlocks = 512;
+
+template <int S>
+hipError_t go_split(const lbac_ctx* h, StepArgs a, int bx) {
+    a.cl_npx = (a.nx + kMarkW - 1) / kMarkW;
+    const int np = a.cl_npx * ((a.ny + kMarkH<S> - 1) / kMarkH<S>);
+    hipError_t e = lbac_host::launch_stepS_band(S, a, bx, h->stream);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(closure_list_kernel, dim3((np + 2047) / 2048), dim3(256), 0, h->stream, a.cl_flags, np,
+                       const_cast<int32_t*>(a.cl_list), a.cl_count);
+    hipLaunchKernelGGL((patch_list_kernel<S, kMarkW, kMarkH<S>, 512>), dim3(std::min(np, kMarkBlocks)), dim3(512), 0,
+                       h->stream, a);
+    return hipGetLastError();
+}
+
 const Shape* shapes_of(const lbac_ctx* h, int& n) {
     if (h->closure) return n = 5, kCl;
     if (h->storage != ST_PLAIN) return n = 1, kF16;
@@ -335,4 +424,13 @@ hipError_t lbac_host::launch_patch(const lbac_ctx* h, int src, int32_t k, const 
         return conv ? go<float, ST_BF16, MODEL_CONVENTIONAL, 1, 28, 28, 1024>(a, h->stream)
                     : go<float, ST_BF16, MODEL_IMPROVED, 1, 28, 28, 1024>(a, h->stream);
     }
+}
+
+hipError_t lbac_host::launch_split(const lbac_ctx* h, const StepArgs& a, int S) {
+    return S == 3 ? go_split<3>(h, a, h->bx) : go_split<2>(h, a, h->bx);
+}
+
+size_t lbac_host::mark_count(int nx, int ny) {
+    static_assert(kMarkH<3> <= kMarkH<2>, "the lower patches are the more");
+    return (size_t)((nx + kMarkW - 1) / kMarkW) * ((ny + kMarkH<3> - 1) / kMarkH<3>);
 }

@@ -104,3 +104,26 @@ def test_autotune_keeps_the_faster_and_the_state():
     assert np.array_equal(a.phi(), b.phi())
     a.close()
     b.close()
+
+
+# the two-pass launches (strips that mark, then the marked patches): grids
+# whose last patch is one to a few nodes wide or high, a disk across the
+# periodic edges, strips of one row, up and down
+@pytest.mark.parametrize("nx,ny", [(145, 97), (147, 98), (160, 100), (33, 25), (1, 40), (300, 13), (17, 300)])
+@pytest.mark.parametrize("launch", [(224, 40, 4), (64, 6, 4), (128, 32, 3), (96, 8, 3)])
+def test_two_pass_closure_equals_one_step(nx, ny, launch):
+    say("case: two-pass closure", nx, ny, launch)
+    case = dict(nx=nx, ny=ny, eps=0.8, tau=0.7, vel="uniform", ux=0.05, uy=-0.04, precision="f32")
+    phi0 = W.circle(nx, 0.8, R_frac=0.3, xc_frac=0.0, yc_frac=1.0, ny=ny)
+    phi0 = np.maximum(phi0, np.roll(phi0, (ny // 2, nx // 2), (0, 1)))
+    out = []
+    for shape in (launch, (64, 8, 0)):
+        s = lbac.Simulation(case, phi0)
+        s.set_closure(driver.init_weights(5, out_scale=0.05), 0.02)
+        s.set_launch(*shape)
+        s.step(launch[2] - 1)
+        a = s.phi()
+        s.step(6 * (launch[2] - 1))
+        out.append((a, s.phi()))
+        s.close()
+    assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
