@@ -546,9 +546,35 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_rsrc(const void* base) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, (int)kRowsRange, 0x00020000);
 }
 
+// What `load` of a multi-step storage type gives: the values as they are in
+// memory, which `unpack` turns into populations where the row is consumed, two
+// iterations later.  (Converted at the load, whose iteration the scheduling
+// barriers of the march keep it in, a 16-bit row is waited for at once: 64 FP16
+// batch instances of 128^2 to 512^2 in 40-row tiles 32.6 ms, 14.5 like this; a
+// 3001 x 2210 BF16 lattice in 240 x 40 tiles 36.9 and 32.9 us per step.)
+struct RawPlain {
+    float v[9];
+};
+struct RawShifted {
+    float phi;            // phi*
+    unsigned short g[9];  // g[1..8]
+};
+// v[0] = phi*, v[i] = w_i phi* + g_i (see StoreShifted)
+template <typename H>
+__device__ __forceinline__ void unpack_shifted(const RawShifted& r, float (&v)[9]) {
+    v[0] = r.phi;
+#pragma unroll
+    for (int q = 1; q < 9; ++q) v[q] = __builtin_fmaf(wq<float>(q), r.phi, h2f<H>(__builtin_bit_cast(H, r.g[q])));
+}
+__device__ __forceinline__ void unpack_plain(const RawPlain& r, float (&v)[9]) {
+#pragma unroll
+    for (int q = 0; q < 9; ++q) v[q] = r.v[q];
+}
+
 template <int ST>
 struct IoRows {
     static constexpr bool kShifted = true;
+    using Raw = RawShifted;
     using H = typename std::conditional<ST == ST_F16, __half, __hip_bfloat16>::type;
     __amdgpu_buffer_rsrc_t sg, dg, sp, dp;
     uint32_t pb[9];
@@ -558,16 +584,12 @@ struct IoRows {
 #pragma unroll
         for (int q = 1; q < 9; ++q) pb[q] = (uint32_t)((mirror ? mirror_q(q) : q) - 1) * (uint32_t)a.plane_stride * 2u;
     }
-    // v[0] = phi*, v[i] = w_i phi* + g_i (see StoreShifted)
-    __device__ __forceinline__ void load(uint32_t off, float (&v)[9]) const {
-        const float ph = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(sp, (int)(off * 4u), 0, 0));
-        v[0] = ph;
+    __device__ __forceinline__ void load(uint32_t off, Raw& r) const {
+        r.phi = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(sp, (int)(off * 4u), 0, 0));
 #pragma unroll
-        for (int q = 1; q < 9; ++q) {
-            const unsigned short g = __builtin_amdgcn_raw_buffer_load_b16(sg, (int)(off * 2u), (int)pb[q], 0);
-            v[q] = __builtin_fmaf(wq<float>(q), ph, h2f<H>(__builtin_bit_cast(H, g)));
-        }
+        for (int q = 1; q < 9; ++q) r.g[q] = __builtin_amdgcn_raw_buffer_load_b16(sg, (int)(off * 2u), (int)pb[q], 0);
     }
+    __device__ __forceinline__ void unpack(const Raw& r, float (&v)[9]) const { unpack_shifted<H>(r, v); }
     __device__ __forceinline__ void store_nt(bool on, uint32_t off, const float (&v)[9], float phi) const {
         const uint32_t b2 = on ? off * 2u : kRowsRange, b4 = on ? off * 4u : kRowsRange;
 #pragma unroll
@@ -582,6 +604,7 @@ struct IoRows {
 template <>
 struct IoRows<ST_PLAIN> {
     static constexpr bool kShifted = false;
+    using Raw = RawPlain;
     __amdgpu_buffer_rsrc_t s0, s1, d0, d1;
     uint32_t pb[9];
     __device__ __forceinline__ IoRows(const StepArgs& a, bool mirror)
@@ -591,11 +614,12 @@ struct IoRows<ST_PLAIN> {
         for (int q = 0; q < 9; ++q)
             pb[q] = (uint32_t)((mirror ? mirror_q(q) : q) - (q < 5 ? 0 : 5)) * (uint32_t)a.plane_stride * 4u;
     }
-    __device__ __forceinline__ void load(uint32_t off, float (&v)[9]) const {
+    __device__ __forceinline__ void load(uint32_t off, Raw& r) const {
 #pragma unroll
         for (int q = 0; q < 9; ++q)
-            v[q] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(q < 5 ? s0 : s1, (int)(off * 4u), (int)pb[q], 0));
+            r.v[q] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(q < 5 ? s0 : s1, (int)(off * 4u), (int)pb[q], 0));
     }
+    __device__ __forceinline__ void unpack(const Raw& r, float (&v)[9]) const { unpack_plain(r, v); }
     __device__ __forceinline__ void store_nt(bool on, uint32_t off, const float (&v)[9], float /*phi*/) const {
         const uint32_t b = on ? off * 4u : kRowsRange;
 #pragma unroll
@@ -624,6 +648,7 @@ struct IoRows<ST_PLAIN> {
 // larger instances.
 struct IoCoherent {
     static constexpr bool kShifted = false;
+    using Raw = RawPlain;
     static constexpr int kSc1 = 16;  // cache-policy operand: sc1 (device scope)
     static constexpr int kNt = 2;    // cache-policy operand: nt (non-temporal)
     __amdgpu_buffer_rsrc_t sr, dr;
@@ -644,12 +669,13 @@ struct IoCoherent {
 #pragma unroll
         for (int q = 0; q < 9; ++q) pb[q] = (uint32_t)(m ? mirror_q(q) : q) * ps;
     }
-    __device__ __forceinline__ void load(uint32_t off, float (&v)[9]) const {
+    __device__ __forceinline__ void load(uint32_t off, Raw& r) const {
         const uint32_t b = off * 4u;
 #pragma unroll
         for (int q = 0; q < 9; ++q)
-            v[q] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(sr, (int)b, (int)pb[q], kSc1));
+            r.v[q] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(sr, (int)b, (int)pb[q], kSc1));
     }
+    __device__ __forceinline__ void unpack(const Raw& r, float (&v)[9]) const { unpack_plain(r, v); }
     // device-scope stores with the non-temporal hint (the hint leaves the
     // scope alone: the stored rows are not read again in the pass, and the L2
     // keeps the rows and halo columns other items read)
@@ -669,6 +695,7 @@ struct IoCoherent {
 template <typename H>
 struct IoCoherentShifted {
     static constexpr bool kShifted = true;
+    using Raw = RawShifted;
     static constexpr int kSc1 = IoCoherent::kSc1;
     __amdgpu_buffer_rsrc_t sg, dg, sp, dp;
     uint32_t pb[9];  // byte offset of the g plane read and written for population q (q >= 1)
@@ -683,17 +710,12 @@ struct IoCoherentShifted {
 #pragma unroll
         for (int q = 1; q < 9; ++q) pb[q] = (uint32_t)((m ? mirror_q(q) : q) - 1) * ps;
     }
-    // v[0] = phi*, v[i] = w_i phi* + g_i
-    __device__ __forceinline__ void load(uint32_t off, float (&v)[9]) const {
-        const float ph =
-            __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(sp, (int)(off * 4u), 0, kSc1));
-        v[0] = ph;
+    __device__ __forceinline__ void load(uint32_t off, Raw& r) const {
+        r.phi = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(sp, (int)(off * 4u), 0, kSc1));
 #pragma unroll
-        for (int q = 1; q < 9; ++q) {
-            const unsigned short g = __builtin_amdgcn_raw_buffer_load_b16(sg, (int)(off * 2u), (int)pb[q], kSc1);
-            v[q] = __builtin_fmaf(wq<float>(q), ph, h2f<H>(__builtin_bit_cast(H, g)));
-        }
+        for (int q = 1; q < 9; ++q) r.g[q] = __builtin_amdgcn_raw_buffer_load_b16(sg, (int)(off * 2u), (int)pb[q], kSc1);
     }
+    __device__ __forceinline__ void unpack(const Raw& r, float (&v)[9]) const { unpack_shifted<H>(r, v); }
     // stores g_i = v_i - w_i phi and phi* = phi when `on` (device scope,
     // non-temporal, as IoCoherent)
     __device__ __forceinline__ void store_nt(bool on, uint32_t off, const float (&v)[9], float phi) const {
@@ -1337,7 +1359,7 @@ __device__ __forceinline__ void stepS_tile_lds(const StepArgs& a, int x0, int w,
     // and the stored one's offset
     RowWalk rl(down ? ys + hh + H - 1 : ys - H, down, a.ny);
     int loads_left = hh + 2 * H - 1;
-    auto load = [&](float(&nv)[9]) __attribute__((always_inline)) {
+    auto load = [&](typename IoT::Raw& nv) __attribute__((always_inline)) {
         io.load((uint32_t)rl.y * (uint32_t)a.pitch + (uint32_t)gcol, nv);
         if (loads_left > 0) rl.next();
         --loads_left;
@@ -1398,7 +1420,7 @@ __device__ __forceinline__ void stepS_tile_lds(const StepArgs& a, int x0, int w,
     int left = hh;  // rows to store
     // An iteration at place U of the period; IT: which one of the pipeline's
     // fill, or -1 (all stages run; past the strip's last row nothing is stored).
-    auto body = [&](float(&nv)[9], auto U_, auto IT_) __attribute__((always_inline)) {
+    auto body = [&](typename IoT::Raw& nv, auto U_, auto IT_) __attribute__((always_inline)) {
         constexpr int U = decltype(U_)::value;
         constexpr int IT = decltype(IT_)::value;  // the fill's iteration, or -1: all stages run
         constexpr int B = U % 2;
@@ -1417,7 +1439,9 @@ __device__ __forceinline__ void stepS_tile_lds(const StepArgs& a, int x0, int w,
         for (int k = 0; k < S; ++k)
             if (IT < 0 || IT >= PER * k + 4) rf[k] = row_pair(a.vrowf, yk[k]);
         // ---- the row loaded two iterations ago into stage 0's ring
-        put(0, U_, nv);
+        float in[9];
+        io.unpack(nv, in);
+        put(0, U_, in);
         load(nv);
         lds_barrier();
 
@@ -1522,7 +1546,7 @@ __device__ __forceinline__ void stepS_tile_lds(const StepArgs& a, int x0, int w,
     };
     // two rows of loads in flight: row r + 2 is loaded while row r is processed,
     // into the register set row r came in
-    float nv[2][9];
+    typename IoT::Raw nv[2];
     load(nv[0]);
     load(nv[1]);
     unrolled([&](auto I) __attribute__((always_inline)) {
