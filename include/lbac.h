@@ -290,7 +290,10 @@ int lbac_batch_mass(lbac_batch* b, double* per_instance);
 
 /* Strip height (>= 8; the default is 40): an instance ny rows high is cut
  * into the nearest whole number of strips to ny / strip_h (at least one, at
- * most ny / 8) of balanced heights.  get_shape also gives the number of
+ * most ny / 8) of balanced heights, or into more where a run's instances do
+ * not fill the GPU with those: the instances with the most passes to take
+ * then get strips of fewer rows (12 at least), since their passes follow one
+ * another and a pass lasts as long as its strips are high.  get_shape also gives the number of
  * batch workgroups the device keeps resident at once (the grid of a batch
  * launch; the schedule's progress does not depend on it). */
 int lbac_batch_set_shape(lbac_batch* b, int32_t strip_h);

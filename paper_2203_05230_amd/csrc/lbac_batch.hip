@@ -32,6 +32,9 @@ namespace {
 constexpr int kBatchMinStrip = kBatchGrow + 2;
 // Slots of one batch launch at most (bounds the host tables).
 constexpr int64_t kBatchMaxSlots = int64_t(1) << 36;
+// Strips are cut finer than asked for only while a launch has at most this
+// many slots (a coarse index of 64 MB).
+constexpr int64_t kBatchFineSlots = int64_t(1) << 30;
 
 struct Geometry {
     int nx, ny;
@@ -71,61 +74,136 @@ std::vector<std::pair<int, int>> column_tiles(int nx) {
     return t;
 }
 
-// Items of every instance (instance-major, strips, tiles) and their dependency
-// lists: an item depends on itself and on every item of its instance whose
-// tile overlaps its read region, columns x0 - G .. x0 + w - 1 + G and rows
-// ys - G .. ys + hh - 1 + G (G = kBatchGrow, periodic).  Returns false if an
-// item would need more than kBatchDeps entries.
-bool build_items(const std::vector<Geometry>& geo, int strip_h, std::vector<ItemH>& items) {
+// Strips of an instance when cut at strip_h: the nearest whole number to ny /
+// strip_h (at least one, at most ny / kBatchMinStrip).
+int nearest_strips(int ny, int strip_h) {
+    return std::max(1, std::min((int)std::lround((double)ny / strip_h), ny / kBatchMinStrip));
+}
+
+// First row of strip j of nby: balanced heights (each strip costs its rows
+// plus the pipeline's fill, so a ragged last strip is avoided), cut at
+// multiples of the march's period where strips are long enough (the kernel
+// runs whole periods of rows).
+int strip_y0(int ny, int nby, int j) {
+    constexpr int Q = TileSRows<kBatchS>::kPeriod;
+    const int y = (int)((int64_t)j * ny / nby);
+    return j == nby || ny < 2 * Q * nby ? y : (y + Q / 2) / Q * Q;
+}
+
+// Items of every instance (instance-major, strips, tiles; instance k cut into
+// nby[k] strips) and their dependency lists: an item depends on itself and on
+// every item of its instance whose tile overlaps its read region, columns
+// x0 - G .. x0 + w - 1 + G and rows ys - G .. ys + hh - 1 + G (G = kBatchGrow,
+// periodic).  Returns false if an item would need more than kBatchDeps
+// entries.
+bool build_items(const std::vector<Geometry>& geo, const std::vector<int>& nby, std::vector<ItemH>& items) {
     constexpr int G = kBatchGrow;
     items.clear();
+    // of a periodic line of n places, part i being cut[i] .. cut[i + 1] - 1:
+    // the parts that part i grown by G places overlaps, in ascending order
+    auto overlaps = [](const std::vector<int>& cut, int n) {
+        std::vector<int> part_of(n);
+        for (int i = 0; i + 1 < (int)cut.size(); ++i)
+            for (int c = cut[i]; c < cut[i + 1]; ++c) part_of[c] = i;
+        std::vector<std::vector<int>> v(cut.size() - 1);
+        for (int i = 0; i + 1 < (int)cut.size(); ++i) {
+            v[i].push_back(i);
+            for (int g = 1; g <= G; ++g) {
+                v[i].push_back(part_of[(((cut[i] - g) % n) + n) % n]);
+                v[i].push_back(part_of[(cut[i + 1] - 1 + g) % n]);
+            }
+            std::sort(v[i].begin(), v[i].end());
+            v[i].erase(std::unique(v[i].begin(), v[i].end()), v[i].end());
+        }
+        return v;
+    };
     for (int k = 0; k < (int)geo.size(); ++k) {
         const int nx = geo[k].nx, ny = geo[k].ny;
-        const std::vector<std::pair<int, int>> ct = column_tiles(nx);
-        // the nearest whole number of strips to ny / strip_h (at least one,
-        // at most ny / kBatchMinStrip), of balanced heights: strip j covers
-        // rows [j ny / nby, (j + 1) ny / nby); each strip costs its rows plus
-        // the pipeline's fill, so a ragged last strip is avoided
-        const int nby = std::max(1, std::min((int)std::lround((double)ny / strip_h), ny / kBatchMinStrip));
-        const int nbx = (int)ct.size();
-        // cut at multiples of the march's period where strips are long enough
-        // (the kernel runs whole periods of rows)
-        constexpr int Q = TileSRows<kBatchS>::kPeriod;
-        auto strip_y0 = [&](int j) {
-            const int y = (int)((int64_t)j * ny / nby);
-            return j == nby || ny < 2 * Q * nby ? y : (y + Q / 2) / Q * Q;
-        };
-        std::vector<int> tile_of_col(nx), strip_of_row(ny);
-        for (int i = 0; i < nbx; ++i)
-            for (int c = ct[i].first; c < ct[i].first + ct[i].second; ++c) tile_of_col[c] = i;
-        for (int j = 0; j < nby; ++j)
-            for (int r = strip_y0(j); r < strip_y0(j + 1); ++r) strip_of_row[r] = j;
-        const int base = (int)items.size();
-        for (int j = 0; j < nby; ++j)
+        std::vector<int> xc, yc;
+        for (const auto& t : column_tiles(nx)) xc.push_back(t.first);
+        xc.push_back(nx);
+        for (int j = 0; j <= nby[k]; ++j) yc.push_back(strip_y0(ny, nby[k], j));
+        const std::vector<std::vector<int>> tx = overlaps(xc, nx), ty = overlaps(yc, ny);
+        const int nbx = (int)tx.size(), base = (int)items.size();
+        for (int j = 0; j < nby[k]; ++j)
             for (int i = 0; i < nbx; ++i) {
                 ItemH it;
                 it.inst = k;
-                it.x0 = ct[i].first;
-                it.w = ct[i].second;
-                it.ys = strip_y0(j);
-                it.hh = strip_y0(j + 1) - strip_y0(j);
+                it.x0 = xc[i];
+                it.w = xc[i + 1] - xc[i];
+                it.ys = yc[j];
+                it.hh = yc[j + 1] - yc[j];
                 it.down = j & 1;
-                std::vector<int> tx, ty;
-                for (int c = it.x0 - G; c <= it.x0 + it.w - 1 + G; ++c) tx.push_back(tile_of_col[((c % nx) + nx) % nx]);
-                for (int r = it.ys - G; r <= it.ys + it.hh - 1 + G; ++r) ty.push_back(strip_of_row[((r % ny) + ny) % ny]);
-                std::sort(tx.begin(), tx.end());
-                tx.erase(std::unique(tx.begin(), tx.end()), tx.end());
-                std::sort(ty.begin(), ty.end());
-                ty.erase(std::unique(ty.begin(), ty.end()), ty.end());
+                if ((int)(tx[i].size() * ty[j].size()) > kBatchDeps) return false;
+                it.dep.reserve(tx[i].size() * ty[j].size());
                 it.dep.push_back(base + j * nbx + i);
-                for (int jj : ty)
-                    for (int ii : tx)
+                for (int jj : ty[j])
+                    for (int ii : tx[i])
                         if (ii != i || jj != j) it.dep.push_back(base + jj * nbx + ii);
-                if ((int)it.dep.size() > kBatchDeps) return false;
                 items.push_back(std::move(it));
             }
     }
     return true;
+}
+
+// Strips of every instance for a run: strip_h rows each, or fewer where the
+// run is short of workgroups.
+//
+// A pass of an item takes the time of its rows and of about 14 more (the
+// pipeline's fill, the ticket and the wait), kRow each when the workgroup has
+// a compute unit to itself, and the passes of an instance follow one another:
+// the run takes at least the longest chain, passes x (rows + 14) x kRow.  And
+// a compute unit with all its workgroups resident takes kBusy per row of a
+// workgroup (four wavefronts) in all, an item costing it about 20 more than
+// its rows.  Shorter strips shorten the chain and add work.  Every
+// candidate gives each instance the tallest strips (at most strip_h, whole
+// periods) with which its own chain stays within a limit, so only the
+// instances with the most passes are cut finer; the one with the least of
+// the larger of the two estimates plus 0.4 times the smaller is taken.  (That
+// sum fits measured runs of 1 to 256 instances of 128^2 to 512^2 with strips
+// of 12 to 96 rows within 15% on either side of the crossing.)
+//
+// 64 instances of 128^2 to 512^2, strips of 72 rows asked for: 20.3 ms as
+// asked, 12.5 cut like this.  A lone 512^2 with strips of 40, 512 steps: 10.5,
+// 5.2.  256 instances, which fill the device: 10.2 either way.
+std::vector<int> choose_strips(const std::vector<Geometry>& geo, int strip_h, const int64_t* nsteps, int cus) {
+    constexpr int Q = TileSRows<kBatchS>::kPeriod, kLow = 2 * Q;  // (rows of the shortest strips cut here)
+    constexpr double kRow = 1.05, kBusy = 0.66;                  // us
+    const int count = (int)geo.size();
+    std::vector<int> uniform(count), best, nby(count);
+    std::vector<double> passes(count), waves(count, 0.0);
+    double longest = 0.0;
+    for (int k = 0; k < count; ++k) {
+        uniform[k] = nearest_strips(geo[k].ny, strip_h);
+        // (a one-step pass is about 0.6 of a full one)
+        passes[k] = (double)(nsteps[k] / kBatchS) + 0.6 * (double)(nsteps[k] % kBatchS);
+        longest = std::max(longest, passes[k]);
+        for (const auto& t : column_tiles(geo[k].nx)) waves[k] += (t.second + 4 * kBatchS + 63) / 64;
+    }
+    double best_t = 0.0;
+    for (int h = kLow; h < strip_h + Q; h += Q) {
+        const double limit = longest * (h + 14);
+        double chain = 0.0, work = 0.0, slots = 0.0;
+        for (int k = 0; k < count; ++k) {
+            const int ny = geo[k].ny;
+            nby[k] = uniform[k];
+            if (passes[k] > 0.0) {
+                const int hk = std::max(kLow, (int)std::min(limit / passes[k] - 14.0, 1e6) / Q * Q);
+                if (hk < strip_h) nby[k] = std::max(nby[k], std::min((ny + hk - 1) / hk, ny / kBatchMinStrip));
+            }
+            const double rows = ((double)ny / nby[k] + Q - 1) / Q * Q;  // about the tallest strip's
+            chain = std::max(chain, passes[k] * (rows + 14.0));
+            work += passes[k] * waves[k] / 4 * (ny + 20.0 * nby[k]);
+            slots += passes[k] * nby[k] * waves[k];
+        }
+        const double c = chain * kRow, w = work * kBusy / cus;
+        const double t = std::max(c, w) + 0.4 * std::min(c, w);
+        if (slots <= (double)kBatchFineSlots && (best.empty() || t < best_t)) {
+            best = nby;
+            best_t = t;
+        }
+    }
+    return best.empty() ? uniform : best;
 }
 
 // Classes of the instances (see batch_kernel): instances dealt largest work
@@ -223,7 +301,8 @@ struct lbac_batch {
     int test_stall = 0;
     bool failed = false;  // a run timed out: the state is undefined until the instances are set again
     // schedule
-    int items_h = -1;  // strip height the item list was built for
+    int cus = 1;
+    std::vector<int> strips;  // of each instance, as the item list was built
     std::vector<ItemH> items;
     int nitems = 0;
     int64_t nslots[2] = {0, 0};  // slots of the two launches of the current run
@@ -433,20 +512,20 @@ int run(lbac_batch* b, const int64_t* nsteps, bool dry, float* ms_out) {
     for (int k = 0; k < count; ++k)
         if (nsteps[k] < 0 || nsteps[k] > (int64_t)INT32_MAX) return bfail(b, LBAC_EINVAL, "step count out of range");
     if (b->strip_h < kBatchMinStrip) return bfail(b, LBAC_EINVAL, "strip height too small");
-    if (b->items_h != b->strip_h) {
-        std::vector<Geometry> geo(count);
-        for (int k = 0; k < count; ++k) geo[k] = {b->inst[k]->p.nx, b->inst[k]->p.ny};
-        if (!build_items(geo, b->strip_h, b->items)) return bfail(b, LBAC_EINVAL, "item dependency list too long");
+    std::vector<Geometry> geo(count);
+    for (int k = 0; k < count; ++k) geo[k] = {b->inst[k]->p.nx, b->inst[k]->p.ny};
+    std::vector<int> strips = choose_strips(geo, b->strip_h, nsteps, b->cus);
+    if (b->strips != strips) {
+        b->strips.clear();
+        if (!build_items(geo, strips, b->items)) return bfail(b, LBAC_EINVAL, "item dependency list too long");
         b->nitems = (int)b->items.size();
-        b->items_h = b->strip_h;
+        b->strips = std::move(strips);
     }
     std::vector<int64_t> pf(count), pr(count);
     for (int k = 0; k < count; ++k) {
         pf[k] = nsteps[k] / kBatchS;
         pr[k] = nsteps[k] % kBatchS;
     }
-    std::vector<Geometry> geo(count);
-    for (int k = 0; k < count; ++k) geo[k] = {b->inst[k]->p.nx, b->inst[k]->p.ny};
     const std::vector<int> cls_of = assign_classes(geo, nsteps);
     Slots sl[2];
     build_slots(b->items, pf, cls_of, sl[0]);
@@ -600,6 +679,7 @@ int lbac_batch_init(const lbac_params* params, const double* const* phi0, int32_
     if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, b->device) == hipSuccess && khz > 0)
         b->ticks_per_s = 1000.0 * khz;
     b->max_wgs = std::max(1, per_cu * cus);
+    b->cus = std::max(1, cus);
     if (hipMalloc(&b->d_inst, sizeof(BatchInst) * 2 * count) != hipSuccess ||
         hipMalloc(&b->d_ctl, sizeof(BatchCtl)) != hipSuccess || hipMalloc(&b->d_nent, 64) != hipSuccess ||
         hipMalloc(&b->d_first, sizeof(int32_t) * (count + 1)) != hipSuccess ||
@@ -721,7 +801,9 @@ int lbac_batch_schedule_check(const int32_t* nx, const int32_t* ny, const int64_
         pr[k] = nsteps[k] % kBatchS;
     }
     std::vector<ItemH> items;
-    if (!build_items(geo, strip_h, items)) return LBAC_EINVAL;
+    std::vector<int> strips(count);
+    for (int k = 0; k < count; ++k) strips[k] = nearest_strips(ny[k], strip_h);
+    if (!build_items(geo, strips, items)) return LBAC_EINVAL;
     const int n = (int)items.size();
     const std::vector<int> cls_of = assign_classes(geo, nsteps);
     // The state, per buffer and item tile: the pass (run-wide index) that last

@@ -267,3 +267,35 @@ def test_batch_stall_times_out_and_reports(gpu_lib):
             call(b.instance(0))
         assert ei.value.code == gpu_lib.LBAC_ESTATE
     b.close()
+
+
+@pytest.mark.parametrize("precision", ["f32", "f32_f16store"])
+@pytest.mark.parametrize("strip_h", [8, 20, 96])
+def test_batch_strips_follow_the_run(gpu_lib, precision, strip_h):
+    """Strips are cut finer for the instances with the most passes, so their
+    heights differ between instances and change between runs (a long run of
+    one instance, then of another, then equal counts): bitwise the single
+    runs, over heights with and without whole periods and instances too low
+    for a second strip."""
+    say("case: batch strips by run,", precision, strip_h)
+    shapes = [(130, 200), (64, 97), (40, 23), (33, 7), (250, 60)]
+    runs = [[41, 3, 6, 30, 0], [2, 50, 33, 3, 9], [12, 12, 12, 12, 12]]
+    cases, phis = [], []
+    for k, (nx, ny) in enumerate(shapes):
+        rng = np.random.default_rng(70 + k)
+        n = max(nx, ny)
+        phi = W.circle(n, 1.0, R_frac=0.3, yc_frac=0.5)[:ny, :nx] * 0.9 + 0.05 * rng.random((ny, nx))
+        cases.append(dict(nx=nx, ny=ny, eps=1.0, tau=0.8, delta=1e-10, vel="vortex", U=0.03, period_T=90.0))
+        phis.append(np.ascontiguousarray(phi))
+    b = gpu_lib.Batch(cases, phis, precision=precision)
+    b.set_shape(strip_h)
+    for steps in runs:
+        b.run(steps)
+    for k, (c, p) in enumerate(zip(cases, phis)):
+        sim = gpu_lib.Simulation({**c, "precision": precision}, p)
+        sim.set_launch(224, 40, 4)
+        for steps in runs:
+            sim.step(steps[k])
+        assert np.array_equal(b.instance(k).phi(), sim.phi()), (k, precision)
+        sim.close()
+    b.close()
