@@ -3,7 +3,7 @@
 //
 // FP32 throughout, on the FP32 matrix cores (16x16x4 MFMA, FP32 products and
 // sums), every reduction in a fixed order so a training run is reproducible:
-//   mlp_block_kernel   one wavefront per 16 samples: the forward pass
+//   mlp_block_kernel   four wavefronts per 16 samples: the forward pass
 //                      (Z1 = W1 X + b1, H1 = gelu(Z1), Z2 = W2 H1 + b2,
 //                      H2 = gelu(Z2), out = W3 H2 + b3), and for training the
 //                      backward pass (d3 = 2 (out - y) / B,
@@ -19,12 +19,13 @@
 // B[k][l % 16] with k the lane group l / 16 of the K-step, and receives
 // D[4 (l / 16) + i][l % 16], i = 0..3.  The forward products keep features on
 // the M side and samples on N, so the accumulator of a layer holds, in lane
-// (g, n), features 16 mt + 4 g + i of sample n, which is directly the next
-// layer's B operand for the K-steps (mt, i); the weight products take the
-// block's 16 samples as K from LDS.
+// (g, n), features 16 mt + 4 g + i of sample n (mt: the wavefront), which is
+// the next layer's B operand for the K-steps (mt, i), read back from LDS; the
+// weight products take the 16 samples as K from LDS.
 // Parameter layout: W1[64][25], b1[64], W2[64][64], b2[64], W3[2][64], b3[2].
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <string>
@@ -44,237 +45,300 @@ constexpr int kKin = 28;                       // inputs padded to whole K-steps
 
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ float gelu(float x) {
-    return 0.5f * x * (1.0f + tanhf(kGeluK * (x + 0.044715f * x * x * x)));
-}
-__device__ __forceinline__ float gelu_grad(float x) {
+// gelu(x) and its derivative from one tanh
+struct Gelu {
+    float v, d;
+};
+__device__ __forceinline__ Gelu gelu(float x) {
     const float t = tanhf(kGeluK * (x + 0.044715f * x * x * x));
-    return 0.5f * (1.0f + t) + 0.5f * x * (1.0f - t * t) * kGeluK * (1.0f + 3.0f * 0.044715f * x * x);
+    return {0.5f * x * (1.0f + t),
+            0.5f * (1.0f + t) + 0.5f * x * (1.0f - t * t) * kGeluK * (1.0f + 3.0f * 0.044715f * x * x)};
 }
 
 __device__ __forceinline__ f32x4_t mfma(float a, float b, f32x4_t c) {
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }
 
+// A layer of the 16 samples, samples x features.  Rows of 68 floats: the 16
+// samples' quadruples of one feature group, which a lane group reads as a
+// K-step operand, cover all 64 banks once.
+constexpr int kRow = kH + 4;
 struct MlpLds {
-    float w[kNParam];
-    float x[kNS][32];   // inputs of the block's samples (25..31 zero)
-    float h1[kH][kNS];  // gelu(z1), features x samples
-    float h2[kH][kNS];
-    float d1[kH][kNS];
-    float d2[kH][kNS];
-    float d3[kOut][kNS];
+    float x[kNS][32];  // inputs of the samples (25..31 zero)
+    float h1[kNS][kRow], h2[kNS][kRow], d1[kNS][kRow], d2[kNS][kRow];
+    float w3[kOut][kH];
 };
 
-// grad_rows: per block kNParam floats; loss_rows: per block one double; out
-// (forward only, may be null): batch x 2.  With train == false only the
-// forward pass runs.
+// One workgroup of four wavefronts per 16 samples at a time, wavefront mt on
+// the 16 features 16 mt .. 16 mt + 15 of each layer: lane (g, r) holds
+// features 16 mt + 4 g + i of sample r, hands them to the other wavefronts
+// through LDS, and keeps its share of the weights, in both directions, in
+// registers over the samples the workgroup takes (b = blockIdx, then every
+// gridDim-th 16).  Every product and sum runs in the order in which one
+// wavefront per 16 samples ran it.
+//
+// Bound by the latency of a chain (weights, two layers of dependent matrix
+// products and tanh, and back): a batch of 4096 is one workgroup per compute
+// unit.  One wavefront per 16 samples, weights staged through LDS: training
+// (forward) 40 (18) us at a batch of 4096, 130 (67) at 40000; this form 11
+// (5.5) and 50 (18).
+//
+// grad_rows: per 16 samples kNParam floats; loss_rows: per 16 samples one
+// double; out (forward only, may be null): batch x 2.  With TRAIN == false
+// only the forward pass runs.
+//
+// kBlkPerCu: workgroups resident per compute unit.  Training takes 208
+// registers, so two; at four it spills (batch 4096 16.7 us, 40000 59).
+constexpr int kBlkThreads = 256;
 template <bool TRAIN>
-__global__ __launch_bounds__(64) void mlp_block_kernel(const float* __restrict__ w, const float* __restrict__ x,
-                                                       const float* __restrict__ y, int64_t batch, float inv_b,
-                                                       float* __restrict__ out, float* __restrict__ grad_rows,
-                                                       double* __restrict__ loss_rows) {
+constexpr int kBlkPerCu = TRAIN ? 2 : 4;
+template <bool TRAIN>
+__global__ __launch_bounds__(kBlkThreads, kBlkPerCu<TRAIN>) void mlp_block_kernel(
+    const float* __restrict__ w, const float* __restrict__ x, const float* __restrict__ y, int64_t batch, float inv_b,
+    float* __restrict__ out, float* __restrict__ grad_rows, double* __restrict__ loss_rows) {
     __shared__ MlpLds L;
-    const int l = threadIdx.x, r = l % 16, g = l / 16;
-    const int64_t s0 = (int64_t)blockIdx.x * kNS;
-    for (int i = l; i < kNParam; i += 64) L.w[i] = w[i];
-    for (int i = l; i < kNS * 32; i += 64) {
-        const int n = i / 32, k = i % 32;
-        L.x[n][k] = (k < kIn && s0 + n < batch) ? x[(s0 + n) * kIn + k] : 0.f;
-    }
-    __syncthreads();
+    const int t = threadIdx.x, l = t % 64, r = l % 16, g = l / 16;
+    const int mt = __builtin_amdgcn_readfirstlane(t / 64);
+    const int f0 = 16 * mt + 4 * g;  // the lane's first feature
+    const int64_t nb = (batch + kNS - 1) / kNS;
+    auto quad = [&](int off) { return *reinterpret_cast<const f32x4_t*>(w + off); };
 
-    // ---- forward: lane (g, r) holds features 16 mt + 4 g + i of sample r
-    f32x4_t z1[4], z2[4];
+    // the wavefront's weights (layer 3's, which every wavefront takes whole, in
+    // LDS): rows 16 mt + r of W1 and W2 (forward), columns 16 mt + r of W2
+    // (backward)
+    float w1[kKin / 4], w2t[4][4];
+    f32x4_t w2[4];
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt) {
-        f32x4_t acc;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) acc[i] = L.w[ob1 + 16 * mt + 4 * g + i];
-#pragma unroll
-        for (int ks = 0; ks < kKin / 4; ++ks) {
-            const int k = 4 * ks + g;
-            acc = mfma(k < kIn ? L.w[oW1 + (16 * mt + r) * kIn + k] : 0.f, L.x[r][k], acc);
-        }
-        z1[mt] = acc;
+    for (int ks = 0; ks < kKin / 4; ++ks) {
+        const int k = 4 * ks + g;
+        w1[ks] = k < kIn ? w[oW1 + (16 * mt + r) * kIn + k] : 0.f;
     }
-    float h1[4][4];
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) h1[mt][i] = gelu(z1[mt][i]);
-#pragma unroll
-    for (int mt = 0; mt < 4; ++mt) {
-        f32x4_t acc;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) acc[i] = L.w[ob2 + 16 * mt + 4 * g + i];
+    for (int kt = 0; kt < 4; ++kt) w2[kt] = quad(oW2 + (16 * mt + r) * kH + 16 * kt + 4 * g);
+    if constexpr (TRAIN) {
 #pragma unroll
         for (int kt = 0; kt < 4; ++kt)
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-                acc = mfma(L.w[oW2 + (16 * mt + r) * kH + 16 * kt + 4 * g + i], h1[kt][i], acc);
-        z2[mt] = acc;
+            for (int i = 0; i < 4; ++i) w2t[kt][i] = w[oW2 + (16 * kt + 4 * g + i) * kH + 16 * mt + r];
     }
-    float h2[4][4];
-#pragma unroll
-    for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) h2[mt][i] = gelu(z2[mt][i]);
-    // layer 3 on the vector units: each lane's 16 features, then the four
-    // lane groups of a sample summed pairwise (the same order on every lane)
-    float o[2];
-#pragma unroll
-    for (int c = 0; c < kOut; ++c) {
-        float p = 0.f;
-#pragma unroll
-        for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) p = __builtin_fmaf(L.w[oW3 + c * kH + 16 * mt + 4 * g + i], h2[mt][i], p);
-        p += __shfl_xor(p, 16, 64);
-        p += __shfl_xor(p, 32, 64);
-        o[c] = L.w[ob3 + c] + p;
-    }
-    const int64_t s = s0 + r;
-    const bool real = s < batch;
-    if (!TRAIN) {
-        if (out && g == 0 && real) {
-            out[s * kOut] = o[0];
-            out[s * kOut + 1] = o[1];
-        }
-        return;
-    }
+    const f32x4_t b1 = quad(ob1 + f0), b2 = quad(ob2 + f0);
+    const float b3[kOut] = {w[ob3], w[ob3 + 1]};
+    if (t < kOut * kH) L.w3[t / kH][t % kH] = w[oW3 + t];
 
-    // ---- loss and backward
-    const float e0 = real ? o[0] - y[s * kOut] : 0.f;
-    const float e1 = real ? o[1] - y[s * kOut + 1] : 0.f;
-    const float d30 = 2.0f * e0 * inv_b, d31 = 2.0f * e1 * inv_b;
-    float d2r[4][4];
+    for (int64_t b = blockIdx.x; b < nb; b += gridDim.x) {
+        const int64_t s0 = b * kNS;
+        for (int i = t; i < kNS * 32; i += kBlkThreads) {
+            const int n = i / 32, k = i % 32;
+            L.x[n][k] = (k < kIn && s0 + n < batch) ? x[(s0 + n) * kIn + k] : 0.f;
+        }
+        __syncthreads();
+
+        // ---- forward
+        f32x4_t acc = b1;
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt)
+        for (int ks = 0; ks < kKin / 4; ++ks) acc = mfma(w1[ks], L.x[r][4 * ks + g], acc);
+        f32x4_t h, gd1, gd2;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const int k = 16 * mt + 4 * g + i;
-            d2r[mt][i] = (L.w[oW3 + k] * d30 + L.w[oW3 + kH + k] * d31) * gelu_grad(z2[mt][i]);
+            const Gelu a = gelu(acc[i]);
+            h[i] = a.v;
+            gd1[i] = a.d;
         }
-    // d1 = (W2^T d2) * gelu'(z1): A[row k1][feature k] = W2[k][k1]
+        *reinterpret_cast<f32x4_t*>(&L.h1[r][f0]) = h;
+        __syncthreads();
+        acc = b2;
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt) {
-        f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+        for (int kt = 0; kt < 4; ++kt) {
+            const f32x4_t v = *reinterpret_cast<const f32x4_t*>(&L.h1[r][16 * kt + 4 * g]);
 #pragma unroll
-        for (int kt = 0; kt < 4; ++kt)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) acc = mfma(L.w[oW2 + (16 * kt + 4 * g + i) * kH + 16 * mt + r], d2r[kt][i], acc);
+            for (int i = 0; i < 4; ++i) acc = mfma(w2[kt][i], v[i], acc);
+        }
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const int k = 16 * mt + 4 * g + i;
-            L.d1[k][r] = acc[i] * gelu_grad(z1[mt][i]);
-            L.h1[k][r] = h1[mt][i];
-            L.h2[k][r] = h2[mt][i];
-            L.d2[k][r] = d2r[mt][i];
+            const Gelu a = gelu(acc[i]);
+            h[i] = a.v;
+            gd2[i] = a.d;
         }
-    }
-    if (g == 0) {
-        L.d3[0][r] = d30;
-        L.d3[1][r] = d31;
-    }
-    // the block's loss share: squared errors of its samples in sample order
-    {
-        const double se = (double)e0 * e0 + (double)e1 * e1;
-        double t = 0.0;
-        for (int n = 0; n < kNS; ++n) t += __shfl(se, n, 64);
-        if (l == 0) loss_rows[blockIdx.x] = t;
-    }
-    __syncthreads();
-
-    // ---- the block's gradient rows: K = the block's 16 samples
-    float* G = grad_rows + (int64_t)blockIdx.x * kNParam;
-    // dW1 [64 x 25] = d1 X^T (N-tiles of 16 inputs)
+        *reinterpret_cast<f32x4_t*>(&L.h2[r][f0]) = h;
+        __syncthreads();
+        // layer 3 on the vector units, on every wavefront: the lane group's 16
+        // features, then the four lane groups of a sample summed pairwise (the
+        // same order on every lane)
+        f32x4_t h2[4];
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt)
+        for (int kt = 0; kt < 4; ++kt) h2[kt] = *reinterpret_cast<const f32x4_t*>(&L.h2[r][16 * kt + 4 * g]);
+        float o[kOut];
+#pragma unroll
+        for (int c = 0; c < kOut; ++c) {
+            float p = 0.f;
+#pragma unroll
+            for (int kt = 0; kt < 4; ++kt) {
+                const f32x4_t w3 = *reinterpret_cast<const f32x4_t*>(&L.w3[c][16 * kt + 4 * g]);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) p = __builtin_fmaf(w3[i], h2[kt][i], p);
+            }
+            p += __shfl_xor(p, 16, 64);
+            p += __shfl_xor(p, 32, 64);
+            o[c] = b3[c] + p;
+        }
+        const int64_t s = s0 + r;
+        const bool real = s < batch;
+        if constexpr (!TRAIN) {
+            if (out && mt == 0 && g == 0 && real) {
+                out[s * kOut] = o[0];
+                out[s * kOut + 1] = o[1];
+            }
+            // (the next samples' inputs and h1 are read by no wavefront that is
+            // still here: all have passed the barrier after h2)
+            continue;
+        }
+
+        // ---- loss and backward
+        const float e0 = real ? o[0] - y[s * kOut] : 0.f;
+        const float e1 = real ? o[1] - y[s * kOut + 1] : 0.f;
+        const float d30 = 2.0f * e0 * inv_b, d31 = 2.0f * e1 * inv_b;
+        {
+            const f32x4_t wa = *reinterpret_cast<const f32x4_t*>(&L.w3[0][f0]);
+            const f32x4_t wb = *reinterpret_cast<const f32x4_t*>(&L.w3[1][f0]);
+            f32x4_t d;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) d[i] = (wa[i] * d30 + wb[i] * d31) * gd2[i];
+            *reinterpret_cast<f32x4_t*>(&L.d2[r][f0]) = d;
+        }
+        __syncthreads();
+        // d1 = (W2^T d2) * gelu'(z1)
+        acc = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int kt = 0; kt < 4; ++kt) {
+            const f32x4_t v = *reinterpret_cast<const f32x4_t*>(&L.d2[r][16 * kt + 4 * g]);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc = mfma(w2t[kt][i], v[i], acc);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[i] = acc[i] * gd1[i];
+        *reinterpret_cast<f32x4_t*>(&L.d1[r][f0]) = acc;
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");  // (read back below by other lanes of this wavefront)
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+
+        // ---- the gradient rows of these samples: K = the 16 samples
+        float* G = grad_rows + b * kNParam;
+        // dW2 [64 x 64] = d2 H1^T, this wavefront's 16 rows
+        float a2[4];
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) a2[ks] = L.d2[4 * ks + g][16 * mt + r];
+#pragma unroll
+        for (int nt = 0; nt < 4; ++nt) {
+            acc = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) acc = mfma(a2[ks], L.h1[4 * ks + g][16 * nt + r], acc);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) G[oW2 + (f0 + i) * kH + 16 * nt + r] = acc[i];
+        }
+        // dW1 [64 x 25] = d1 X^T (N-tiles of 16 inputs); d1 of this
+        // wavefront's features, which it wrote itself
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) a2[ks] = L.d1[4 * ks + g][16 * mt + r];
 #pragma unroll
         for (int nt = 0; nt < 2; ++nt) {
-            f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+            acc = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int ks = 0; ks < kNS / 4; ++ks) acc = mfma(L.d1[16 * mt + r][4 * ks + g], L.x[4 * ks + g][16 * nt + r], acc);
+            for (int ks = 0; ks < 4; ++ks) acc = mfma(a2[ks], L.x[4 * ks + g][16 * nt + r], acc);
             const int k = 16 * nt + r;
             if (k < kIn)
 #pragma unroll
-                for (int i = 0; i < 4; ++i) G[oW1 + (16 * mt + 4 * g + i) * kIn + k] = acc[i];
+                for (int i = 0; i < 4; ++i) G[oW1 + (f0 + i) * kIn + k] = acc[i];
         }
-    // dW2 [64 x 64] = d2 H1^T
+        __syncthreads();  // d1 of every feature
+        // dW3 [2 x 64] = d3 H2^T (wavefronts 0, 1) and the bias rows
+        // (wavefronts 2, 3): sums over samples in order; d3 of sample n in lane n
+        if (mt < 2) {
+            const float d3 = mt == 0 ? d30 : d31;
+            float a = 0.f, bs = 0.f;
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt)
+            for (int n = 0; n < kNS; ++n) {
+                const float dn = __shfl(d3, n, 64);
+                a = __builtin_fmaf(dn, L.h2[n][l], a);
+                bs += dn;
+            }
+            G[oW3 + mt * kH + l] = a;
+            if (l == 0) G[ob3 + mt] = bs;
+        } else {
+            float bs = 0.f;
+            const float(*d)[kRow] = mt == 2 ? L.d1 : L.d2;
 #pragma unroll
-        for (int nt = 0; nt < 4; ++nt) {
-            f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int ks = 0; ks < kNS / 4; ++ks)
-                acc = mfma(L.d2[16 * mt + r][4 * ks + g], L.h1[16 * nt + r][4 * ks + g], acc);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) G[oW2 + (16 * mt + 4 * g + i) * kH + 16 * nt + r] = acc[i];
+            for (int n = 0; n < kNS; ++n) bs += d[n][l];
+            G[(mt == 2 ? ob1 : ob2) + l] = bs;
         }
-    // dW3 [2 x 64] = d3 H2^T and the bias rows: sums over samples in order
-    {
-        float a0 = 0.f, a1 = 0.f, b1s = 0.f, b2s = 0.f;
-        for (int n = 0; n < kNS; ++n) {
-            a0 = __builtin_fmaf(L.d3[0][n], L.h2[l][n], a0);
-            a1 = __builtin_fmaf(L.d3[1][n], L.h2[l][n], a1);
-            b1s += L.d1[l][n];
-            b2s += L.d2[l][n];
+        // the samples' loss share: squared errors in sample order
+        if (mt == 3) {
+            const double se = (double)e0 * e0 + (double)e1 * e1;
+            double a = 0.0;
+#pragma unroll
+            for (int n = 0; n < kNS; ++n) a += __shfl(se, n, 64);
+            if (l == 0) loss_rows[b] = a;
         }
-        G[oW3 + l] = a0;
-        G[oW3 + kH + l] = a1;
-        G[ob1 + l] = b1s;
-        G[ob2 + l] = b2s;
-        if (l < kOut) {
-            float b3s = 0.f;
-            for (int n = 0; n < kNS; ++n) b3s += L.d3[l][n];
-            G[ob3 + l] = b3s;
-        }
+        __syncthreads();  // every value of these samples has been read
     }
 }
 
-// The gradient as the sum of the blocks' rows, in a fixed order: a block of
-// 256 threads takes 64 parameters; thread (q, p) sums the rows b = q mod 4
-// with four running sums (rows q, q + 4, q + 8, q + 12 modulo 16), which
-// are then added pairwise, and the four quarters are added pairwise again.
-// With adam != 0 the Adam update of the weights follows.  Block 0 also sums
+// The gradient as the sum of the blocks' rows, in a fixed order: row b belongs
+// to sum b mod 16, each taken in ascending order by a thread of its own (16
+// loads each at a batch of 4096); sum 4 u + q is the u-th of quarter q, the
+// four of a quarter are added pairwise and the four quarters are added
+// pairwise again.  A workgroup takes 32 parameters, whole 128-byte lines: 187
+// of them and one for the loss.  (64 parameters and four sums per thread, 94
+// workgroups: 11.2 us at a batch of 4096; this form 4.4.)
+// With adam != 0 the Adam update of the weights follows.  The last block sums
 // the loss shares (thread t the rows t mod 256, then a pairwise tree) into
 // *loss (divided by the batch size).
-constexpr int kRedParams = 64;
-__global__ __launch_bounds__(256) void mlp_reduce_kernel(const float* __restrict__ grad_rows,
-                                                         const double* __restrict__ loss_rows, int nblk,
-                                                         int64_t batch, float* __restrict__ grad,
-                                                         double* __restrict__ loss, int adam, float* __restrict__ w,
-                                                         float* __restrict__ m, float* __restrict__ v, float lr,
-                                                         float b1, float b2, float eps, float c1, float c2) {
-    __shared__ float part[4][kRedParams];
-    __shared__ double lsum[256];
-    const int t = threadIdx.x, q = t / kRedParams, pl = t % kRedParams;
-    const int p = blockIdx.x * kRedParams + pl;
-    if (blockIdx.x == 0) {
-        double a = 0.0;
-        for (int b = t; b < nblk; b += 256) a += loss_rows[b];
-        lsum[t] = a;
+constexpr int kRedParams = 32, kRedSums = 16;
+constexpr int kRedBlocks = (kNParam + kRedParams - 1) / kRedParams + 1;
+__global__ __launch_bounds__(kRedParams* kRedSums) void mlp_reduce_kernel(
+    const float* __restrict__ grad_rows, const double* __restrict__ loss_rows, int nblk, int64_t batch,
+    float* __restrict__ grad, double* __restrict__ loss, int adam, float* __restrict__ w, float* __restrict__ m,
+    float* __restrict__ v, float lr, float b1, float b2, float eps, float c1, float c2) {
+    __shared__ float part[kRedSums][kRedParams];
+    const int t = threadIdx.x;
+    if (blockIdx.x == kRedBlocks - 1) {
+        __shared__ double lsum[256];
+        if (t < 256) {
+            double a = 0.0;
+            for (int b = t; b < nblk; b += 256) a += loss_rows[b];
+            lsum[t] = a;
+        }
         __syncthreads();
         for (int h = 128; h > 0; h >>= 1) {
             if (t < h) lsum[t] += lsum[t + h];
             __syncthreads();
         }
         if (t == 0) loss[0] = lsum[0] / (double)batch;
+        return;
     }
-    float acc[4] = {0.f, 0.f, 0.f, 0.f};
+    const int sum = t / kRedParams, pl = t % kRedParams;
+    const int p = blockIdx.x * kRedParams + pl;
+    float acc = 0.f;
     if (p < kNParam) {
-        int b = q;
-        for (; b + 12 < nblk; b += 16)
+        // eight rows in flight
+        int b = sum;
+        const float* row = grad_rows + (int64_t)b * kNParam + p;
+        constexpr int64_t kStep = (int64_t)kRedSums * kNParam;
+        for (; b + 7 * kRedSums < nblk; b += 8 * kRedSums, row += 8 * kStep) {
+            float in[8];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) acc[u] += grad_rows[(int64_t)(b + 4 * u) * kNParam + p];
-        for (int u = 0; b < nblk; b += 4, ++u) acc[u] += grad_rows[(int64_t)b * kNParam + p];
+            for (int u = 0; u < 8; ++u) in[u] = row[u * kStep];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) acc += in[u];
+        }
+        for (; b < nblk; b += kRedSums, row += kStep) acc += row[0];
     }
-    part[q][pl] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+    part[sum][pl] = acc;
     __syncthreads();
-    if (q != 0 || p >= kNParam) return;
-    const float gp = (part[0][pl] + part[1][pl]) + (part[2][pl] + part[3][pl]);
+    if (sum != 0 || p >= kNParam) return;
+    float quarter[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) quarter[q] = (part[q][pl] + part[4 + q][pl]) + (part[8 + q][pl] + part[12 + q][pl]);
+    const float gp = (quarter[0] + quarter[1]) + (quarter[2] + quarter[3]);
     grad[p] = gp;
     if (!adam) return;
     const float mp = b1 * m[p] + (1.0f - b1) * gp;
@@ -314,6 +378,12 @@ int mfail(lbac_mlp* h, int code, const std::string& msg) {
     } while (0)
 
 int64_t blocks_of(int64_t batch) { return (batch + kNS - 1) / kNS; }
+// Workgroups of the block kernel: what a device of 256 compute units keeps
+// resident, each taking several 16 samples beyond that.
+template <bool TRAIN>
+unsigned grid_of(int64_t batch) {
+    return (unsigned)std::min<int64_t>(blocks_of(batch), 256 * kBlkPerCu<TRAIN>);
+}
 
 int ensure(lbac_mlp* h, int64_t batch) {
     const int64_t nb = blocks_of(batch);
@@ -336,7 +406,7 @@ int gradient_step(lbac_mlp* h, const float* x, const float* y, int64_t batch, fl
     int rc = ensure(h, batch);
     if (rc != LBAC_OK) return rc;
     const int nb = (int)blocks_of(batch);
-    hipLaunchKernelGGL(mlp_block_kernel<true>, dim3(nb), dim3(64), 0, h->stream, h->w, x, y, batch,
+    hipLaunchKernelGGL(mlp_block_kernel<true>, dim3(grid_of<true>(batch)), dim3(kBlkThreads), 0, h->stream, h->w, x, y, batch,
                        1.0f / (float)batch, (float*)nullptr, h->grad_rows, h->loss_rows);
     float c1 = 1.f, c2 = 1.f;
     if (lr > 0.f) {
@@ -344,7 +414,7 @@ int gradient_step(lbac_mlp* h, const float* x, const float* y, int64_t batch, fl
         c1 = (float)(1.0 - std::pow(0.9, (double)h->t));
         c2 = (float)(1.0 - std::pow(0.999, (double)h->t));
     }
-    hipLaunchKernelGGL(mlp_reduce_kernel, dim3((kNParam + kRedParams - 1) / kRedParams), dim3(256), 0, h->stream,
+    hipLaunchKernelGGL(mlp_reduce_kernel, dim3(kRedBlocks), dim3(kRedParams * kRedSums), 0, h->stream,
                        h->grad_rows,
                        h->loss_rows, nb, batch, h->g, h->loss, lr > 0.f ? 1 : 0, h->w, h->m, h->v, lr, 0.9f, 0.999f,
                        1e-8f, c1, c2);
@@ -423,7 +493,7 @@ int lbac_mlp_set_weights(lbac_mlp* h, const float* in) {
 int lbac_mlp_forward(lbac_mlp* h, const float* x_dev, int64_t batch, float* out_dev) {
     if (!h || !x_dev || !out_dev || batch < 1) return LBAC_EINVAL;
     if (batch > ((int64_t)1 << 31) * kNS) return mfail(h, LBAC_EINVAL, "batch too large");
-    hipLaunchKernelGGL(mlp_block_kernel<false>, dim3((unsigned)blocks_of(batch)), dim3(64), 0, h->stream, h->w, x_dev,
+    hipLaunchKernelGGL(mlp_block_kernel<false>, dim3(grid_of<false>(batch)), dim3(kBlkThreads), 0, h->stream, h->w, x_dev,
                        (const float*)nullptr, batch, 1.0f / (float)batch, out_dev, (float*)nullptr, (double*)nullptr);
     MHIP(h, hipGetLastError());
     return LBAC_OK;

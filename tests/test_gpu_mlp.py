@@ -97,3 +97,30 @@ def test_training_reduces_loss(gpu_lib):
         net.train_step(xd.data_ptr(), yd.data_ptr(), 4096, 3e-3)
     last = net.train_step(xd.data_ptr(), yd.data_ptr(), 4096, 3e-3, want_loss=True)
     assert last < 0.1 * first
+
+
+@pytest.mark.parametrize("B", [8192, 8193, 16391, 16384 + 8192 + 5])
+def test_batches_beyond_the_resident_workgroups(gpu_lib, B):
+    """Workgroups that take several groups of 16 samples (more than 512 groups
+    in training, 1024 in the forward pass), whole and ragged last groups: the
+    outputs are bitwise those of the same samples in small batches, and the
+    gradient, the FP32 sum of the groups' shares, is within the tolerance of
+    test_loss_and_gradient_match_oracle of the FP64 one."""
+    import torch
+
+    say("case: mlp, batch", B)
+    w = M.init_weights(21, scale=1.3).astype(np.float32)
+    X, Y = data(5, B)
+    net = gpu_lib.Mlp(w)
+    xd, yd = dev(torch, X), dev(torch, Y)
+    od, pd = (torch.empty((B, 2), dtype=torch.float32, device="cuda") for _ in range(2))
+    net.forward(xd.data_ptr(), B, od.data_ptr())
+    for s in range(0, B, 4096):
+        net.forward(xd[s:].data_ptr(), min(4096, B - s), pd[s:].data_ptr())
+    torch.cuda.synchronize()
+    assert torch.equal(od, pd)
+    L, g = net.loss_grad(xd.data_ptr(), yd.data_ptr(), B)
+    Lr, gr = M.loss_and_grad(w.astype(np.float64), X.astype(np.float64), Y.astype(np.float64))
+    assert L == pytest.approx(Lr, rel=1e-5)
+    assert np.linalg.norm(g - gr) <= 2e-5 * np.linalg.norm(gr)
+    assert np.max(np.abs(g - gr)) <= 2e-5 * np.max(np.abs(gr))
