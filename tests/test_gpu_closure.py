@@ -240,3 +240,47 @@ def test_trained_closure_reduces_shape_error(gpu_lib):
     truth = [r["closure_vs_plain_truth"] for r in rows]
     say("  |closure - fine| / |plain - fine|:", ["%.3f" % v for v in truth])
     assert max(truth) < 1.0
+
+
+@pytest.mark.parametrize("nxf,nyf,r", [(37, 64, 1), (130, 70, 2), (99, 45, 3), (264, 80, 8), (320, 96, 16),
+                                       (340, 102, 17), (700, 24, 1), (2300, 20, 2)])
+def test_extraction_tiles_rows_and_chunks(gpu_lib, nxf, nyf, r):
+    """Ragged tiles, the largest factor that is tiled and the first that is
+    not, rows of band nodes longer than a pass over the columns (512) and than
+    a chunk of nodes (128), and a row with more than 1024 (counted, but only
+    the first 1024 are written): within the tolerances of
+    test_extraction_matches_oracle."""
+    import torch
+
+    say("case: closure sample extraction", nxf, nyf, r)
+    rng = np.random.default_rng(nxf)
+    if nyf < 30:
+        phi_f = 0.2 + 0.6 * rng.random((nyf, nxf))  # (nearly) every node in the band
+    else:
+        n = max(nxf, nyf)
+        phi_f = W.circle(n, float(r), R_frac=0.25, yc_frac=0.5 * nyf / n)[:nyf, :nxf] + 1e-3 * rng.standard_normal((nyf, nxf))
+    phi_f = np.ascontiguousarray(phi_f)
+    phi_c, tx, ty = CR.target(phi_f, float(r), 1.0, r=r)
+    mask = CR.band(phi_c, 0.02)
+    Xr, jj, ii = CR.stencils(phi_c, mask)
+    Yr = np.stack([tx[mask], ty[mask]], 1)
+    ordinal = np.arange(len(jj)) - np.searchsorted(jj, jj)  # place of the node in its row
+    written = ordinal < 1024
+    ws = torch.empty(gpu_lib.closure_workspace_bytes(nxf, nyf, r), dtype=torch.uint8, device="cuda")
+    pf = torch.from_numpy(phi_f).cuda()
+    for augment, base in ((False, 3), (True, 0)):
+        m = 8 if augment else 1
+        cap = base + m * len(Xr)
+        X = torch.full((cap + 4, 25), -7.0, dtype=torch.float32, device="cuda")
+        Y = torch.full((cap + 4, 2), -7.0, dtype=torch.float32, device="cuda")
+        n = gpu_lib.closure_extract(pf.data_ptr(), nxf, nyf, r, float(r), 1.0, 1e-10, 0.02, augment, ws.data_ptr(),
+                                    X.data_ptr(), Y.data_ptr(), base, cap - m)  # (the last node does not fit)
+        assert n == m * len(Xr) > 0
+        Xg, Yg = X.cpu().numpy(), Y.cpu().numpy()
+        w = written.copy()
+        w[-1] = False
+        first = Xg[base:cap].reshape(-1, m, 25)[:, 0], Yg[base:cap].reshape(-1, m, 2)[:, 0]
+        assert np.max(np.abs(first[0][w] - Xr[w])) <= 1e-7
+        assert np.max(np.abs(first[1][w] - Yr[w])) <= 1e-6 * max(1.0, np.max(np.abs(Yr)))
+        assert np.all(Xg[base:cap].reshape(-1, m, 25)[~w] == -7.0) and np.all(Yg[base:cap].reshape(-1, m, 2)[~w] == -7.0)
+        assert np.all(Xg[:base] == -7.0) and np.all(Xg[cap:] == -7.0)
