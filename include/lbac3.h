@@ -91,7 +91,10 @@ int lbac3_time(lbac3_ctx* h, int64_t* t);
  * tiles with x fastest, then y, then the strip; 1: the strip index fastest.
  * Even strips march up and odd strips down, so two neighbouring strips read
  * the planes they share at the same time.  Results do not depend on the
- * launch shape (bitwise).  LBAC_EINVAL for other values. */
+ * launch shape (bitwise).  LBAC_EINVAL for other values.  Until a shape is
+ * set, or chosen by lbac3_autotune, steps take one chosen by the grid's size;
+ * lbac3_get_launch then reports the shape the context was created with
+ * (32 x 16, LBAC3_KEEP, 32 planes). */
 #define LBAC3_KEEP 0
 #define LBAC3_REPULL 1
 #define LBAC3_PREFETCH 2

@@ -23,7 +23,6 @@ using lbac::kDropOffset;
 using lbac::lds_barrier;
 using lbac::Math;
 using lbac::plane_rsrc;
-using lbac::time_factor;
 using lbac::wrap_idx;
 using lbac::xcd_tile;
 
@@ -55,8 +54,9 @@ struct Args3 {
     int32_t z_major;       // 1: tile order with the strip index fastest
     const double* vtab;    // per component u, v, w: factors over x (nx), y (ny), z (nz)
     const int64_t* t_dev;
+    const double* tfac;    // time factors from t_dev on (see lbac::fill_factors)
     int32_t k;             // step offset within a chunk of launches
-    double period_T, eps, tau, delta;
+    double delta, psi_scale, s_scale, omega, kforce, keep;  // (see make_args3)
     int32_t time_dep;      // 1: velocity scaled by cos(pi t / T)
 };
 
@@ -116,15 +116,11 @@ __global__ __launch_bounds__(TX * TY) void step3_kernel(Args3 a) {
     // plane entering at iteration i (from one below the strip up, or from one
     // above it down); the plane updated at iteration i is the one of i - 1
     auto plane_at = [&](int i) { return wrap_idx(down ? z0 + hz - i : z0 - 1 + i, a.nz); };
-    const int64_t t = a.t_dev[0] + a.k;
-
-    const bool first = (t == 0);
-    const R s_now = a.time_dep ? R(time_factor(a.period_T, t)) : R(1);
-    const R s_old = first ? s_now : (a.time_dep ? R(time_factor(a.period_T, t - 1)) : R(1));
-    const R delta = R(a.delta);
-    const R psi_scale = R(a.eps * 0.69314718055994530942);
-    const R s_scale = R(1.0 / (a.eps * (1.0 + 2.0 * a.delta) * (1.0 + 2.0 * a.delta)));
-    const R omega = R(1.0 / a.tau), kforce = R(1.0 - 0.5 / a.tau), keep = R(1.0 - 1.0 / a.tau);
+    const bool first = a.t_dev[0] + a.k == 0;
+    const R s_now = a.time_dep ? R(a.tfac[a.k + 1]) : R(1);
+    const R s_old = first ? s_now : (a.time_dep ? R(a.tfac[a.k]) : R(1));
+    const R delta = R(a.delta), psi_scale = R(a.psi_scale), s_scale = R(a.s_scale);
+    const R omega = R(a.omega), kforce = R(a.kforce), keep = R(a.keep);
     const int L = a.nx + a.ny + a.nz;
     // x and y factors of the three velocity components for this column
     const R fxu = R(a.vtab[gx]), fyu = R(a.vtab[a.nx + gy]);
@@ -132,14 +128,22 @@ __global__ __launch_bounds__(TX * TY) void step3_kernel(Args3 a) {
     const R fxw = R(a.vtab[2 * L + gx]), fyw = R(a.vtab[2 * L + a.nx + gy]);
 
     const R* pold_plane = static_cast<const R*>(a.phi_old);
-    R* dst = static_cast<R*>(a.dst);
     const int64_t zs = (int64_t)a.pitch * a.ny;  // elements per z plane
     // Pull sources: column gx - c_x, row gy - c_y (wrapped once per thread), as
     // 32-bit byte offsets from uniform plane bases (a plane is below 2 GiB).
-    const char* sb = static_cast<const char*>(a.src);
     const uint32_t pb = (uint32_t)(a.plane_stride * (int64_t)sizeof(R));  // bytes between planes (< 2^31)
     const uint32_t rowb = (uint32_t)a.pitch * (uint32_t)sizeof(R);
     const uint32_t zsb = (uint32_t)zs * (uint32_t)sizeof(R);
+    // The 19 planes' bases are formed anew, one from the other, wherever they
+    // are used: held through the march (38 scalar registers for the loads, 80
+    // for the stores' resources) they spilled to vector lanes, 80 to 170 reads
+    // of which per plane: 200^3 in FP32, 128 x 8 tiles, 332 us, 313 like this.
+    typedef const __attribute__((address_space(1))) char* Global;
+    auto walk = [](const void* p) __attribute__((always_inline)) {
+        uint64_t v = (uint64_t)p;
+        asm volatile("" : "+s"(v));
+        return v;
+    };
     struct Col {
         uint32_t x[3], y[3];  // index c + 1
     };
@@ -158,9 +162,10 @@ __global__ __launch_bounds__(TX * TY) void step3_kernel(Args3 a) {
     auto pull = [&](const Col& c, int zp, R (&v)[19]) __attribute__((always_inline)) {
         const uint32_t zoff[3] = {(uint32_t)wrap_idx(zp + 1, a.nz) * zsb, (uint32_t)zp * zsb,
                                   (uint32_t)wrap_idx(zp - 1, a.nz) * zsb};  // plane zp - c_z, index c_z + 1
+        Global b = (Global)walk(a.src);
 #pragma unroll
-        for (int q = 0; q < 19; ++q)
-            v[q] = *reinterpret_cast<const R*>(sb + (size_t)q * pb + (zoff[cz3(q) + 1] + c.y[cy3(q) + 1] + c.x[cx3(q) + 1]));
+        for (int q = 0; q < 19; ++q, b += pb)
+            v[q] = *reinterpret_cast<const __attribute__((address_space(1))) R*>(b + (zoff[cz3(q) + 1] + c.y[cy3(q) + 1] + c.x[cx3(q) + 1]));
     };
     auto pold_at = [&](int zp) { return pold_plane[(int64_t)zp * zs + (int64_t)gy * a.pitch + gx]; };
     auto psi_of = [&](R phi) {
@@ -245,15 +250,14 @@ __global__ __launch_bounds__(TX * TY) void step3_kernel(Args3 a) {
         // at 256^3)
         const uint32_t node = (uint32_t)((int64_t)zc * zs + (int64_t)gy * a.pitch + gx);
         const uint32_t b = st ? node * (uint32_t)sizeof(R) : kDropOffset;
-        if constexpr (sizeof(R) == 4) {
+        uint64_t d = walk(a.dst);
 #pragma unroll
-            for (int q = 0; q < 19; ++q) lbac::bstore_nt(out[q], plane_rsrc(dst + (size_t)q * a.plane_stride), b);
-            lbac::bstore_nt(phi, plane_rsrc(a.phi_new), b);
-        } else {
-#pragma unroll
-            for (int q = 0; q < 19; ++q) bstore(out[q], plane_rsrc(dst + (size_t)q * a.plane_stride), b);
-            bstore(phi, plane_rsrc(a.phi_new), b);
+        for (int q = 0; q < 19; ++q, d += pb) {
+            if constexpr (sizeof(R) == 4) lbac::bstore_nt(out[q], plane_rsrc((void*)d), b);
+            else bstore(out[q], plane_rsrc((void*)d), b);
         }
+        if constexpr (sizeof(R) == 4) lbac::bstore_nt(phi, plane_rsrc(a.phi_new), b);
+        else bstore(phi, plane_rsrc(a.phi_new), b);
     };
 
     lds_barrier();
@@ -321,7 +325,7 @@ __global__ void init3_kernel(Args3 a, const double* __restrict__ phi0) {
     const int x = blockIdx.x * blockDim.x + threadIdx.x, y = blockIdx.y, z = blockIdx.z;
     if (x >= a.nx) return;
     const int L = a.nx + a.ny + a.nz;
-    const double s0 = a.time_dep ? time_factor(a.period_T, 0) : 1.0;
+    const double s0 = a.time_dep ? a.tfac[1] : 1.0;
     R* dst = static_cast<R*>(a.dst);
     const int64_t zs = (int64_t)a.pitch * a.ny, off = (int64_t)z * zs + (int64_t)y * a.pitch + x;
     for (int q = 0; q < 19; ++q) {
@@ -388,10 +392,6 @@ __global__ void sum_parts_kernel(const double* __restrict__ part, int nparts, do
     }
 }
 
-__global__ void advance3_kernel(int64_t* t_dev, int64_t n) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) t_dev[0] += n;
-}
-
 }  // namespace lbac3
 
 // ---------------------------------------------------------------------------
@@ -409,6 +409,7 @@ struct lbac3_ctx {
     void* phis[2] = {nullptr, nullptr};
     double* vtab = nullptr;
     int64_t* t_dev = nullptr;
+    double* tfac = nullptr;   // time factors from t_dev on (kTimeFactors + 1 values)
     double* dtmp = nullptr;   // nz*ny*nx doubles
     double* dref = nullptr;   // nz*ny*nx doubles (reference field)
     double* part = nullptr;   // partial sums
@@ -422,6 +423,7 @@ struct lbac3_ctx {
     int tile_y = 16;
     int mode = 0;        // 0 keep, 1 re-pull, 2 prefetch (see step3_kernel)
     int z_major = 0;     // tile order: 0 x fastest, 1 strip fastest
+    bool shape_set = false;  // by lbac3_set_launch or lbac3_autotune; else launches follow the grid's size
     std::string err;
 };
 
@@ -524,7 +526,69 @@ int validate3(const lbac3_params* p, std::string& why) {
     return LBAC_OK;
 }
 
-lbac3::Args3 make_args3(const lbac3_ctx* h, int src, int32_t k) {
+// Tile shapes (columns along x and y).  Blocks of 1024 threads need at most
+// 128 registers per lane, which the FP64 update exceeds: those shapes are
+// FP32 only.
+constexpr int kShapes[][2] = {{32, 8}, {32, 16}, {64, 4}, {64, 8}, {128, 4}, {32, 32}, {64, 16}, {128, 8}};
+
+bool tile_ok(int precision, int tile_x, int tile_y) {
+    for (const auto& sh : kShapes)
+        if (sh[0] == tile_x && sh[1] == tile_y) return tile_x * tile_y <= 512 || precision == LBAC_F32;
+    return false;
+}
+
+struct Shape3 {
+    int tx, ty, mode, sz, zm;  // tile, variant, strip, tile order
+};
+
+// The shape of a step when none has been set, by the grid's size.  A workgroup
+// marches its strip plane by plane, so a step takes at least the time of one
+// strip: its planes and two more, each kAlone and kWave more per wavefront (its
+// own and its rim's) of the workgroups that share a compute unit.  And it
+// takes the time of its traffic, kNode per node a workgroup pulls, a row of
+// its tile counting kEdge nodes more (partial lines), a tile a row and a strip
+// kEnd planes more.  Of the tiles and strips of 1 to 64 planes the one with
+// the least of the larger of the two is taken: few planes where the grid is
+// too small to fill the device, wide tiles and long strips where it is large.
+// The constants are fitted to steps of sixteen grids of 24 x 31 x 24 to 256^3
+// in every shape; the choice is within 14% of the best shape there in FP32
+// (24% in FP64), 5% on average.  Tiles of 1024 columns keep the next plane's
+// loads in flight, as FP64 does; the others keep more workgroups resident
+// instead.
+// us per step, with the shape before (32 x 16 tiles, strips of 32 planes) and
+// with this one: FP32 24 x 31 x 89 101 and 10, 64^3 125 and 19, 128^3 145 and
+// 79, 200^3 468 and 360, 256^3 674 and 541; FP64 64^3 169 and 29, 128^3 265 and
+// 149.
+Shape3 auto_shape3(const lbac3_params& p) {
+    const bool f64 = p.precision == LBAC_F64;
+    const double kAlone = f64 ? 0.0 : 2.1, kWave = f64 ? 0.45 : 0.14;
+    const double kNode = f64 ? 30e-6 : 21e-6, kEdge = f64 ? 30.0 : 26.0, kEnd = f64 ? 1.1 : 0.74;
+    const int strips[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64};
+    Shape3 best{};
+    double best_t = -1.0;
+    for (const auto& sh : kShapes) {
+        const int tx = sh[0], ty = sh[1];
+        if (!tile_ok(p.precision, tx, ty) || (f64 && (tx * ty != 512 || tx == 128))) continue;
+        const int waves = tx * ty / 64 + (2 * (tx + 2) + 2 * ty + 63) / 64;
+        for (int sz : strips) {
+            if (sz > p.nz) continue;
+            const int64_t n = (int64_t)((p.nx + tx - 1) / tx) * ((p.ny + ty - 1) / ty) * ((p.nz + sz - 1) / sz);
+            const double t = std::max((sz + 2) * (kAlone + kWave * (double)((n + 255) / 256) * waves),
+                                      kNode * n * (sz + kEnd) * (ty + 1) * (tx + kEdge));
+            if (best_t < 0.0 || t < best_t) {
+                best_t = t;
+                best = Shape3{tx, ty, f64 || tx * ty == 1024 ? 2 : 0, sz, 0};
+            }
+        }
+    }
+    return best;
+}
+
+Shape3 shape3(const lbac3_ctx* h) {
+    return h->shape_set ? Shape3{h->tile_x, h->tile_y, h->mode, h->strip_z, h->z_major} : auto_shape3(h->p);
+}
+
+lbac3::Args3 make_args3(const lbac3_ctx* h, int src, int32_t k, const Shape3& sh) {
     lbac3::Args3 a{};
     a.src = h->pop[src];
     a.dst = h->pop[1 - src];
@@ -535,67 +599,63 @@ lbac3::Args3 make_args3(const lbac3_ctx* h, int src, int32_t k) {
     a.nx = h->p.nx;
     a.ny = h->p.ny;
     a.nz = h->p.nz;
-    a.strip_z = std::min(h->strip_z, h->p.nz);
-    a.nbx = (h->p.nx + h->tile_x - 1) / h->tile_x;
-    a.nby = (h->p.ny + h->tile_y - 1) / h->tile_y;
+    a.strip_z = std::min(sh.sz, h->p.nz);
+    a.nbx = (h->p.nx + sh.tx - 1) / sh.tx;
+    a.nby = (h->p.ny + sh.ty - 1) / sh.ty;
     a.nbz = (h->p.nz + a.strip_z - 1) / a.strip_z;
     a.n_xcd = 8;
-    a.z_major = h->z_major;
+    a.z_major = sh.zm;
     a.vtab = h->vtab;
     a.t_dev = h->t_dev;
+    a.tfac = h->tfac;
     a.k = k;
-    a.period_T = h->p.period_T > 0.0 ? h->p.period_T : 1.0;
-    a.eps = h->p.eps;
-    a.tau = h->p.tau;
-    a.delta = h->p.delta;
+    const double eps = h->p.eps, tau = h->p.tau, delta = h->p.delta;
+    a.delta = delta;
+    a.psi_scale = eps * 0.69314718055994530942;
+    a.s_scale = 1.0 / (eps * (1.0 + 2.0 * delta) * (1.0 + 2.0 * delta));
+    a.omega = 1.0 / tau;
+    a.kforce = 1.0 - 0.5 / tau;
+    a.keep = 1.0 - 1.0 / tau;
     a.time_dep = (h->p.vel_kind == LBAC3_VEL_DEFORMATION || h->p.vel_kind == LBAC3_VEL_VORTEX_XY) ? 1 : 0;
     return a;
 }
+lbac3::Args3 make_args3(const lbac3_ctx* h, int src) { return make_args3(h, src, 0, Shape3{32, 16, 0, 32, 0}); }
+
+double period3(const lbac3_ctx* h) { return h->p.period_T > 0.0 ? h->p.period_T : 1.0; }
 
 template <typename R, int TX, int TY>
-void launch3_shape(const lbac3_ctx* h, const lbac3::Args3& a, dim3 grid) {
+void launch3_shape(const lbac3_ctx* h, const lbac3::Args3& a, dim3 grid, int mode) {
     const dim3 block(TX * TY);
-    if (h->mode == 1)
+    if (mode == 1)
         hipLaunchKernelGGL((lbac3::step3_kernel<R, TX, TY, 1>), grid, block, 0, h->stream, a);
-    else if (h->mode == 2)
+    else if (mode == 2)
         hipLaunchKernelGGL((lbac3::step3_kernel<R, TX, TY, 2>), grid, block, 0, h->stream, a);
     else
         hipLaunchKernelGGL((lbac3::step3_kernel<R, TX, TY, 0>), grid, block, 0, h->stream, a);
 }
 
-// Tile shapes (columns along x and y).  Blocks of 1024 threads need at most
-// 128 registers per lane, which the FP64 update exceeds: those shapes are
-// FP32 only.
-constexpr int kShapes[][2] = {{32, 8}, {32, 16}, {64, 4}, {64, 8}, {128, 4}, {32, 32}, {64, 16}, {128, 8}};
-
-bool tile_ok(const lbac3_ctx* h, int tile_x, int tile_y) {
-    for (const auto& sh : kShapes)
-        if (sh[0] == tile_x && sh[1] == tile_y) return tile_x * tile_y <= 512 || h->p.precision == LBAC_F32;
-    return false;
-}
-
 template <typename R>
-void launch3_t(const lbac3_ctx* h, const lbac3::Args3& a, dim3 grid) {
-    const int tx = h->tile_x, ty = h->tile_y;
-    if (tx == 32 && ty == 8) launch3_shape<R, 32, 8>(h, a, grid);
-    else if (tx == 32 && ty == 16) launch3_shape<R, 32, 16>(h, a, grid);
-    else if (tx == 64 && ty == 4) launch3_shape<R, 64, 4>(h, a, grid);
-    else if (tx == 64 && ty == 8) launch3_shape<R, 64, 8>(h, a, grid);
-    else if (tx == 128 && ty == 4) launch3_shape<R, 128, 4>(h, a, grid);
+void launch3_t(const lbac3_ctx* h, const lbac3::Args3& a, dim3 grid, const Shape3& sh) {
+    const int tx = sh.tx, ty = sh.ty;
+    if (tx == 32 && ty == 8) launch3_shape<R, 32, 8>(h, a, grid, sh.mode);
+    else if (tx == 32 && ty == 16) launch3_shape<R, 32, 16>(h, a, grid, sh.mode);
+    else if (tx == 64 && ty == 4) launch3_shape<R, 64, 4>(h, a, grid, sh.mode);
+    else if (tx == 64 && ty == 8) launch3_shape<R, 64, 8>(h, a, grid, sh.mode);
+    else if (tx == 128 && ty == 4) launch3_shape<R, 128, 4>(h, a, grid, sh.mode);
     else if constexpr (sizeof(R) == 4) {
-        if (tx == 32 && ty == 32) launch3_shape<R, 32, 32>(h, a, grid);
-        else if (tx == 64 && ty == 16) launch3_shape<R, 64, 16>(h, a, grid);
-        else if (tx == 128 && ty == 8) launch3_shape<R, 128, 8>(h, a, grid);
+        if (tx == 32 && ty == 32) launch3_shape<R, 32, 32>(h, a, grid, sh.mode);
+        else if (tx == 64 && ty == 16) launch3_shape<R, 64, 16>(h, a, grid, sh.mode);
+        else if (tx == 128 && ty == 8) launch3_shape<R, 128, 8>(h, a, grid, sh.mode);
     }
 }
 
-hipError_t launch_step3(const lbac3_ctx* h, int src, int32_t k) {
-    const lbac3::Args3 a = make_args3(h, src, k);
+hipError_t launch_step3(const lbac3_ctx* h, int src, int32_t k, const Shape3& sh) {
+    const lbac3::Args3 a = make_args3(h, src, k, sh);
     const dim3 grid(a.nbx * a.nby * a.nbz);
     if (h->p.precision == LBAC_F64)
-        launch3_t<double>(h, a, grid);
+        launch3_t<double>(h, a, grid, sh);
     else
-        launch3_t<float>(h, a, grid);
+        launch3_t<float>(h, a, grid, sh);
     return hipGetLastError();
 }
 
@@ -606,6 +666,7 @@ void release3(lbac3_ctx* h) {
     }
     if (h->vtab) (void)hipFree(h->vtab);
     if (h->t_dev) (void)hipFree(h->t_dev);
+    if (h->tfac) (void)hipFree(h->tfac);
     if (h->dtmp) (void)hipFree(h->dtmp);
     if (h->dref) (void)hipFree(h->dref);
     if (h->part) (void)hipFree(h->part);
@@ -614,16 +675,21 @@ void release3(lbac3_ctx* h) {
     if (h->own_stream && h->stream) (void)hipStreamDestroy(h->stream);
 }
 
+// phi of the current state into out (device, nz*ny*nx doubles)
+hipError_t launch_phi3(const lbac3_ctx* h, double* out) {
+    const lbac3::Args3 a = make_args3(h, h->cur);
+    const dim3 grid((a.nx + 255) / 256, a.ny, a.nz);
+    if (h->p.precision == LBAC_F64)
+        hipLaunchKernelGGL(lbac3::phi3_kernel<double>, grid, dim3(256), 0, h->stream, a, out);
+    else
+        hipLaunchKernelGGL(lbac3::phi3_kernel<float>, grid, dim3(256), 0, h->stream, a, out);
+    return hipGetLastError();
+}
+
 int sums3(lbac3_ctx* h, const double* ref_host, double out[5]) {
     lbac_host::DeviceGuard g(h->device);
     const int64_t n = (int64_t)h->p.nx * h->p.ny * h->p.nz;
-    lbac3::Args3 a = make_args3(h, h->cur, 0);
-    const dim3 grid((h->p.nx + 255) / 256, h->p.ny, h->p.nz);
-    if (h->p.precision == LBAC_F64)
-        hipLaunchKernelGGL(lbac3::phi3_kernel<double>, grid, dim3(256), 0, h->stream, a, h->dtmp);
-    else
-        hipLaunchKernelGGL(lbac3::phi3_kernel<float>, grid, dim3(256), 0, h->stream, a, h->dtmp);
-    HIP3(h, hipGetLastError());
+    HIP3(h, launch_phi3(h, h->dtmp));
     if (ref_host) HIP3(h, hipMemcpyAsync(h->dref, ref_host, n * sizeof(double), hipMemcpyHostToDevice, h->stream));
     const int64_t chunk = (n + kNParts - 1) / kNParts;
     const int nparts = (int)((n + chunk - 1) / chunk);
@@ -709,16 +775,18 @@ int lbac3_init(const lbac3_params* p, const double* phi0, lbac3_ctx** out) {
     std::vector<double> tab;
     build_tables(*p, tab);
     if (hipMalloc(&h->vtab, tab.size() * sizeof(double)) != hipSuccess || hipMalloc(&h->t_dev, 64) != hipSuccess ||
+        hipMalloc(&h->tfac, (lbac::kTimeFactors + 1) * sizeof(double)) != hipSuccess ||
         hipMalloc(&h->dtmp, n * sizeof(double)) != hipSuccess || hipMalloc(&h->dref, n * sizeof(double)) != hipSuccess ||
         hipMalloc(&h->part, 5 * kNParts * sizeof(double)) != hipSuccess || hipMalloc(&h->out5, 64) != hipSuccess ||
         hipHostMalloc((void**)&h->host5, 64, hipHostMallocDefault) != hipSuccess)
         return bail(LBAC_ENOMEM, "tables");
     if (hipMemcpyAsync(h->vtab, tab.data(), tab.size() * sizeof(double), hipMemcpyHostToDevice, h->stream) != hipSuccess ||
-        hipMemsetAsync(h->t_dev, 0, 64, h->stream) != hipSuccess ||
         hipMemcpyAsync(h->dtmp, phi0, n * sizeof(double), hipMemcpyHostToDevice, h->stream) != hipSuccess)
         return bail(LBAC_EDEVICE, "upload");
     h->cur = 0;
-    lbac3::Args3 a = make_args3(h, 1, 0);  // dst = pop[0], phi_new = phis[0]
+    hipLaunchKernelGGL(lbac::set_time_kernel, dim3(1), dim3(lbac::kTimeThreads), 0, h->stream, h->t_dev, h->tfac,
+                       period3(h), (int64_t)0);
+    lbac3::Args3 a = make_args3(h, 1);  // dst = pop[0], phi_new = phis[0]
     const dim3 grid((p->nx + 255) / 256, p->ny, p->nz);
     if (p->precision == LBAC_F64)
         hipLaunchKernelGGL(lbac3::init3_kernel<double>, grid, dim3(256), 0, h->stream, a, h->dtmp);
@@ -734,14 +802,17 @@ int lbac3_step(lbac3_ctx* h, int64_t n) {
     if (!h || n < 0) return LBAC_EINVAL;
     lbac_host::DeviceGuard g(h->device);
     // each launch reads the device step counter plus its offset within the
-    // current run of launches; the counter advances after every run
+    // current run of launches; the counter advances, and the time factors with
+    // it, after every run
+    const Shape3 sh = shape3(h);
     int32_t pending = 0;
     for (int64_t s = 0; s < n; ++s) {
-        HIP3(h, launch_step3(h, h->cur, pending));
+        HIP3(h, launch_step3(h, h->cur, pending, sh));
         h->cur ^= 1;
         ++pending;
-        if (pending == (1 << 20) || s == n - 1) {
-            hipLaunchKernelGGL(lbac3::advance3_kernel, dim3(1), dim3(64), 0, h->stream, h->t_dev, (int64_t)pending);
+        if (pending == lbac::kTimeFactors || s == n - 1) {
+            hipLaunchKernelGGL(lbac::advance_kernel, dim3(1), dim3(lbac::kTimeThreads), 0, h->stream, h->t_dev, h->tfac,
+                               period3(h), (int64_t)pending);
             HIP3(h, hipGetLastError());
             pending = 0;
         }
@@ -754,13 +825,7 @@ int lbac3_phi(lbac3_ctx* h, double* out) {
     if (!h || !out) return LBAC_EINVAL;
     lbac_host::DeviceGuard g(h->device);
     const int64_t n = (int64_t)h->p.nx * h->p.ny * h->p.nz;
-    lbac3::Args3 a = make_args3(h, h->cur, 0);
-    const dim3 grid((h->p.nx + 255) / 256, h->p.ny, h->p.nz);
-    if (h->p.precision == LBAC_F64)
-        hipLaunchKernelGGL(lbac3::phi3_kernel<double>, grid, dim3(256), 0, h->stream, a, h->dtmp);
-    else
-        hipLaunchKernelGGL(lbac3::phi3_kernel<float>, grid, dim3(256), 0, h->stream, a, h->dtmp);
-    HIP3(h, hipGetLastError());
+    HIP3(h, launch_phi3(h, h->dtmp));
     HIP3(h, hipMemcpyAsync(out, h->dtmp, n * sizeof(double), hipMemcpyDeviceToHost, h->stream));
     HIP3(h, hipStreamSynchronize(h->stream));
     return LBAC_OK;
@@ -796,7 +861,7 @@ int lbac3_set_launch(lbac3_ctx* h, int32_t tile_x, int32_t tile_y, int32_t varia
                      int32_t z_major) {
     if (!h) return LBAC_EINVAL;
     if (z_major != 0 && z_major != 1) return fail3(h, LBAC_EINVAL, "z_major must be 0 or 1");
-    if (!tile_ok(h, tile_x, tile_y))
+    if (!tile_ok(h->p.precision, tile_x, tile_y))
         return fail3(h, LBAC_EINVAL, "tile shape must be 32x8, 32x16, 64x4, 64x8, 128x4 (or, with FP32, 32x32, 64x16, 128x8)");
     if (variant < 0 || variant > 2) return fail3(h, LBAC_EINVAL, "variant must be 0, 1 or 2");
     if (strip_z < 1) return fail3(h, LBAC_EINVAL, "strip_z must be >= 1");
@@ -805,6 +870,7 @@ int lbac3_set_launch(lbac3_ctx* h, int32_t tile_x, int32_t tile_y, int32_t varia
     h->mode = variant;
     h->strip_z = std::min(strip_z, h->p.nz);
     h->z_major = z_major;
+    h->shape_set = true;
     return LBAC_OK;
 }
 
@@ -825,8 +891,7 @@ int lbac3_autotune(lbac3_ctx* h, int32_t steps, double* us_per_step) {
     hipEvent_t e0, e1;
     HIP3(h, hipEventCreate(&e0));
     HIP3(h, hipEventCreate(&e1));
-    const int keep = h->strip_z, keep_tx = h->tile_x, keep_ty = h->tile_y, keep_rp = h->mode, keep_zm = h->z_major;
-    int best_s = keep, best_tx = keep_tx, best_ty = keep_ty, best_rp = keep_rp, best_zm = keep_zm;
+    Shape3 best_sh = shape3(h);
     float best = 1e30f;
     hipError_t e = hipSuccess;
     // strips: powers of two, and nz split into k equal parts (so that a grid
@@ -836,25 +901,18 @@ int lbac3_autotune(lbac3_ctx* h, int32_t steps, double* us_per_step) {
     for (int k = 1; k <= 16; ++k) strips.push_back((h->p.nz + k - 1) / k);
     std::sort(strips.begin(), strips.end());
     strips.erase(std::unique(strips.begin(), strips.end()), strips.end());
-    struct Shape {
-        int tx, ty, rp, sz, zm;
-    };
-    std::vector<Shape> shapes;
+    std::vector<Shape3> shapes{auto_shape3(h->p)};
     for (const auto& sh : kShapes)
         for (int rp = 0; rp < 3; ++rp)
             for (int sz : strips)
                 for (int zm = 0; zm < 2; ++zm)
-                    if (tile_ok(h, sh[0], sh[1]) && !(zm == 1 && sz == h->p.nz)) shapes.push_back({sh[0], sh[1], rp, sz, zm});
-    for (const Shape& c : shapes) {
-        h->tile_x = c.tx;
-        h->tile_y = c.ty;
-        h->mode = c.rp;
-        h->strip_z = c.sz;
-        h->z_major = c.zm;
+                    if (tile_ok(h->p.precision, sh[0], sh[1]) && !(zm == 1 && sz == h->p.nz))
+                        shapes.push_back({sh[0], sh[1], rp, sz, zm});
+    for (const Shape3& c : shapes) {
         // repeated step from pop[cur] into the other buffer: the state is untouched
-        for (int w = 0; w < 2 && e == hipSuccess; ++w) e = launch_step3(h, h->cur, 0);
+        for (int w = 0; w < 2 && e == hipSuccess; ++w) e = launch_step3(h, h->cur, 0, c);
         if (e == hipSuccess) e = hipEventRecord(e0, h->stream);
-        for (int s = 0; s < steps && e == hipSuccess; ++s) e = launch_step3(h, h->cur, 0);
+        for (int s = 0; s < steps && e == hipSuccess; ++s) e = launch_step3(h, h->cur, 0, c);
         if (e == hipSuccess) e = hipEventRecord(e1, h->stream);
         if (e == hipSuccess) e = hipEventSynchronize(e1);
         float ms = 0.f;
@@ -862,21 +920,18 @@ int lbac3_autotune(lbac3_ctx* h, int32_t steps, double* us_per_step) {
         if (e != hipSuccess) break;
         if (ms < best) {
             best = ms;
-            best_s = c.sz;
-            best_tx = c.tx;
-            best_ty = c.ty;
-            best_rp = c.rp;
-            best_zm = c.zm;
+            best_sh = c;
         }
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
-    h->strip_z = e == hipSuccess ? best_s : keep;
-    h->tile_x = e == hipSuccess ? best_tx : keep_tx;
-    h->tile_y = e == hipSuccess ? best_ty : keep_ty;
-    h->mode = e == hipSuccess ? best_rp : keep_rp;
-    h->z_major = e == hipSuccess ? best_zm : keep_zm;
     if (e != hipSuccess) return fail3(h, LBAC_EDEVICE, std::string("autotune: ") + hipGetErrorString(e));
+    h->tile_x = best_sh.tx;
+    h->tile_y = best_sh.ty;
+    h->mode = best_sh.mode;
+    h->strip_z = best_sh.sz;
+    h->z_major = best_sh.zm;
+    h->shape_set = true;
     if (us_per_step) *us_per_step = 1000.0 * best / steps;
     return LBAC_OK;
 }

@@ -175,3 +175,24 @@ def test_autotune_keeps_state(gpu_lib):
     b.step(4)
     assert np.array_equal(a.phi(), b.phi())
     assert a.bytes_per_node() == 152.0
+
+
+@pytest.mark.parametrize("precision", ["f64", "f32"])
+@pytest.mark.parametrize("nx,ny,nz", [(3, 2, 1), (24, 31, 9), (70, 40, 33), (33, 130, 17), (130, 65, 70)])
+def test_launches_by_grid_size_equal_a_set_shape(gpu_lib, precision, nx, ny, nz):
+    """With no shape set the tile and strip follow the grid's size (one-plane
+    strips, narrow and wide tiles, more strips than planes): bitwise the
+    32 x 8 tiles with strips of 5 planes.  270 steps in one call pass the
+    table of time factors (256 steps) once; the other context takes them in
+    calls of 1, 255 and 14, and phi is read where the grid is ragged in every
+    direction."""
+    say("case: 3-D launches by grid size", precision, nx, ny, nz)
+    c = dict(nx=nx, ny=ny, nz=nz, eps=1.0, tau=0.8, delta=1e-10, vel="deformation", U=0.02, period_T=300.0)
+    phi0 = np.random.default_rng(nx).uniform(0.05, 0.95, size=(nz, ny, nx))
+    a = gpu(gpu_lib, c, phi0, 270, precision)
+    assert a.get_launch() == (32, 16, 0, 32, 0)
+    b = gpu(gpu_lib, c, phi0, 1, precision, launch=(32, 8, 0, 5))
+    b.step(255)
+    b.step(14)
+    assert np.array_equal(a.phi(), b.phi())
+    assert a.mass() == b.mass()
