@@ -287,19 +287,28 @@ struct Shape {
 constexpr Shape kF32[] = {{6, 8, 8, 7.5f, 3.7f},   {4, 16, 16, 6.4f, 2.8f}, {6, 24, 24, 14.3f, 11.4f},
                           {4, 32, 16, 7.8f, 4.1f}, {3, 52, 20, 8.3f, 5.2f}, {2, 24, 24, 5.4f, 2.2f},
                           {1, 28, 28, 5.0f, 2.1f}};
-// FP64 (for example 2.34 us per step with four steps of 8 x 8 at 64^2, 3.3
-// with four of 16 x 16 at 200^2, 31 and 436 with three of 52 x 20 at 1024^2
-// and 4096^2; the best one-step strips 7.2, 9.8, 37 and 522 us).
-constexpr Shape kF64[] = {{4, 8, 8, 10.f, 6.5f},    {4, 16, 16, 13.3f, 10.6f}, {3, 20, 20, 11.1f, 9.1f},
-                          {3, 52, 20, 19.f, 20.f}, {2, 24, 24, 9.9f, 8.3f},   {1, 28, 28, 6.6f, 6.f}};
+// FP64 is bound by its instructions where a SIMD has more than a wavefront or
+// two, so small patches and just enough threads for the grown patch pay
+// (us per step: 1.97 with three steps of 4 x 4 at 64^2, 2.37 with three of 8 x
+// 8 at 100^2, 2.83 with four of 12 x 8 at 150^2, 3.14 with three of 13 x 13
+// at 200^2, 7.3 with two of 16 x 16 at 400^2, 31 and 436 with three of 52 x 20
+// at 1024^2 and 4096^2; with only four steps of 8 x 8 or 16 x 16 before, 2.41,
+// 2.55, 3.37, 3.50 and 9.0; the best one-step strips 7.2 at 64^2, 9.8 at
+// 200^2, 37 and 522).
+constexpr Shape kF64[] = {{3, 4, 4, 5.9f, 1.65f},   {3, 8, 8, 7.f, 3.1f},     {4, 12, 8, 11.f, 5.7f},
+                          {3, 13, 13, 9.3f, 5.f},   {3, 16, 16, 10.5f, 7.5f}, {2, 16, 16, 7.5f, 4.2f},
+                          {3, 20, 20, 11.1f, 9.1f}, {2, 24, 24, 9.9f, 8.3f},  {3, 52, 20, 19.f, 20.f},
+                          {1, 28, 28, 6.6f, 6.f}};
 // 16-bit storage: one step, since a launch rounds once (5.2, 7.1, 11.3 and
 // 16.0 us at 256^2, 512^2, 768^2 and 1024^2; strips 7.9, 9.6, 13.9 and 16.9).
 constexpr Shape kF16[] = {{1, 28, 28, 5.2f, 2.1f}};
-// FP32 with the closure, a disk's edge in the field (5.7, 14.3, 26 and 43 us
-// per step at 128^2, 512^2, 1024^2 and 1536^2; the two-pass launches at their
-// best 17.8, 17.7, 21.7 and 32).
-constexpr Shape kCl[] = {{4, 8, 8, 23.f, 9.f}, {3, 14, 14, 20.f, 5.f}, {2, 20, 20, 15.f, 6.5f}, {2, 52, 20, 24.f, 8.5f},
-                         {1, 26, 26, 10.f, 3.4f}};
+// FP32 with the closure, a disk's edge in the field (5.2, 6.6, 7.3 and 12.8 us
+// per step at 128^2, 200^2, 256^2 and 512^2; with four steps of 8 x 8, three of
+// 14 x 14 and two of 20 x 20 before, 5.7, 7.9, 8.1 and 14.3; the two-pass
+// launches at their best 17.8 at 128^2, 17.7 at 512^2 and 21.7 at 1024^2).
+constexpr Shape kCl[] = {{2, 8, 8, 10.5f, 2.4f},  {2, 14, 14, 13.f, 4.2f},  {2, 16, 16, 14.f, 5.7f},
+                         {2, 20, 20, 15.f, 6.5f}, {1, 16, 16, 8.4f, 1.9f}, {2, 52, 20, 24.f, 8.5f},
+                         {1, 26, 26, 9.8f, 3.f}};
 
 template <typename R, int ST, int MODEL, int S, int PW, int PH, int NT, bool CL = false>
 hipError_t go(StepArgs a, hipStream_t s) {
@@ -334,15 +343,23 @@ template <int MODEL>
 hipError_t go_f64(int shape, const StepArgs& a, hipStream_t s) {
     switch (shape) {
     case 0:
-        return go<double, ST_PLAIN, MODEL, 4, 8, 8, 576>(a, s);
+        return go<double, ST_PLAIN, MODEL, 3, 4, 4, 256>(a, s);
     case 1:
-        return go<double, ST_PLAIN, MODEL, 4, 16, 16, 1024>(a, s);
+        return go<double, ST_PLAIN, MODEL, 3, 8, 8, 448>(a, s);
     case 2:
-        return go<double, ST_PLAIN, MODEL, 3, 20, 20, 1024>(a, s);
+        return go<double, ST_PLAIN, MODEL, 4, 12, 8, 704>(a, s);
     case 3:
-        return go<double, ST_PLAIN, MODEL, 3, 52, 20, 1024>(a, s);
+        return go<double, ST_PLAIN, MODEL, 3, 13, 13, 640>(a, s);
     case 4:
+        return go<double, ST_PLAIN, MODEL, 3, 16, 16, 832>(a, s);
+    case 5:
+        return go<double, ST_PLAIN, MODEL, 2, 16, 16, 576>(a, s);
+    case 6:
+        return go<double, ST_PLAIN, MODEL, 3, 20, 20, 1024>(a, s);
+    case 7:
         return go<double, ST_PLAIN, MODEL, 2, 24, 24, 1024>(a, s);
+    case 8:
+        return go<double, ST_PLAIN, MODEL, 3, 52, 20, 1024>(a, s);
     default:
         return go<double, ST_PLAIN, MODEL, 1, 28, 28, 1024>(a, s);
     }
@@ -351,12 +368,16 @@ hipError_t go_f64(int shape, const StepArgs& a, hipStream_t s) {
 hipError_t go_cl(int shape, const StepArgs& a, hipStream_t s) {
     switch (shape) {
     case 0:
-        return go<float, ST_PLAIN, MODEL_IMPROVED, 4, 8, 8, 1024, true>(a, s);
+        return go<float, ST_PLAIN, MODEL_IMPROVED, 2, 8, 8, 448, true>(a, s);
     case 1:
-        return go<float, ST_PLAIN, MODEL_IMPROVED, 3, 14, 14, 1024, true>(a, s);
+        return go<float, ST_PLAIN, MODEL_IMPROVED, 2, 14, 14, 704, true>(a, s);
     case 2:
-        return go<float, ST_PLAIN, MODEL_IMPROVED, 2, 20, 20, 1024, true>(a, s);
+        return go<float, ST_PLAIN, MODEL_IMPROVED, 2, 16, 16, 832, true>(a, s);
     case 3:
+        return go<float, ST_PLAIN, MODEL_IMPROVED, 2, 20, 20, 1024, true>(a, s);
+    case 4:
+        return go<float, ST_PLAIN, MODEL_IMPROVED, 1, 16, 16, 512, true>(a, s);
+    case 5:
         return go<float, ST_PLAIN, MODEL_IMPROVED, 2, 52, 20, 1024, true>(a, s);
     default:
         return go<float, ST_PLAIN, MODEL_IMPROVED, 1, 26, 26, 1024, true>(a, s);
@@ -384,11 +405,15 @@ hipError_t go_split(const lbac_ctx* h, StepArgs a, int bx) {
     return hipGetLastError();
 }
 
+template <int N>
+const Shape* all(const Shape (&t)[N], int& n) {
+    n = N;
+    return t;
+}
 const Shape* shapes_of(const lbac_ctx* h, int& n) {
-    if (h->closure) return n = 5, kCl;
-    if (h->storage != ST_PLAIN) return n = 1, kF16;
-    if (h->p.precision == LBAC_F64) return n = 6, kF64;
-    return n = 7, kF32;
+    if (h->closure) return all(kCl, n);
+    if (h->storage != ST_PLAIN) return all(kF16, n);
+    return h->p.precision == LBAC_F64 ? all(kF64, n) : all(kF32, n);
 }
 
 }  // namespace

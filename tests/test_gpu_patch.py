@@ -127,3 +127,15 @@ def test_two_pass_closure_equals_one_step(nx, ny, launch):
         out.append((a, s.phi()))
         s.close()
     assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
+
+
+# FP64 patches of 4x4, 8x8, 12x8, 13x13, 16x16 and 20x20, and the closure's
+# of 8x8, 14x14, 16x16, 20x20 and 26x26, off the patches' edges
+@pytest.mark.parametrize("precision,closure,nx,ny", [
+    ("f64", False, 61, 63), ("f64", False, 101, 99), ("f64", False, 145, 151), ("f64", False, 199, 209),
+    ("f64", False, 255, 253), ("f64", False, 301, 299), ("f32", True, 127, 121), ("f32", True, 201, 197),
+    ("f32", True, 255, 249), ("f32", True, 299, 301), ("f32", True, 601, 590)])
+def test_small_patches_equal_strips(precision, closure, nx, ny):
+    say("case: small patches", precision, closure, nx, ny)
+    a, b = sims(nx, ny, precision, closure=closure)
+    check(a, b, (3, 2, 1, 11))
