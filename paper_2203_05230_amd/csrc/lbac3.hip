@@ -140,9 +140,10 @@ __global__ __launch_bounds__(TX * TY) void step3_kernel(Args3 a) {
     // of which per plane: 200^3 in FP32, 128 x 8 tiles, 332 us, 313 like this.
     typedef const __attribute__((address_space(1))) char* Global;
     auto walk = [](const void* p) __attribute__((always_inline)) {
-        uint64_t v = (uint64_t)p;
-        asm volatile("" : "+s"(v));
-        return v;
+        uint32_t lo, hi;  // (opaque here, and uniform however the code is compiled)
+        asm volatile("" : "=s"(lo) : "0"(__builtin_amdgcn_readfirstlane((int)(uint64_t)p)));
+        asm volatile("" : "=s"(hi) : "0"(__builtin_amdgcn_readfirstlane((int)((uint64_t)p >> 32))));
+        return (uint64_t)hi << 32 | lo;
     };
     struct Col {
         uint32_t x[3], y[3];  // index c + 1
