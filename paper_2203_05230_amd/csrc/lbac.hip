@@ -574,8 +574,8 @@ int lbac_host::create(const lbac_params* p, const double* phi0, bool phi0_on_dev
         if ((h->pitch / unit) % 2 == 0) h->pitch += unit;
     }
     h->plane_stride = (int64_t)h->pitch * p->ny + kPlanePadBytes / h->elem_bytes;
-    h->bx = default_bx(p->nx);
-    h->strip_h = std::min(64, p->ny);
+    h->bx = h->unset_bx = default_bx(p->nx);
+    h->strip_h = h->unset_strip_h = std::min(64, p->ny);
     const size_t pop_bytes = (size_t)h->plane_stride * h->nplanes * h->elem_bytes;
     const size_t phis_bytes = ((size_t)h->pitch * p->ny + 64) * sizeof(float);
     for (int i = 0; i < 2; ++i) {
@@ -864,9 +864,9 @@ int lbac_get_launch(lbac_ctx* h, int32_t* variant, int32_t* bx, int32_t* strip_h
     if (!h) return LBAC_EINVAL;
     // a context whose shape nobody set reports the shape of creation, which
     // lbac_set_launch accepts
-    if (variant) *variant = h->shape_set ? h->variant : LBAC_KERNEL_BLOCK;
-    if (bx) *bx = h->shape_set ? h->bx : default_bx(h->p.nx);
-    if (strip_h) *strip_h = h->shape_set ? h->strip_h : std::min(64, h->p.ny);
+    if (variant) *variant = h->shape_set ? h->variant : h->unset_variant;
+    if (bx) *bx = h->shape_set ? h->bx : h->unset_bx;
+    if (strip_h) *strip_h = h->shape_set ? h->strip_h : h->unset_strip_h;
     return LBAC_OK;
 }
 
@@ -930,7 +930,10 @@ int lbac_autotune(lbac_ctx* h, int32_t steps, double* us_per_step) {
         }
         if (e != hipSuccess) break;
     }
-    // the launches a context makes whose shape nobody set (the patch kernels on small grids)
+    // The launches a context makes whose shape nobody set (the patch kernels on
+    // small grids).  Where they win, the context keeps making them, and
+    // lbac_get_launch gives the fastest of the shapes that can be set, for a
+    // caller that sets it on another context.
     bool set = true;
     if (e == hipSuccess) {
         h->shape_set = false;
@@ -947,6 +950,11 @@ int lbac_autotune(lbac_ctx* h, int32_t steps, double* us_per_step) {
     h->variant = best_v;
     h->bx = best_bx;
     h->strip_h = best_h;
+    if (!set) {
+        h->unset_variant = best_v;
+        h->unset_bx = best_bx;
+        h->unset_strip_h = best_h;
+    }
     drop_graphs(h);
     if (e != hipSuccess) {
         h->shape_set = keep_set;

@@ -57,6 +57,9 @@ struct lbac_ctx {
     int variant = LBAC_KERNEL_BLOCK;
     int bx = 256, strip_h = 64;
     bool shape_set = false;  // launch shape set by the caller or the autotuner (else plan_launch chooses per run)
+    // what lbac_get_launch gives while none is set: the shape at creation, or
+    // the fastest that can be set when lbac_autotune found the plan faster still
+    int unset_variant = LBAC_KERNEL_BLOCK, unset_bx = 256, unset_strip_h = 64;
     int graph_chunk = 0;
     hipGraphExec_t gexec[2] = {nullptr, nullptr};
     int gexec_chunk[2] = {0, 0};
