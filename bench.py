@@ -259,7 +259,7 @@ CLOSURE_LAUNCHES = ((224, 40, 4), (192, 40, 4), (160, 40, 4), (224, 80, 4), (224
 
 def closure_leg(lbac, torch, case, phi0, steps, theta=0.02, launch=None):
     """The step with the learned closure on the benchmark grid (BF16 MFMA
-    inference on interface-band nodes inside the multi-step kernel's steps),
+    inference on interface-band nodes in every step of the multi-step launches),
     with a seeded network; the cost depends on the band's size, not on the
     weights' values.  The launch shape is the fastest of a few multi-step
     shapes on 24 steps (or `launch`); also reported: the one-step path (step

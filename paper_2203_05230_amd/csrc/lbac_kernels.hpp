@@ -1265,7 +1265,7 @@ struct RowWalk {
 // 230, 51 and 30, 167 registers.)  8192^2 FP32 in 224 x 40 tiles: 355 -> 341
 // us per step, where a launch now moves the state at the rate of a plain copy;
 // 3000 x 1500: 37.5 -> 26.9; 1000 x 1400, two steps per launch on 160 x 8
-// tiles: 21.1 -> 16.1 (FP16 storage 21.4 -> 14.1).
+// tiles: 21.1 -> 15.9 (FP16 storage 21.4 -> 12.9).
 //
 // lds: TileSRows<S>::bytes(bx) bytes, bx >= w the widest tile of the launch.
 //
@@ -1295,7 +1295,7 @@ __device__ __forceinline__ void stepS_tile_lds(const StepArgs& a, int x0, int w,
     const StepSThread th = stepS_thread<ST>(x0, w, H);
     const int cxo = th.cxo;
     // Stage k forms phi/psi validly on the columns (and rows) up to
-    // RC (S - k) - 1 beyond the tile and updates up to RC (S - 1 - k) beyond
+    // 2 (S - k) - 1 beyond the tile and updates up to 2 (S - 1 - k) beyond
     // it.  Every thread runs every stage (branching on these ranges would only
     // hold per-lane masks, since every wavefront has lanes inside them):
     // outside them a thread forms values from rows or columns that are not
