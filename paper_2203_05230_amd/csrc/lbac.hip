@@ -405,7 +405,10 @@ Launch plan_launch(lbac_ctx* h, int64_t left) {
         const int S = launch_steps_of(h);
         return {false, {}, S > 1 && left >= S ? S : 1};
     }
-    const bool three = h->p.precision == LBAC_F32 && stepS_allowed(h) && left >= 3;
+    // (the closure at theta = 0: every node that is not clipped exactly is in
+    // the band, so the two-pass launches recompute the whole grid: 298 us per
+    // step at 2048^2, 162 with one-step launches)
+    const bool three = h->p.precision == LBAC_F32 && stepS_allowed(h) && left >= 3 && !(h->closure && h->cl_theta == 0.f);
     const float strips = default_strips(h, three, h->variant, h->bx, h->strip_h);
     // (the closure with the conventional model: one-step launches only)
     if (!h->closure || h->p.model == LBAC_MODEL_IMPROVED) {

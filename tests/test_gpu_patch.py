@@ -11,6 +11,12 @@ from paper_2203_05230_amd import closure as driver  # noqa: E402
 from paper_2203_05230_amd import lbac, workloads as W  # noqa: E402
 
 
+@pytest.fixture(autouse=True)
+def the_library(gpu_lib):
+    """Every test here needs the GPU and the built library (gpu_lib also opens
+    the device through torch first, which finds none once another HIP runtime has)."""
+
+
 def say(*a):
     print(*a, flush=True)
 
@@ -139,3 +145,14 @@ def test_small_patches_equal_strips(precision, closure, nx, ny):
     say("case: small patches", precision, closure, nx, ny)
     a, b = sims(nx, ny, precision, closure=closure)
     check(a, b, (3, 2, 1, 11))
+
+
+@pytest.mark.parametrize("nx,ny", [(120, 90), (1700, 1300)])
+def test_default_launches_with_the_closure_at_theta_zero(nx, ny):
+    """theta = 0 puts nearly every node in the band: patches on a small grid,
+    one-step launches on a large one."""
+    say("case: closure at theta 0", nx, ny)
+    a, b = sims(nx, ny, "f32")
+    for s in (a, b):
+        s.set_closure(driver.init_weights(5, out_scale=0.05), 0.0)
+    check(a, b, (4, 7))
