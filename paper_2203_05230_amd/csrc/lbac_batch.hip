@@ -173,15 +173,18 @@ std::vector<int> choose_strips(const std::vector<Geometry>& geo, int strip_h, co
     std::vector<int> uniform(count), best, nby(count);
     std::vector<double> passes(count), waves(count, 0.0);
     double longest = 0.0;
+    int top = 0;  // no strip is taller than the tallest instance
     for (int k = 0; k < count; ++k) {
+        top = std::max(top, geo[k].ny);
         uniform[k] = nearest_strips(geo[k].ny, strip_h);
         // (a one-step pass is about 0.6 of a full one)
         passes[k] = (double)(nsteps[k] / kBatchS) + 0.6 * (double)(nsteps[k] % kBatchS);
         longest = std::max(longest, passes[k]);
         for (const auto& t : column_tiles(geo[k].nx)) waves[k] += (t.second + 4 * kBatchS + 63) / 64;
     }
+    top = std::min(top, strip_h);
     double best_t = 0.0;
-    for (int h = kLow; h < strip_h + Q; h += Q) {
+    for (int h = kLow; h < top + Q; h += std::max(Q, h / 16 / Q * Q)) {
         const double limit = longest * (h + 14);
         double chain = 0.0, work = 0.0, slots = 0.0;
         for (int k = 0; k < count; ++k) {

@@ -270,7 +270,7 @@ def test_batch_stall_times_out_and_reports(gpu_lib):
 
 
 @pytest.mark.parametrize("precision", ["f32", "f32_f16store"])
-@pytest.mark.parametrize("strip_h", [8, 20, 96])
+@pytest.mark.parametrize("strip_h", [8, 20, 96, 2**31 - 1])
 def test_batch_strips_follow_the_run(gpu_lib, precision, strip_h):
     """Strips are cut finer for the instances with the most passes, so their
     heights differ between instances and change between runs (a long run of
