@@ -299,9 +299,14 @@ constexpr Shape kF64[] = {{3, 4, 4, 5.9f, 1.65f},   {3, 8, 8, 7.f, 3.1f},     {4
                           {3, 13, 13, 9.3f, 5.f},   {3, 16, 16, 10.5f, 7.5f}, {2, 16, 16, 7.5f, 4.2f},
                           {3, 20, 20, 11.1f, 9.1f}, {2, 24, 24, 9.9f, 8.3f},  {3, 52, 20, 19.f, 20.f},
                           {1, 28, 28, 6.6f, 6.f}};
-// 16-bit storage: one step, since a launch rounds once (5.2, 7.1, 11.3 and
-// 16.0 us at 256^2, 512^2, 768^2 and 1024^2; strips 7.9, 9.6, 13.9 and 16.9).
-constexpr Shape kF16[] = {{1, 28, 28, 5.2f, 2.1f}};
+// 16-bit storage: one step, since a launch rounds once (us per step, and
+// the best strips: 3.3 and 4.0 at 64^2, 3.8 and 4.4 at 200^2, 6.2 and 6.7 at
+// 512^2, 12.6 and 14.8 at 1024^2, 22 and 26 at 1536^2, 36 and 39 at 2048^2; only
+// 28 x 28 before, 4.3, 4.6, 7.0, 16.2, 28.5 and 49.  Where the state no longer
+// stays in the last-level cache the strips win: 105 and 103 at 3000^2, 176 and
+// 151 at 4096^2).
+constexpr Shape kF16[] = {{1, 12, 12, 3.3f, 0.48f}, {1, 28, 12, 3.6f, 0.9f}, {1, 60, 28, 5.7f, 3.2f}};
+
 // FP32 with the closure, a disk's edge in the field (5.2, 6.6, 7.3 and 12.8 us
 // per step at 128^2, 200^2, 256^2 and 512^2; with four steps of 8 x 8, three of
 // 14 x 14 and two of 20 x 20 before, 5.7, 7.9, 8.1 and 14.3; the two-pass
@@ -362,6 +367,18 @@ hipError_t go_f64(int shape, const StepArgs& a, hipStream_t s) {
         return go<double, ST_PLAIN, MODEL, 3, 52, 20, 1024>(a, s);
     default:
         return go<double, ST_PLAIN, MODEL, 1, 28, 28, 1024>(a, s);
+    }
+}
+
+template <int ST, int MODEL>
+hipError_t go_f16(int shape, const StepArgs& a, hipStream_t s) {
+    switch (shape) {
+    case 0:
+        return go<float, ST, MODEL, 1, 12, 12, 256>(a, s);
+    case 1:
+        return go<float, ST, MODEL, 1, 28, 12, 512>(a, s);
+    default:
+        return go<float, ST, MODEL, 1, 60, 28, 1024>(a, s);
     }
 }
 
@@ -443,11 +460,11 @@ hipError_t lbac_host::launch_patch(const lbac_ctx* h, int src, int32_t k, const 
     case LBAC_F32:
         return conv ? go_f32<MODEL_CONVENTIONAL>(p.shape, a, h->stream) : go_f32<MODEL_IMPROVED>(p.shape, a, h->stream);
     case LBAC_F32_F16STORE:
-        return conv ? go<float, ST_F16, MODEL_CONVENTIONAL, 1, 28, 28, 1024>(a, h->stream)
-                    : go<float, ST_F16, MODEL_IMPROVED, 1, 28, 28, 1024>(a, h->stream);
+        return conv ? go_f16<ST_F16, MODEL_CONVENTIONAL>(p.shape, a, h->stream)
+                    : go_f16<ST_F16, MODEL_IMPROVED>(p.shape, a, h->stream);
     default:
-        return conv ? go<float, ST_BF16, MODEL_CONVENTIONAL, 1, 28, 28, 1024>(a, h->stream)
-                    : go<float, ST_BF16, MODEL_IMPROVED, 1, 28, 28, 1024>(a, h->stream);
+        return conv ? go_f16<ST_BF16, MODEL_CONVENTIONAL>(p.shape, a, h->stream)
+                    : go_f16<ST_BF16, MODEL_IMPROVED>(p.shape, a, h->stream);
     }
 }
 
