@@ -274,31 +274,34 @@ using namespace lbac;
 // A shape: S steps of patches of pw x ph nodes.  first, more: microseconds of
 // a launch of at most 256 patches (one per CU) and of every further 256,
 // fitted to launches back to back on an MI355X.  They rank the shapes against
-// each other and against the strip kernels.
+// each other and against the strip kernels.  conv: the same relative to the
+// other shapes with the conventional model, whose step without logarithms
+// leaves less to gain from fewer shared nodes.
 struct Shape {
     int S, pw, ph;
-    float first, more;
+    float first, more, conv = 1.f;
 };
 
 // FP32: measured at 64^2 to 4096^2 (for example 1.24 us per step with six
 // steps of 8 x 8 at 64^2, 1.62 with four of 16 x 16 at 256^2, 2.93 with four
-// of 32 x 16 at 512^2, 8.9 with three of 52 x 20 at 1024^2; the best of the
-// strip shapes take 6.9, 7.4, 8.1 and 12.6 us there).
+// of 32 x 16 at 512^2, 2.4, 5.4 and 8.9 with four of 48 x 16 at 400^2, 768^2 and
+// 1024^2; the best of the strip shapes take 6.9, 7.4, 8.1 and, at 1024^2, 12.6).
 constexpr Shape kF32[] = {{6, 8, 8, 7.5f, 3.7f},   {4, 16, 16, 6.4f, 2.8f}, {6, 24, 24, 14.3f, 11.4f},
                           {4, 32, 16, 7.8f, 4.1f}, {3, 52, 20, 8.3f, 5.2f}, {2, 24, 24, 5.4f, 2.2f},
-                          {1, 28, 28, 5.0f, 2.1f}};
+                          {4, 48, 16, 9.8f, 5.3f}, {1, 28, 28, 5.0f, 2.1f}};
 // FP64 is bound by its instructions where a SIMD has more than a wavefront or
 // two, so small patches and just enough threads for the grown patch pay
 // (us per step: 1.97 with three steps of 4 x 4 at 64^2, 2.37 with three of 8 x
 // 8 at 100^2, 2.83 with four of 12 x 8 at 150^2, 3.14 with three of 13 x 13
-// at 200^2, 7.3 with two of 16 x 16 at 400^2, 31 and 436 with three of 52 x 20
-// at 1024^2 and 4096^2; with only four steps of 8 x 8 or 16 x 16 before, 2.41,
+// at 200^2, 6.2, 8.8 and 25 with two of 24 x 16, one node per thread of twelve
+// wavefronts, at 400^2, 512^2 and 1024^2, where three of 52 x 20 and two of 24 x
+// 24 had taken 6.9, 9.6 and 31; with only four steps of 8 x 8 or 16 x 16 before, 2.41,
 // 2.55, 3.37, 3.50 and 9.0; the best one-step strips 7.2 at 64^2, 9.8 at
 // 200^2, 37 and 522).
 constexpr Shape kF64[] = {{3, 4, 4, 5.9f, 1.65f},   {3, 8, 8, 7.f, 3.1f},     {4, 12, 8, 11.f, 5.7f},
                           {3, 13, 13, 9.3f, 5.f},   {3, 16, 16, 10.5f, 7.5f}, {2, 16, 16, 7.5f, 4.2f},
-                          {3, 20, 20, 11.1f, 9.1f}, {2, 24, 24, 9.9f, 8.3f},  {3, 52, 20, 19.f, 20.f},
-                          {1, 28, 28, 6.6f, 6.f}};
+                          {3, 20, 20, 11.1f, 9.1f}, {2, 24, 24, 9.9f, 8.3f},  {3, 52, 20, 19.7f, 20.f},
+                          {2, 24, 16, 8.4f, 4.5f, 1.25f}, {1, 28, 28, 6.6f, 6.f}};
 // 16-bit storage: one step, since a launch rounds once (us per step, and
 // the best strips: 3.3 and 4.0 at 64^2, 3.8 and 4.4 at 200^2, 6.2 and 6.7 at
 // 512^2, 12.6 and 14.8 at 1024^2, 22 and 26 at 1536^2, 36 and 39 at 2048^2; only
@@ -339,6 +342,8 @@ hipError_t go_f32(int shape, const StepArgs& a, hipStream_t s) {
         return go<float, ST_PLAIN, MODEL, 3, 52, 20, 1024>(a, s);
     case 5:
         return go<float, ST_PLAIN, MODEL, 2, 24, 24, 1024>(a, s);
+    case 6:
+        return go<float, ST_PLAIN, MODEL, 4, 48, 16, 1024>(a, s);
     default:
         return go<float, ST_PLAIN, MODEL, 1, 28, 28, 1024>(a, s);
     }
@@ -365,6 +370,8 @@ hipError_t go_f64(int shape, const StepArgs& a, hipStream_t s) {
         return go<double, ST_PLAIN, MODEL, 2, 24, 24, 1024>(a, s);
     case 8:
         return go<double, ST_PLAIN, MODEL, 3, 52, 20, 1024>(a, s);
+    case 9:
+        return go<double, ST_PLAIN, MODEL, 2, 24, 16, 768>(a, s);
     default:
         return go<double, ST_PLAIN, MODEL, 1, 28, 28, 1024>(a, s);
     }
@@ -441,10 +448,12 @@ lbac_host::PatchPlan lbac_host::plan_patch(const lbac_ctx* h, int64_t left) {
     const Shape* t = shapes_of(h, n);
     // the state read and written once per launch at 4 TB/s bounds short launches on large grids
     const float mem = 2.5e-7f * (float)((int64_t)h->p.nx * h->p.ny) * 2.f * state_bytes(h);
+    const bool conv = h->p.model == LBAC_MODEL_CONVENTIONAL;
     for (int i = 0; i < n; ++i) {
         if (t[i].S > left) continue;
         const int64_t tiles = (int64_t)((h->p.nx + t[i].pw - 1) / t[i].pw) * ((h->p.ny + t[i].ph - 1) / t[i].ph);
-        const float us = std::max(mem, t[i].first + (float)((tiles + 255) / 256 - 1) * t[i].more) / (float)t[i].S;
+        const float cost = t[i].first + (float)((tiles + 255) / 256 - 1) * t[i].more;
+        const float us = std::max(mem, conv ? cost * t[i].conv : cost) / (float)t[i].S;
         if (best.shape < 0 || us < best.us) best = {i, t[i].S, us};
     }
     return best;

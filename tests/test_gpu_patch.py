@@ -156,3 +156,12 @@ def test_default_launches_with_the_closure_at_theta_zero(nx, ny):
     for s in (a, b):
         s.set_closure(driver.init_weights(5, out_scale=0.05), 0.0)
     check(a, b, (4, 7))
+
+
+@pytest.mark.parametrize("precision,model", [("f32", "improved"), ("f64", "improved"), ("f64", "conventional")])
+@pytest.mark.parametrize("nx,ny", [(399, 401), (770, 765), (1000, 1021)])
+def test_middle_patches_equal_strips(nx, ny, precision, model):
+    """FP32 patches of 48 x 16 and FP64 ones of 24 x 16, off their edges."""
+    say("case: middle patches", precision, model, nx, ny)
+    a, b = sims(nx, ny, precision, model=model)
+    check(a, b, (4, 1, 6))
