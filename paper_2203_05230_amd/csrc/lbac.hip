@@ -350,6 +350,32 @@ struct Launch {
     int S;
 };
 
+// What a row of a one-step strip costs: a strip takes its rows and the
+// pipeline's four, each alone + busy k microseconds with k tiles on a CU, of
+// which `resident` run at once; never less than the state read and written
+// once at 4.75 TB/s.  The 256-column FP64 tile (five wavefronts, bound by their
+// instructions) takes as long again for every further tile, so that a height
+// whose tiles divide evenly among the 256 CUs is worth more than many tiles;
+// FP32 tiles wait for loads and share a CU better.  Fitted to heights of 4 to
+// 64 on seventeen grids from 4096 x 64 to 8192 x 4096 and 16 x 65536; the
+// choice is within 15% of the best of them (9% but for one), and no slower
+// than strips of 64.  us per step, strips of 64, of about 1024 tiles whatever
+// the type (the earlier rule) and these: FP64 65536 x 16 43, 63 and 43 (16 rows),
+// 2048^2 140, 159 and 140 (64), 3000 x 2000 273, 261 and 208 (48); FP32 3000 x
+// 2000 104, 108 and 96 (48); FP16 storage 3000^2 115, 112 and 92 (48).
+struct RowCost {
+    float alone, busy;
+    int resident;
+};
+RowCost one_step_row(const lbac_ctx* h, int bx) {
+    const int w = bx == 256 ? 0 : (bx == 128 ? 1 : 2);
+    constexpr RowCost f32[] = {{0.58f, 0.39f, 5}, {0.70f, 0.17f, 10}, {0.74f, 0.09f, 16}};
+    constexpr RowCost f64[] = {{0.f, 1.92f, 2}, {0.84f, 0.57f, 5}, {1.03f, 0.26f, 9}};
+    constexpr RowCost f64_conv[] = {{0.f, 1.46f, 2}, {0.65f, 0.46f, 5}, {0.78f, 0.20f, 9}};
+    if (h->p.precision != LBAC_F64) return f32[w];
+    return h->p.model == LBAC_MODEL_CONVENTIONAL ? f64_conv[w] : f64[w];
+}
+
 // The default shape of the strip kernels, for grids the patch kernels leave to
 // them, and an estimate of its time per step in microseconds (as PatchPlan's).
 //
@@ -362,11 +388,7 @@ struct Launch {
 // at 2048^2 (42; 30 rows 27.2, 48 27.3), 37.8 at 3001 x 2210 (42), 93.5 at
 // 4096^2 and 341 at 8192^2 (42); the best of 72 shapes 16.5, 25.4, 36.6, 91.4.
 //
-// One step: strips of such a height that about 1024 tiles, four per CU, share
-// the device: 256-column tiles at 16-bit storage ran at 17.9, 27.0, 38.6, 74
-// and 155 us per step at 1024^2, 1536^2, 2048^2, 3001 x 2210 and 4096^2
-// (strips of 4, 12, 16, 24, 64), the best of 54 shapes to 2%, against 60 us
-// and more below 2048^2 at strips of 64.
+// One step: the height of the least estimate by RowCost.
 float default_strips(const lbac_ctx* h, bool three, int& variant, int& bx, int& strip_h) {
     const int nx = h->p.nx, ny = h->p.ny;
     const float mnodes = 1e-6f * (float)((int64_t)nx * ny);
@@ -391,9 +413,19 @@ float default_strips(const lbac_ctx* h, bool three, int& variant, int& bx, int& 
     variant = LBAC_KERNEL_BLOCK;
     bx = default_bx(nx);
     const int64_t nbx = (nx + bx - 1) / bx;
-    strip_h = (int)std::min<int64_t>(ny, std::max<int64_t>(4, std::min<int64_t>(64, nbx * ny / 1024)));
-    // the state read and written at 4.6 TB/s; the closure's passes about half as much again
-    return (h->closure ? 30.f : 8.f) + (h->closure ? 1.5f : 1.f) * mnodes * 2.f * state_bytes(h) / 4.6f;
+    const RowCost rc = one_step_row(h, bx);
+    const float mem = mnodes * 2.f * state_bytes(h) / 4.75f;
+    float best = 1e30f;
+    for (int sh : {64, 48, 32, 24, 16, 12, 8, 6, 4}) {
+        const int64_t k = (nbx * ((ny + sh - 1) / sh) + 255) / 256;
+        const float row = rc.alone * (float)((k + rc.resident - 1) / rc.resident) + rc.busy * (float)k;
+        const float us = std::max(row * (float)(std::min(sh, ny) + 4), mem) + 3.f;
+        if (us < best) {
+            best = us;
+            strip_h = std::min(sh, ny);
+        }
+    }
+    return h->closure ? best + 17.f + 9.f * std::sqrt(mnodes) : best;
 }
 
 // The next launch of a run with `left` steps to go: the shape that was set,

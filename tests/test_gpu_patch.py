@@ -165,3 +165,14 @@ def test_middle_patches_equal_strips(nx, ny, precision, model):
     say("case: middle patches", precision, model, nx, ny)
     a, b = sims(nx, ny, precision, model=model)
     check(a, b, (4, 1, 6))
+
+
+@pytest.mark.parametrize("model", ["improved", "conventional"])
+def test_fp64_default_launches_on_large_grids(model):
+    """Single steps take strips of a height chosen by the grid, longer runs
+    patches, beyond 2048 nodes a side and off the tiles' and patches' edges;
+    on a wide, low grid the strips are as high as the grid."""
+    for nx, ny, steps in ((2050, 2049, (1, 2, 3, 5)), (16500, 17, (1, 1, 4))):
+        say("case: FP64 default launches", model, nx, ny)
+        a, b = sims(nx, ny, "f64", model=model)
+        check(a, b, steps)
