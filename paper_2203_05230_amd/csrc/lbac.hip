@@ -51,6 +51,12 @@ void drop_graphs(lbac_ctx* h) {
     }
 }
 
+// What the closure changes: the launches of a context whose shape nobody set.
+void drop_plans(lbac_ctx* h) {
+    for (Launch& l : h->plans) l.S = 0;
+    drop_graphs(h);
+}
+
 void release(lbac_ctx* h) {
     if (h->stream) (void)hipStreamSynchronize(h->stream);
     drop_graphs(h);
@@ -343,13 +349,6 @@ hipError_t launch_stepS(const lbac_ctx* h, int src, int32_t k, int S) {
     }
 }
 
-// One launch of a run: the patch kernels, an S-step launch or a one-step launch.
-struct Launch {
-    bool patch;
-    PatchPlan p;
-    int S;
-};
-
 // What a row of a one-step strip costs: a strip takes its rows and the
 // pipeline's four, each alone + busy k microseconds with k tiles on a CU, of
 // which `resident` run at once; never less than the state read and written
@@ -430,24 +429,38 @@ float default_strips(const lbac_ctx* h, bool three, int& variant, int& bx, int& 
 
 // The next launch of a run with `left` steps to go: the shape that was set,
 // or, where nobody set one, the faster of the patch kernels and the strip
-// kernels.  Results do not depend on the choice (16-bit storage takes one
+// kernels (made once per context: the estimates take as long as a launch's own
+// host work).  Results do not depend on the choice (16-bit storage takes one
 // step per launch here, as its rounding depends on the steps of a launch).
 Launch plan_launch(lbac_ctx* h, int64_t left) {
     if (h->shape_set) {
         const int S = launch_steps_of(h);
-        return {false, {}, S > 1 && left >= S ? S : 1};
+        return {false, {}, S > 1 && left >= S ? S : 1, h->variant, h->bx, h->strip_h};
     }
-    // (the closure at theta = 0: every node that is not clipped exactly is in
-    // the band, so the two-pass launches recompute the whole grid: 298 us per
-    // step at 2048^2, 162 with one-step launches)
-    const bool three = h->p.precision == LBAC_F32 && stepS_allowed(h) && left >= 3 && !(h->closure && h->cl_theta == 0.f);
-    const float strips = default_strips(h, three, h->variant, h->bx, h->strip_h);
-    // (the closure with the conventional model: one-step launches only)
-    if (!h->closure || h->p.model == LBAC_MODEL_IMPROVED) {
-        const PatchPlan p = plan_patch(h, left);
-        if (p.shape >= 0 && p.us < strips) return {true, p, p.S};
+    Launch& l = h->plans[std::min<int64_t>(left, kPlanSteps)];
+    if (l.S == 0) {
+        // (the closure at theta = 0: every node that is not clipped exactly is in
+        // the band, so the two-pass launches recompute the whole grid: 298 us per
+        // step at 2048^2, 162 with one-step launches)
+        const bool three =
+            h->p.precision == LBAC_F32 && stepS_allowed(h) && left >= 3 && !(h->closure && h->cl_theta == 0.f);
+        l.patch = false;
+        l.S = three ? 3 : 1;
+        const float strips = default_strips(h, three, l.variant, l.bx, l.strip_h);
+        // (the closure with the conventional model: one-step launches only)
+        if (!h->closure || h->p.model == LBAC_MODEL_IMPROVED) {
+            const PatchPlan p = plan_patch(h, left);
+            if (p.shape >= 0 && p.us < strips) {
+                l.patch = true;
+                l.p = p;
+                l.S = p.S;
+            }
+        }
     }
-    return {false, {}, three ? 3 : 1};
+    h->variant = l.variant;
+    h->bx = l.bx;
+    h->strip_h = l.strip_h;
+    return l;
 }
 
 hipError_t do_launch(const lbac_ctx* h, const Launch& l, int src, int32_t k) {
@@ -1015,7 +1028,7 @@ int lbac_set_closure(lbac_ctx* h, const float* params, float theta) {
     DeviceGuard g(h->device);
     if (!params) {
         h->closure = false;
-        drop_graphs(h);
+        drop_plans(h);
         return LBAC_OK;
     }
     if (h->p.precision != LBAC_F32) return fail(h, LBAC_EINVAL, "the learned closure runs with LBAC_F32 only");
@@ -1044,7 +1057,7 @@ int lbac_set_closure(lbac_ctx* h, const float* params, float theta) {
     HIPCHK(h, hipStreamSynchronize(h->stream));
     h->closure = true;
     h->cl_theta = theta;
-    drop_graphs(h);
+    drop_plans(h);
     return LBAC_OK;
 }
 

@@ -28,6 +28,22 @@ struct DeviceGuard {
     }
 };
 
+// A launch of the patch kernels: which shape, its steps, and the time per
+// step that ranks it (microseconds); shape < 0: none.
+struct PatchPlan {
+    int shape, S;
+    float us;
+};
+// One launch of a run whose shape nobody set: a patch kernel, or S steps of
+// the strip kernels in the given shape.
+struct Launch {
+    bool patch;
+    PatchPlan p;
+    int S = 0;
+    int variant, bx, strip_h;  // strips
+};
+constexpr int kPlanSteps = 6;  // steps of the longest launch
+
 }  // namespace lbac_host
 
 struct lbac_ctx {
@@ -60,6 +76,7 @@ struct lbac_ctx {
     // what lbac_get_launch gives while none is set: the shape at creation, or
     // the fastest that can be set when lbac_autotune found the plan faster still
     int unset_variant = LBAC_KERNEL_BLOCK, unset_bx = 256, unset_strip_h = 64;
+    lbac_host::Launch plans[lbac_host::kPlanSteps + 1];  // with i steps to go, or more than kPlanSteps; S = 0: not made yet
     int graph_chunk = 0;
     hipGraphExec_t gexec[2] = {nullptr, nullptr};
     int gexec_chunk[2] = {0, 0};
@@ -87,12 +104,6 @@ void* dev_alloc(lbac_ctx* h, size_t bytes);
 void dev_free(lbac_ctx* h, void* ptr);
 lbac::StepArgs make_args(const lbac_ctx* h, int src, int32_t k);
 
-// A launch of the patch kernels: which shape, its steps, and the time per
-// step that ranks it (microseconds); shape < 0: none.
-struct PatchPlan {
-    int shape, S;
-    float us;
-};
 float state_bytes(const lbac_ctx* h);  // stored bytes per node
 PatchPlan plan_patch(const lbac_ctx* h, int64_t left);  // the best shape of at most `left` steps
 hipError_t launch_patch(const lbac_ctx* h, int src, int32_t k, const PatchPlan& p);

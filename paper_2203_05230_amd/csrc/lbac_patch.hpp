@@ -446,14 +446,20 @@ lbac_host::PatchPlan lbac_host::plan_patch(const lbac_ctx* h, int64_t left) {
     PatchPlan best{-1, 0, 0.f};
     int n = 0;
     const Shape* t = shapes_of(h, n);
-    // the state read and written once per launch at 4 TB/s bounds short launches on large grids
-    const float mem = 2.5e-7f * (float)((int64_t)h->p.nx * h->p.ny) * 2.f * state_bytes(h);
+    // the state read and written once per launch bounds short launches on large
+    // grids: 4 TB/s from HBM, about 6 where both buffers stay in the last-level
+    // cache (FP64, one step at 1024^2: 151 MB in 25 us)
+    const float moved = 1e-6f * (float)((int64_t)h->p.nx * h->p.ny) * 2.f * state_bytes(h);  // MB
+    const float mem = moved / (moved < 256.f ? 6.f : 4.f);
     const bool conv = h->p.model == LBAC_MODEL_CONVENTIONAL;
+    // FP64 without the logarithms: 9.9, 17.2 and 25 us for one step of 28 x 28 at 600^2, 768^2 and 1024^2, where the
+    // table gives 12.6, 24.6 and 36.6; the strips, whose costs are the model's own, take 21, 27 and 33
+    const float conv_all = h->p.precision == LBAC_F64 ? 0.7f : 1.f;
     for (int i = 0; i < n; ++i) {
         if (t[i].S > left) continue;
         const int64_t tiles = (int64_t)((h->p.nx + t[i].pw - 1) / t[i].pw) * ((h->p.ny + t[i].ph - 1) / t[i].ph);
         const float cost = t[i].first + (float)((tiles + 255) / 256 - 1) * t[i].more;
-        const float us = std::max(mem, conv ? cost * t[i].conv : cost) / (float)t[i].S;
+        const float us = std::max(mem, conv ? cost * t[i].conv * conv_all : cost) / (float)t[i].S;
         if (best.shape < 0 || us < best.us) best = {i, t[i].S, us};
     }
     return best;
