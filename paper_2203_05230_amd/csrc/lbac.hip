@@ -57,6 +57,20 @@ void drop_plans(lbac_ctx* h) {
     drop_graphs(h);
 }
 
+// The closure's buffers: all of them, or (after this) none.
+void free_closure(lbac_ctx* h) {
+    for (void* p : {(void*)h->cl_param, (void*)h->cl_w, (void*)h->cl_b, (void*)h->cl_mask, (void*)h->cl_list,
+                    (void*)h->cl_count, (void*)h->cl_flags})
+        dev_free(h, p);
+    h->cl_param = nullptr;
+    h->cl_w = nullptr;
+    h->cl_b = nullptr;
+    h->cl_mask = nullptr;
+    h->cl_list = nullptr;
+    h->cl_count = nullptr;
+    h->cl_flags = nullptr;
+}
+
 void release(lbac_ctx* h) {
     if (h->stream) (void)hipStreamSynchronize(h->stream);
     drop_graphs(h);
@@ -71,13 +85,7 @@ void release(lbac_ctx* h) {
     dev_free(h, h->rows);
     dev_free(h, h->red5);
     dev_free(h, h->dtmp);
-    dev_free(h, h->cl_param);
-    dev_free(h, h->cl_w);
-    dev_free(h, h->cl_b);
-    dev_free(h, h->cl_mask);
-    dev_free(h, h->cl_list);
-    dev_free(h, h->cl_count);
-    dev_free(h, h->cl_flags);
+    free_closure(h);
     if (h->host5) (void)hipHostFree(h->host5);
     if (h->own_stream && h->stream) (void)hipStreamDestroy(h->stream);
 }
@@ -1046,9 +1054,13 @@ int lbac_set_closure(lbac_ctx* h, const float* params, float theta) {
         h->cl_count = (uint32_t*)dev_alloc(h, 256);
         const size_t marks = (mark_count(h->p.nx, h->p.ny) + 7) / 8 * 8;
         h->cl_flags = (uint8_t*)dev_alloc(h, marks);
-        if (!h->cl_param || !h->cl_w || !h->cl_b || !h->cl_mask || !h->cl_list || !h->cl_count || !h->cl_flags)
+        if (!h->cl_param || !h->cl_w || !h->cl_b || !h->cl_mask || !h->cl_list || !h->cl_count || !h->cl_flags) {
+            free_closure(h);  // a later call starts over, rather than run without the missing ones
             return fail(h, LBAC_ENOMEM, "closure buffers");
-        HIPCHK(h, hipMemsetAsync(h->cl_flags, 0, marks, h->stream));
+        }
+        const hipError_t e = hipMemsetAsync(h->cl_flags, 0, marks, h->stream);
+        if (e != hipSuccess) free_closure(h);
+        HIPCHK(h, e);
     }
     HIPCHK(h, hipMemcpyAsync(h->cl_param, params, sizeof(float) * LBAC_MLP_NPARAM, hipMemcpyHostToDevice, h->stream));
     hipLaunchKernelGGL(closure_pack_kernel, dim3((64 * 64 + 255) / 256), dim3(256), 0, h->stream, h->cl_param, h->cl_w,

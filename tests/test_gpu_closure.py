@@ -284,3 +284,40 @@ def test_extraction_tiles_rows_and_chunks(gpu_lib, nxf, nyf, r):
         assert np.max(np.abs(first[1][w] - Yr[w])) <= 1e-6 * max(1.0, np.max(np.abs(Yr)))
         assert np.all(Xg[base:cap].reshape(-1, m, 25)[~w] == -7.0) and np.all(Yg[base:cap].reshape(-1, m, 2)[~w] == -7.0)
         assert np.all(Xg[:base] == -7.0) and np.all(Xg[cap:] == -7.0)
+
+
+def test_a_closure_without_memory_can_be_set_again(gpu_lib, monkeypatch):
+    """An allocation that fails leaves no closure half made: the next call
+    allocates again (and fails while there is none), and with memory the run
+    is that of a context that never failed."""
+    class Scarce(gpu_lib.TorchAllocator):
+        left = None  # allocations that still succeed
+
+        def _do_alloc(self, nbytes, user):
+            if self.left is not None:
+                if self.left == 0:
+                    return None
+                self.left -= 1
+            return super()._do_alloc(nbytes, user)
+
+    monkeypatch.setattr(gpu_lib, "TorchAllocator", Scarce)
+    case = {**W.single_vortex_case(96, eps=1.0, U=0.04, period_T=200.0), "precision": "f32"}
+    phi0, w = W.circle(96, 1.0), closure_params(3, 0.05)
+    a = gpu_lib.Simulation(case, phi0, torch_alloc=True)
+    alloc = a._keep[0]
+    for k in range(7):  # the closure's seven buffers
+        for _ in range(2):
+            say("case: closure, allocation", k, "fails")
+            alloc.left = k
+            with pytest.raises(gpu_lib.LbacError) as e:
+                a.set_closure(w, 0.02)
+            assert e.value.code == gpu_lib.LBAC_ENOMEM
+    alloc.left = None
+    a.set_closure(w, 0.02)
+    b = gpu_lib.Simulation(case, phi0)
+    b.set_closure(w, 0.02)
+    for s in (a, b):
+        s.step(31)
+    assert np.array_equal(a.phi(), b.phi())
+    a.close()
+    b.close()
