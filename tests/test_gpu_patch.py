@@ -176,3 +176,19 @@ def test_fp64_default_launches_on_large_grids(model):
         say("case: FP64 default launches", model, nx, ny)
         a, b = sims(nx, ny, "f64", model=model)
         check(a, b, steps)
+
+
+@pytest.mark.parametrize("theta", [5e-8, 1e-9, 1e-4])
+@pytest.mark.parametrize("launch", [None, (224, 40, 4), (96, 8, 3)])
+def test_two_pass_closure_at_small_theta(theta, launch):
+    """The band test of the marking strips at thetas near the rounding of phi:
+    a disk whose tails pass through them, on a grid that takes two-pass
+    launches by default."""
+    say("case: two-pass closure, theta", theta, launch)
+    a, b = sims(1501, 1203, "f32")
+    for s in (a, b):
+        s.set_closure(driver.init_weights(5, out_scale=0.05), theta)
+    if launch:
+        a.set_launch(*launch)
+    assert a.steps_per_launch() == (3 if launch is None else launch[2] - 1)
+    check(a, b, (3, 7))
