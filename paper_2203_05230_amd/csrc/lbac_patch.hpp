@@ -449,8 +449,15 @@ lbac_host::PatchPlan lbac_host::plan_patch(const lbac_ctx* h, int64_t left) {
     // the state read and written once per launch bounds short launches on large
     // grids: 4 TB/s from HBM, about 6 where both buffers stay in the last-level
     // cache (FP64, one step at 1024^2: 151 MB in 25 us)
-    const float moved = 1e-6f * (float)((int64_t)h->p.nx * h->p.ny) * 2.f * state_bytes(h);  // MB
-    const float mem = moved / (moved < 256.f ? 6.f : 4.f);
+    const float state = 1e-6f * (float)((int64_t)h->p.nx * h->p.ny) * state_bytes(h);  // MB
+    // The closure's patches share three nodes a step on each side, so they read
+    // more than the state once it no longer stays in the cache (4096^2, one step
+    // of 26 x 26: 382 us).  And they wait for the network where the band is
+    // wide: its width goes with log(1 / theta), and from theta = 0.02 to 1e-4 two
+    // steps of 52 x 20 take 285 -> 520 us per step at 4096^2, 81 -> 189 at 2048^2,
+    // one of 26 x 26 382 -> 501 and 100 -> 160, the one-step strips 293 -> 297
+    // and 105 -> 107.
+    const float tail = h->closure ? std::max(1.f, -0.256f * std::log(h->cl_theta + 1e-10f)) : 1.f;
     const bool conv = h->p.model == LBAC_MODEL_CONVENTIONAL;
     // FP64 without the logarithms: 9.9, 17.2 and 25 us for one step of 28 x 28 at 600^2, 768^2 and 1024^2, where the
     // table gives 12.6, 24.6 and 36.6; the strips, whose costs are the model's own, take 21, 27 and 33
@@ -458,8 +465,12 @@ lbac_host::PatchPlan lbac_host::plan_patch(const lbac_ctx* h, int64_t left) {
     for (int i = 0; i < n; ++i) {
         if (t[i].S > left) continue;
         const int64_t tiles = (int64_t)((h->p.nx + t[i].pw - 1) / t[i].pw) * ((h->p.ny + t[i].ph - 1) / t[i].ph);
-        const float cost = t[i].first + (float)((tiles + 255) / 256 - 1) * t[i].more;
-        const float us = std::max(mem, conv ? cost * t[i].conv * conv_all : cost) / (float)t[i].S;
+        float cost = t[i].first + (float)((tiles + 255) / 256 - 1) * t[i].more;
+        if (h->closure) cost *= t[i].S == 1 ? std::min(0.6f + 0.4f * tail, 1.35f) : std::min(tail, 2.2f);
+        if (conv) cost *= t[i].conv * conv_all;
+        const int halo = h->closure ? 6 * t[i].S : 0;
+        const float moved = state * (1.f + (float)((t[i].pw + halo) * (t[i].ph + halo)) / (float)(t[i].pw * t[i].ph));
+        const float us = std::max(cost, moved / (2.f * state < 256.f ? 6.f : 4.f)) / (float)t[i].S;
         if (best.shape < 0 || us < best.us) best = {i, t[i].S, us};
     }
     return best;
