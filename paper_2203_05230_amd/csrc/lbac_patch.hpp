@@ -452,8 +452,8 @@ lbac_host::PatchPlan lbac_host::plan_patch(const lbac_ctx* h, int64_t left) {
     const float state = 1e-6f * (float)((int64_t)h->p.nx * h->p.ny) * state_bytes(h);  // MB
     // The closure's patches share three nodes a step on each side, so they read
     // more than the state once it no longer stays in the cache (4096^2, one step
-    // of 26 x 26: 382 us).  And they wait for the network where the band is
-    // wide: its width goes with log(1 / theta), and from theta = 0.02 to 1e-4 two
+    // of 26 x 26: 382 us).  And where there are several to a CU they wait for the
+    // network of the last ones, the longer the wider the band is: its width goes with log(1 / theta), and from theta = 0.02 to 1e-4 two
     // steps of 52 x 20 take 285 -> 520 us per step at 4096^2, 81 -> 189 at 2048^2,
     // one of 26 x 26 382 -> 501 and 100 -> 160, the one-step strips 293 -> 297
     // and 105 -> 107.
@@ -465,8 +465,8 @@ lbac_host::PatchPlan lbac_host::plan_patch(const lbac_ctx* h, int64_t left) {
     for (int i = 0; i < n; ++i) {
         if (t[i].S > left) continue;
         const int64_t tiles = (int64_t)((h->p.nx + t[i].pw - 1) / t[i].pw) * ((h->p.ny + t[i].ph - 1) / t[i].ph);
-        float cost = t[i].first + (float)((tiles + 255) / 256 - 1) * t[i].more;
-        if (h->closure) cost *= t[i].S == 1 ? std::min(0.6f + 0.4f * tail, 1.35f) : std::min(tail, 2.2f);
+        const float wait = t[i].S == 1 ? std::min(0.6f + 0.4f * tail, 1.35f) : std::min(tail, 2.2f);
+        float cost = t[i].first + (float)((tiles + 255) / 256 - 1) * t[i].more * wait;
         if (conv) cost *= t[i].conv * conv_all;
         const int halo = h->closure ? 6 * t[i].S : 0;
         const float moved = state * (1.f + (float)((t[i].pw + halo) * (t[i].ph + halo)) / (float)(t[i].pw * t[i].ph));
