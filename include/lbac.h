@@ -199,6 +199,9 @@ int lbac_set_graph_chunk(lbac_ctx* h, int32_t chunk);
  * without the network and marks the patches of nodes whose result it can
  * change; those are then recomputed with the network, several steps at a
  * time in LDS, from the launch's input, which the step leaves in place.
+ * That is for thin bands: on grids of 2^19 nodes and more, while the last look
+ * (this call, lbac_set_state, or a launch) marked over three sixteenths of the grid,
+ * launches take one step of patches over the whole grid instead.
  * One-step launches run the block-variant step kernel (which records the
  * band), a scan that lists the band nodes and a pass that adds the correction
  * at those nodes.  Both give the same results bit for bit.  Needs device

@@ -197,6 +197,7 @@ StepArgs lbac_host::make_args(const lbac_ctx* h, int src, int32_t k) {
         a.cl_flags = h->cl_flags;
         a.cl_list = h->cl_list;
         a.cl_count = h->cl_count;
+        a.cl_seen = h->cl_seen;
     }
     return a;
 }
@@ -439,36 +440,57 @@ float default_strips(const lbac_ctx* h, bool three, int& variant, int& bx, int& 
     return h->closure ? best + 17.f + 9.f * std::sqrt(mnodes) : best;
 }
 
+// Whether the closure's band is wide: the last look at it, or two-pass launch,
+// marked more than three sixteenths of a grid on which that matters.  Two-pass
+// launches are for thin bands: they compute a patch they mark again, with two
+// to three times the band nodes of one step.  One-step patches over the whole
+// grid, a single pass whose network takes no node twice, are the faster from
+// about there on (the closure's 4096^2, us per step: a disk, 1% marked, 119 in
+// two passes, 382 in patches, 293 in one-step strips; rows of drops, all
+// marked, a third of the nodes in the band, 1969, 696 and 1579; every node in
+// the band 3251, 1174 and 3387; three steps with the network inside the strips
+// had taken 1156 and 2293 at the last two).  Below 2^19 nodes only a caller
+// chooses two passes, and gains by them at any band (512^2, every node in it: 82
+// us per step, with the network inside the strips 445).
+constexpr int64_t kLookNodes = int64_t(1) << 19;
+constexpr int kLookSteps = 256;  // a wide band is looked at again after so many steps (0.3 ms at 4096^2)
+bool look_grid(const lbac_ctx* h) {
+    return h->p.model == LBAC_MODEL_IMPROVED && (int64_t)h->p.nx * h->p.ny >= kLookNodes;
+}
+bool wide_band(const lbac_ctx* h) {
+    return h->closure && look_grid(h) && (!h->shape_set || launch_steps_of(h) > 1) &&
+           16 * (int64_t)__atomic_load_n(h->cl_seen, __ATOMIC_RELAXED) > 3 * (int64_t)h->p.nx * h->p.ny;
+}
+
 // The next launch of a run with `left` steps to go: the shape that was set,
 // or, where nobody set one, the faster of the patch kernels and the strip
 // kernels (made once per context: the estimates take as long as a launch's own
-// host work).  Results do not depend on the choice (16-bit storage takes one
-// step per launch here, as its rounding depends on the steps of a launch).
+// host work); patches of one step where the closure's band is wide.  Results
+// do not depend on the choice (16-bit storage takes one step per launch here,
+// as its rounding depends on the steps of a launch).
 Launch plan_launch(lbac_ctx* h, int64_t left) {
-    if (h->shape_set) {
+    const bool wide = wide_band(h);
+    if (h->shape_set && !wide) {
         const int S = launch_steps_of(h);
         return {false, {}, S > 1 && left >= S ? S : 1, h->variant, h->bx, h->strip_h};
     }
-    Launch& l = h->plans[std::min<int64_t>(left, kPlanSteps)];
+    Launch& l = h->plans[wide ? 0 : std::min<int64_t>(left, kPlanSteps)];
     if (l.S == 0) {
-        // (the closure at theta = 0: every node that is not clipped exactly is in
-        // the band, so the two-pass launches recompute the whole grid: 298 us per
-        // step at 2048^2, 162 with one-step launches)
-        const bool three =
-            h->p.precision == LBAC_F32 && stepS_allowed(h) && left >= 3 && !(h->closure && h->cl_theta == 0.f);
+        const bool three = !wide && h->p.precision == LBAC_F32 && stepS_allowed(h) && left >= 3;
         l.patch = false;
         l.S = three ? 3 : 1;
         const float strips = default_strips(h, three, l.variant, l.bx, l.strip_h);
         // (the closure with the conventional model: one-step launches only)
         if (!h->closure || h->p.model == LBAC_MODEL_IMPROVED) {
-            const PatchPlan p = plan_patch(h, left);
-            if (p.shape >= 0 && p.us < strips) {
+            const PatchPlan p = plan_patch(h, wide ? 1 : left);
+            if (p.shape >= 0 && (wide || p.us < strips)) {
                 l.patch = true;
                 l.p = p;
                 l.S = p.S;
             }
         }
     }
+    if (h->shape_set) return l;
     h->variant = l.variant;
     h->bx = l.bx;
     h->strip_h = l.strip_h;
@@ -485,12 +507,26 @@ void launch_set_time(const lbac_ctx* h, int64_t t) {
                        time_period(h->p), t);
 }
 
+// Looks at the closure's band: marks the patches of pop[src] as three steps of
+// the strips do (into the other buffer, which the next launch overwrites), for
+// *cl_seen.
+hipError_t look(lbac_ctx* h, int src) {
+    int variant, bx;
+    StepArgs a = make_args(h, src, 0);
+    default_strips(h, true, variant, bx, a.strip_h);
+    h->cl_since = 0;
+    return launch_look(h, a, bx);
+}
+hipError_t look_again(lbac_ctx* h, int src) {
+    return wide_band(h) && h->cl_since >= kLookSteps ? look(h, src) : hipSuccess;
+}
+
 // Queues `n` steps from pop[src], several per launch where the plan allows and
 // single steps for the rest, and the advance of the step counter.  The
 // counter (and the table of time factors with it) moves after every
 // kTimeFactors steps at the latest.  *flips gets the number of launches
-// (buffer swaps).
-hipError_t launch_steps(lbac_ctx* h, int src, int64_t n, int64_t* flips) {
+// (buffer swaps).  look: look at a wide band again when it is time.
+hipError_t launch_steps(lbac_ctx* h, int src, int64_t n, int64_t* flips, bool look) {
     int64_t f = 0;
     hipError_t e = hipSuccess;
     int32_t k = 0;  // steps queued since the counter moved
@@ -503,8 +539,10 @@ hipError_t launch_steps(lbac_ctx* h, int src, int64_t n, int64_t* flips) {
     for (int64_t left = n; left > 0 && e == hipSuccess;) {
         const Launch l = plan_launch(h, left);
         if (k + l.S > kTimeFactors) e = advance();
+        if (look && k == 0 && e == hipSuccess) e = look_again(h, src ^ (int)(f & 1));
         if (e == hipSuccess) e = do_launch(h, l, src ^ (int)(f & 1), k);
         k += l.S;
+        h->cl_since += l.S;
         left -= l.S;
         ++f;
     }
@@ -663,6 +701,8 @@ int lbac_host::create(const lbac_params* p, const double* phi0, bool phi0_on_dev
         h->host5 = nullptr;
         return bail(LBAC_ENOMEM);
     }
+    h->cl_seen = reinterpret_cast<uint32_t*>(h->host5 + 7);
+    *h->cl_seen = 0;
     if (hipMemcpyAsync(h->vtab, tab.data(), tab.size() * sizeof(double), hipMemcpyHostToDevice, h->stream) !=
             hipSuccess ||
         hipMemcpyAsync(h->vtabf, tabf.data(), tabf.size() * sizeof(float), hipMemcpyHostToDevice, h->stream) !=
@@ -694,14 +734,15 @@ void lbac_host::destroy(lbac_ctx* h) {
 namespace {
 
 int capture_graph(lbac_ctx* h, int parity) {
-    if (h->gexec[parity] && h->gexec_chunk[parity] == h->graph_chunk) return LBAC_OK;
+    const bool wide = wide_band(h);
+    if (h->gexec[parity] && h->gexec_chunk[parity] == h->graph_chunk && h->gexec_wide[parity] == wide) return LBAC_OK;
     if (h->gexec[parity]) {
         (void)hipGraphExecDestroy(h->gexec[parity]);
         h->gexec[parity] = nullptr;
     }
     HIPCHK(h, hipStreamBeginCapture(h->stream, hipStreamCaptureModeThreadLocal));
     int64_t flips = 0;
-    hipError_t e = launch_steps(h, parity, h->graph_chunk, &flips);
+    hipError_t e = launch_steps(h, parity, h->graph_chunk, &flips, false);
     hipGraph_t g = nullptr;
     hipError_t e2 = hipStreamEndCapture(h->stream, &g);
     if (e != hipSuccess || e2 != hipSuccess) {
@@ -714,6 +755,7 @@ int capture_graph(lbac_ctx* h, int parity) {
     if (e != hipSuccess) return fail(h, LBAC_EDEVICE, std::string("graph instantiate: ") + hipGetErrorString(e));
     h->gexec[parity] = ge;
     h->gexec_chunk[parity] = h->graph_chunk;
+    h->gexec_wide[parity] = wide;
     h->gexec_flips[parity] = (int)(flips & 1);
     return LBAC_OK;
 }
@@ -772,7 +814,9 @@ int lbac_step(lbac_ctx* h, int64_t n) {
         while (n - done >= h->graph_chunk) {
             int rc = capture_graph(h, h->cur);
             if (rc != LBAC_OK) return rc;
+            HIPCHK(h, look_again(h, h->cur));
             HIPCHK(h, hipGraphLaunch(h->gexec[h->cur], h->stream));
+            h->cl_since += h->graph_chunk;
             done += h->graph_chunk;
             h->t += h->graph_chunk;
             h->cur ^= h->gexec_flips[h->cur];  // parity of the chunk's launches
@@ -781,7 +825,7 @@ int lbac_step(lbac_ctx* h, int64_t n) {
     const int64_t r = n - done;
     if (r > 0) {
         int64_t flips = 0;
-        HIPCHK(h, launch_steps(h, h->cur, r, &flips));
+        HIPCHK(h, launch_steps(h, h->cur, r, &flips, true));
         h->cur ^= (int)(flips & 1);
         h->t += r;
     }
@@ -897,6 +941,7 @@ int lbac_set_state(lbac_ctx* h, const void* buf, size_t bytes) {
     if (phib) HIPCHK(h, hipMemcpyAsync(h->phis[h->cur], d + h->nplanes * plane, phib, hipMemcpyHostToDevice, h->stream));
     launch_set_time(h, t);
     HIPCHK(h, hipGetLastError());
+    if (h->closure && look_grid(h)) HIPCHK(h, look(h, h->cur));
     HIPCHK(h, hipStreamSynchronize(h->stream));
     h->t = t;
     return LBAC_OK;
@@ -1070,10 +1115,13 @@ int lbac_set_closure(lbac_ctx* h, const float* params, float theta) {
     hipLaunchKernelGGL(closure_pack_kernel, dim3((64 * 64 + 255) / 256), dim3(256), 0, h->stream, h->cl_param, h->cl_w,
                        h->cl_b);
     HIPCHK(h, hipGetLastError());
-    HIPCHK(h, hipStreamSynchronize(h->stream));
     h->closure = true;
     h->cl_theta = theta;
     drop_plans(h);
+    hipError_t e = look_grid(h) ? look(h, h->cur) : hipSuccess;
+    if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
+    if (e != hipSuccess) h->closure = false;
+    HIPCHK(h, e);
     return LBAC_OK;
 }
 
@@ -1128,7 +1176,7 @@ int lbac_bytes_per_node(lbac_ctx* h, double* bytes) {
 
 int lbac_steps_per_launch(lbac_ctx* h, int32_t* steps) {
     if (!h || !steps) return LBAC_EINVAL;
-    *steps = plan_launch(h, INT32_MAX).S;
+    *steps = h->shape_set ? launch_steps_of(h) : plan_launch(h, INT32_MAX).S;
     return LBAC_OK;
 }
 

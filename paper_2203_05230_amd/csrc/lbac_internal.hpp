@@ -76,11 +76,13 @@ struct lbac_ctx {
     // what lbac_get_launch gives while none is set: the shape at creation, or
     // the fastest that can be set when lbac_autotune found the plan faster still
     int unset_variant = LBAC_KERNEL_BLOCK, unset_bx = 256, unset_strip_h = 64;
-    lbac_host::Launch plans[lbac_host::kPlanSteps + 1];  // with i steps to go, or more than kPlanSteps; S = 0: not made yet
+    // with i steps to go, or more than kPlanSteps (0: any, a wide band); S = 0: not made yet
+    lbac_host::Launch plans[lbac_host::kPlanSteps + 1];
     int graph_chunk = 0;
     hipGraphExec_t gexec[2] = {nullptr, nullptr};
     int gexec_chunk[2] = {0, 0};
     int gexec_flips[2] = {0, 0};  // parity of the launches in each graph
+    bool gexec_wide[2] = {false, false};  // made for a wide band
     bool in_batch = false;   // owned by a batch: lbac_free refuses it
     bool failed = false;     // its batch's run timed out: the state is undefined
     // learned closure (FP32 plain storage only)
@@ -94,6 +96,8 @@ struct lbac_ctx {
     uint32_t* cl_count = nullptr; // entries in cl_list
     uint8_t* cl_flags = nullptr;  // marks of the two-pass launches, a byte per patch, zero between launches
     int32_t cl_words = 0;         // mask words per row
+    uint32_t* cl_seen = nullptr;  // pinned (the last word of host5): nodes of the patches last marked
+    int cl_since = 0;             // steps since a look at a wide band
     std::string err;
 };
 
@@ -111,6 +115,7 @@ hipError_t launch_patch(const lbac_ctx* h, int src, int32_t k, const PatchPlan& 
 // The closure's two-pass launches (strips, then the marked patches with the network).
 hipError_t launch_split(const lbac_ctx* h, const lbac::StepArgs& a, int S);
 hipError_t launch_stepS_band(int S, lbac::StepArgs a, int bx, hipStream_t s);  // the strips, marking
+hipError_t launch_look(const lbac_ctx* h, lbac::StepArgs a, int bx);            // three steps' strips, marking, for *cl_seen
 size_t mark_count(int nx, int ny);                                             // marks at most
 
 int create(const lbac_params* p, const double* phi0, bool phi0_on_device, lbac_ctx** out);

@@ -89,6 +89,7 @@ struct StepArgs {
     int32_t cl_npx;
     const int32_t* cl_list; // closure: the marked patches
     uint32_t* cl_count;     // entries in cl_list
+    uint32_t* cl_seen;      // closure: nodes of the marked patches, in host memory (see closure_seen)
     int32_t cl_words;       // words per row of cl_mask
 };
 
@@ -1621,6 +1622,15 @@ stepS_kernel_lds(StepArgs a) {
     if (BAND && blockIdx.x == 0 && threadIdx.x == 0) a.cl_count[0] = 0;  // (the patch list starts empty)
     stepS_tile_lds<MODEL, S, ST, false, BAND>(a, x0, min(a.tile_w, a.nx - x0), a.tile_w, ys, min(a.strip_h, a.ny - ys), 0,
                                  (syi & 1) != 0, stepS_lds);
+}
+
+// Tells the host how many nodes the marked patches have (it reads the word
+// whenever it plans a launch, without waiting: any recent value will do).
+__device__ __forceinline__ void closure_seen(const StepArgs& a, uint32_t patches, uint32_t nodes_per_patch) {
+    __hip_atomic_store(a.cl_seen, patches * nodes_per_patch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+static __global__ void closure_seen_kernel(StepArgs a, uint32_t nodes_per_patch) {
+    closure_seen(a, a.cl_count[0], nodes_per_patch);
 }
 
 // The marked patches as a list (in any order: each is recomputed by itself),

@@ -254,6 +254,7 @@ __global__ __launch_bounds__(NT) void patch_list_kernel(StepArgs a) {
     __shared__ PatchLds<float, S, PW, PH, true> lds;
     patch_network<NT>(a, lds);
     const int n = (int)a.cl_count[0];
+    if (blockIdx.x == 0 && threadIdx.x == 0) closure_seen(a, (uint32_t)n, PW * PH);
     for (int i = blockIdx.x; i < n; i += gridDim.x) {
         const int tile = a.cl_list[i];
         patch_steps<float, ST_PLAIN, MODEL_IMPROVED, S, PW, PH, NT, true, true>(a, (tile % a.cl_npx) * PW, (tile / a.cl_npx) * PH,
@@ -416,14 +417,23 @@ hipError_t go_cl(int shape, const StepArgs& a, hipStream_t s) {
 // inside, at two wavefronts per SIMD.
 constexpr int kMarkBlocks = 512;
 
+// The strips and the list of the marked patches (a: completed for the patches).
 template <int S>
-hipError_t go_split(const lbac_ctx* h, StepArgs a, int bx) {
+hipError_t go_marks(const lbac_ctx* h, StepArgs& a, int bx) {
     a.cl_npx = (a.nx + kMarkW - 1) / kMarkW;
     const int np = a.cl_npx * ((a.ny + kMarkH<S> - 1) / kMarkH<S>);
-    hipError_t e = lbac_host::launch_stepS_band(S, a, bx, h->stream);
+    const hipError_t e = lbac_host::launch_stepS_band(S, a, bx, h->stream);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(closure_list_kernel, dim3((np + 2047) / 2048), dim3(256), 0, h->stream, a.cl_flags, np,
                        const_cast<int32_t*>(a.cl_list), a.cl_count);
+    return hipGetLastError();
+}
+
+template <int S>
+hipError_t go_split(const lbac_ctx* h, StepArgs a, int bx) {
+    const hipError_t e = go_marks<S>(h, a, bx);
+    if (e != hipSuccess) return e;
+    const int np = a.cl_npx * ((a.ny + kMarkH<S> - 1) / kMarkH<S>);
     hipLaunchKernelGGL((patch_list_kernel<S, kMarkW, kMarkH<S>, 512>), dim3(std::min(np, kMarkBlocks)), dim3(512), 0,
                        h->stream, a);
     return hipGetLastError();
@@ -496,6 +506,13 @@ hipError_t lbac_host::launch_patch(const lbac_ctx* h, int src, int32_t k, const 
 
 hipError_t lbac_host::launch_split(const lbac_ctx* h, const StepArgs& a, int S) {
     return S == 3 ? go_split<3>(h, a, h->bx) : go_split<2>(h, a, h->bx);
+}
+
+hipError_t lbac_host::launch_look(const lbac_ctx* h, StepArgs a, int bx) {
+    const hipError_t e = go_marks<3>(h, a, bx);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(closure_seen_kernel, dim3(1), dim3(1), 0, h->stream, a, (uint32_t)(kMarkW * kMarkH<3>));
+    return hipGetLastError();
 }
 
 size_t lbac_host::mark_count(int nx, int ny) {

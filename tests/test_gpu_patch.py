@@ -182,13 +182,68 @@ def test_fp64_default_launches_on_large_grids(model):
 @pytest.mark.parametrize("launch", [None, (224, 40, 4), (96, 8, 3)])
 def test_two_pass_closure_at_small_theta(theta, launch):
     """The band test of the marking strips at thetas near the rounding of phi:
-    a disk whose tails pass through them, on a grid that takes two-pass
-    launches by default."""
+    a disk whose tails pass through them (and whose inside does, but for what
+    rounds to 1), small enough for two-pass launches on its grid."""
     say("case: two-pass closure, theta", theta, launch)
-    a, b = sims(1501, 1203, "f32")
-    for s in (a, b):
+    nx, ny = 1501, 1203
+    case = dict(nx=nx, ny=ny, eps=0.8, tau=0.7, vel="vortex", U=0.03, period_T=37.0, precision="f32")
+    phi0 = W.circle(nx, 0.8, R_frac=0.12, yc_frac=0.5, ny=ny)
+    a, b = out = [lbac.Simulation(case, phi0) for _ in range(2)]
+    for s in out:
         s.set_closure(driver.init_weights(5, out_scale=0.05), theta)
     if launch:
         a.set_launch(*launch)
+    b.set_launch(64, 8, 0)
     assert a.steps_per_launch() == (3 if launch is None else launch[2] - 1)
     check(a, b, (3, 7))
+
+
+def drops(nx, ny):
+    y, x = np.mgrid[0:ny, 0:nx]
+    return 0.5 + 0.5 * np.tanh(10.0 * np.sin(2 * np.pi * x / 64.0) * np.sin(2 * np.pi * y / 64.0))
+
+
+@pytest.mark.parametrize("launch", [None, (224, 40, 4), (160, 8, 3)])
+def test_closure_with_a_wide_band(launch):
+    """Where most of a large grid is in the band, launches that would take two
+    passes take patches of one step instead, from the first one on, and two
+    passes again once the band is thin; the launches in graphs follow.  All of
+    it the same bits as one-step strips."""
+    say("case: closure, wide band", launch)
+    nx, ny = 1501, 1203
+    case = dict(nx=nx, ny=ny, eps=0.8, tau=0.7, vel="vortex", U=0.03, period_T=37.0, precision="f32")
+    thin = W.circle(nx, 0.8, R_frac=0.3, yc_frac=0.5, ny=ny)
+    out = []
+    for shape in (launch, (64, 8, 0)):
+        s = lbac.Simulation(case, drops(nx, ny))
+        s.set_closure(driver.init_weights(5, out_scale=0.05), 0.02)
+        if shape:
+            s.set_launch(*shape)
+        out.append(s)
+    a, b = out
+    if launch is None:
+        assert a.steps_per_launch() == 1
+    t = lbac.Simulation(case, thin)
+    state = t.get_state()
+    t.close()
+    for graph in (0, 60):
+        a.set_graph_chunk(graph)
+        for n in (7, 300, 5):  # past a look at the band
+            a.step(n)
+            b.step(n)
+            assert np.array_equal(a.phi(), b.phi()), (graph, n)
+        for s in out:
+            s.set_state(state)
+        if launch is None:
+            assert a.steps_per_launch() == 3
+        for n in (7, 60):
+            a.step(n)
+            b.step(n)
+            assert np.array_equal(a.phi(), b.phi()), (graph, n)
+        wide = lbac.Simulation(case, drops(nx, ny))
+        blob = wide.get_state()
+        wide.close()
+        for s in out:
+            s.set_state(blob)
+    a.close()
+    b.close()
