@@ -156,7 +156,8 @@ int lbac_set_state(lbac_ctx* h, const void* buf, size_t bytes);
  * columns (any multiple of 32 in that range, and 240), the block being the
  * bx + 4 S grown columns rounded up to whole wavefronts, and their strips
  * strip_h rounded to the nearest whole period of the march (4 rows at S = 2,
- * 6 at S = 3, at least one); a step count
+ * 6 at S = 3, at least one), or to the next above where that spares a strip
+ * that would not run beside the others; a step count
  * that is not a multiple of S ends with one-step launches (bx 256 where bx
  * is not 64, 128 or 256).  With the closure and the conventional model every
  * step is a one-step launch.  strip_h: rows each tile marches (>= 1).

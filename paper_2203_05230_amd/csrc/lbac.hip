@@ -321,14 +321,33 @@ int launch_steps_of(const lbac_ctx* h) {
     return h->variant == LBAC_KERNEL_FUSED2 ? 2 : (h->variant == LBAC_KERNEL_FUSED3 ? 3 : 1);
 }
 
-// One S-step launch with tiles of bx columns, in strips of whole periods of the
-// kernel's march, which runs whole periods (the multiple nearest to the height
-// asked for).
+// What a row of a strip takes in a launch of `tiles` S-step tiles (us): up to
+// three run on a CU at once, 768 in all; a started round counts half.
+float stepS_row(int64_t tiles) {
+    const int64_t rounds = (tiles + 767) / 768;
+    return tiles <= 256 ? 0.35f : (tiles <= 512 ? 0.455f : (tiles <= 768 ? 0.65f
+           : 0.31f * ((float)tiles / 768.f + (float)rounds)));
+}
+
+// Rows of the strips when `rows` are asked for: the kernel marches whole
+// periods of Q rows, so the nearest multiple (at least one); but the multiple
+// above where the one below would add a strip that it does not (200 rows in
+// one strip become 198 and 2) and the added tiles find no room beside the
+// others.  Three steps on 128-column tiles, us per step with the nearest and
+// with these: 2048^2 in strips of 128 53 and 47, 8192^2 in strips of 512 457
+// and 361; where all run at once the shorter strips are the faster.
+int stepS_height(int nx, int ny, int bx, int rows, int Q) {
+    const int h = std::max(Q, (rows + Q / 2) / Q * Q), high = h + Q;
+    auto strips = [&](int r) { return (ny + r - 1) / r; };
+    auto us = [&](int r) { return stepS_row((int64_t)((nx + bx - 1) / bx) * strips(r)) * (float)(r + 14); };
+    return h < rows && strips(high) == strips(rows) && us(high) < us(h) ? high : h;
+}
+
+// One S-step launch with tiles of bx columns.
 template <int MODEL, int S, int ST, bool BAND = false>
 hipError_t launch_stepS_m(StepArgs a, int bx, hipStream_t s) {
     using L = TileSRows<S>;
-    constexpr int Q = L::kPeriod;
-    a.strip_h = std::max(Q, (a.strip_h + Q / 2) / Q * Q);
+    a.strip_h = stepS_height(a.nx, a.ny, bx, a.strip_h, L::kPeriod);
     a.nby = (a.ny + a.strip_h - 1) / a.strip_h;
     a.n_xcd = kXcds;
     a.tile_w = bx;
@@ -410,10 +429,7 @@ float default_strips(const lbac_ctx* h, bool three, int& variant, int& bx, int& 
         const int64_t nbx = (nx + bx - 1) / bx;
         float best = 1e30f;
         for (int sh : {42, 36, 48, 30, 54, 24, 60, 18, 12}) {
-            const int64_t tiles = nbx * ((ny + sh - 1) / sh), rounds = (tiles + 767) / 768;
-            const float row = tiles <= 256 ? 0.35f : (tiles <= 512 ? 0.455f : (tiles <= 768 ? 0.65f
-                              : 0.31f * ((float)tiles / 768.f + (float)rounds)));
-            const float us = std::max(row * (float)(sh + 14), 5.04f * mnodes);
+            const float us = std::max(stepS_row(nbx * ((ny + sh - 1) / sh)) * (float)(sh + 14), 5.04f * mnodes);
             if (us < best) {
                 best = us;
                 strip_h = std::min(sh, ny);
@@ -1016,7 +1032,12 @@ int lbac_autotune(lbac_ctx* h, int32_t steps, double* us_per_step) {
         const int S = var == LBAC_KERNEL_FUSED2 ? 2 : (var == LBAC_KERNEL_FUSED3 ? 3 : 1);
         if (bx > 64 && bx / 2 >= h->p.nx) continue;
         if (S == 1 ? !one_step_bx(bx) : !stepS_bx(bx)) continue;
+        int last = 0;
         for (int sh : hs) {
+            // (heights that come to the same launch are timed once)
+            const int run = S == 1 ? sh : stepS_height(h->p.nx, h->p.ny, bx, sh, S == 2 ? TileSRows<2>::kPeriod : TileSRows<3>::kPeriod);
+            if (run == last) continue;
+            last = run;
             h->variant = var;
             h->bx = bx;
             h->strip_h = std::min(sh, h->p.ny);

@@ -128,6 +128,23 @@ def test_checkpoint_resume_in_the_middle(gpu_lib, variant):
     assert np.array_equal(a.phi(), b.phi())
 
 
+@pytest.mark.parametrize("launch,n", [((128, 128, 4), 2047), ((128, 512, 4), 4097), ((64, 50, 3), 1001)])
+def test_heights_that_round_to_another_strip_count(gpu_lib, launch, n):
+    """Strip heights whose nearest whole period would add a strip the next one
+    above does not (17 strips of 126 rows against 16 of 132), on grids whose
+    tiles do not all run at once; 50 rows, 20 strips of 52, stay the nearest."""
+    case = {**W.single_vortex_case(n, eps=1.0, U=0.04, period_T=200.0), "precision": "f32"}
+    phi0 = W.circle(n, 1.0)
+    a, b = [gpu_lib.Simulation(case, phi0) for _ in range(2)]
+    a.set_launch(*launch)
+    b.set_launch(256, 64, 0)
+    for s in (a, b):
+        s.step(7)
+    assert np.array_equal(a.phi(), b.phi())
+    a.close()
+    b.close()
+
+
 def test_needs_fp32_collision(gpu_lib):
     case = W.single_vortex_case(32)
     sim = gpu_lib.Simulation({**case, "precision": "f64"}, W.circle(32, 1.0))
