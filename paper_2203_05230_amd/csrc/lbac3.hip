@@ -416,6 +416,14 @@ __global__ void sum_parts_kernel(const double* __restrict__ part, int nparts, do
 // ---------------------------------------------------------------------------
 // host side
 
+namespace {
+
+struct Shape3 {
+    int tx, ty, mode, sz, zm;  // tile, variant, strip, tile order
+};
+
+}  // namespace
+
 struct lbac3_ctx {
     lbac3_params p{};
     int device = 0;
@@ -442,7 +450,8 @@ struct lbac3_ctx {
     int tile_y = 16;
     int mode = 0;        // 0 keep, 1 re-pull, 2 prefetch (see step3_kernel)
     int z_major = 0;     // tile order: 0 x fastest, 1 strip fastest
-    bool shape_set = false;  // by lbac3_set_launch or lbac3_autotune; else launches follow the grid's size
+    bool shape_set = false;  // by lbac3_set_launch or lbac3_autotune; else launches follow the grid's size:
+    Shape3 by_size{};
     std::string err;
 };
 
@@ -556,47 +565,52 @@ bool tile_ok(int precision, int tile_x, int tile_y) {
     return false;
 }
 
-struct Shape3 {
-    int tx, ty, mode, sz, zm;  // tile, variant, strip, tile order
-};
-
 // The shape of a step when none has been set, by the grid's size.  A workgroup
 // marches its strip plane by plane, so a step takes at least the time of one
-// strip: its planes and two more, each kAlone and kWave more per wavefront (its
-// own and its rim's) of the workgroups that share a compute unit.  And it
-// takes the time of its traffic, kNode per node a workgroup pulls, a row of
-// its tile counting kEdge nodes more (partial lines), a tile a row and a strip
-// kEnd planes more.  Of the tiles and strips of 1 to 64 planes the one with
-// the least of the larger of the two is taken: few planes where the grid is
-// too small to fill the device, wide tiles and long strips where it is large.
-// The constants are fitted to steps of sixteen grids of 24 x 31 x 24 to 256^3
-// in every shape; the choice is within 14% of the best shape there in FP32
-// (24% in FP64), 5% on average.  Tiles of 1024 columns keep the next plane's
-// loads in flight, as FP64 does; the others keep more workgroups resident
-// instead.
-// us per step, with the shape before (32 x 16 tiles, strips of 32 planes) and
-// with this one: FP32 24 x 31 x 89 101 and 10, 64^3 125 and 19, 128^3 145 and
-// 79, 200^3 468 and 360, 256^3 674 and 541; FP64 64^3 169 and 29, 128^3 265 and
-// 149.
+// strip: its planes and two more, each `alone` and `wave` more per wavefront
+// (its own and its rim's) of the workgroups that share a compute unit.  And it
+// takes the time of its traffic, `node` per node a workgroup pulls, a row of
+// its tile counting `edge` nodes more (partial lines), a tile a row and a strip
+// `end` planes more.  Of the tiles, of strips of 1 to 64 planes and of the
+// variants that keep the pulled values and that prefetch the next plane's
+// (whose planes take longer with many workgroups to a unit, and whose traffic
+// less), the one with the least of the larger of the two is taken (their sum in
+// the ninth power, as the two meet): few planes where the grid is too small to
+// fill the device, wide tiles and long strips where it is large.  The constants
+// are fitted to steps of 62 grids of 16^3 to 320^3, uneven ones among them, in
+// every shape; the choice is within 17% of the best shape there, 4% on average,
+// and nowhere slower than 32 x 16 tiles in strips of 32 planes.
+// us per step, with those, with the variant bound to the tile (the earlier fit,
+// to sixteen grids) and with this one: FP32 64^3 124, 18.7 and 15.2, 160^3 183,
+// 200 and 156, 240^3 624, 634 and 543, 288^3 990, 1027 and 897; FP64 32^3 161,
+// 16.3 and 11.8, 128^3 266, 148 and 152, 200^3 854, 737 and 707.
 Shape3 auto_shape3(const lbac3_params& p) {
     const bool f64 = p.precision == LBAC_F64;
-    const double kAlone = f64 ? 0.0 : 2.1, kWave = f64 ? 0.45 : 0.14;
-    const double kNode = f64 ? 30e-6 : 21e-6, kEdge = f64 ? 30.0 : 26.0, kEnd = f64 ? 1.1 : 0.74;
+    struct Cost {
+        double alone, wave, node;
+    };
+    const Cost keep = f64 ? Cost{0.33, 0.36, 34.3e-6} : Cost{1.47, 0.16, 17.4e-6};
+    const Cost prefetch = f64 ? Cost{0.68, 0.36, 30.3e-6} : Cost{1.34, 0.20, 16.4e-6};
+    const double edge = f64 ? 26.0 : 50.0, end = f64 ? 1.0 : 0.92;
     const int strips[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64};
     Shape3 best{};
     double best_t = -1.0;
     for (const auto& sh : kShapes) {
         const int tx = sh[0], ty = sh[1];
-        if (!tile_ok(p.precision, tx, ty) || (f64 && (tx * ty != 512 || tx == 128))) continue;
+        if (!tile_ok(p.precision, tx, ty)) continue;
         const int waves = tx * ty / 64 + (2 * (tx + 2) + 2 * ty + 63) / 64;
-        for (int sz : strips) {
-            if (sz > p.nz) continue;
-            const int64_t n = (int64_t)((p.nx + tx - 1) / tx) * ((p.ny + ty - 1) / ty) * ((p.nz + sz - 1) / sz);
-            const double t = std::max((sz + 2) * (kAlone + kWave * (double)((n + 255) / 256) * waves),
-                                      kNode * n * (sz + kEnd) * (ty + 1) * (tx + kEdge));
-            if (best_t < 0.0 || t < best_t) {
-                best_t = t;
-                best = Shape3{tx, ty, f64 || tx * ty == 1024 ? 2 : 0, sz, 0};
+        for (int mode : {0, 2}) {
+            const Cost& c = mode == 0 ? keep : prefetch;
+            for (int sz : strips) {
+                if (sz > p.nz) continue;
+                const int64_t n = (int64_t)((p.nx + tx - 1) / tx) * ((p.ny + ty - 1) / ty) * ((p.nz + sz - 1) / sz);
+                const double strip = (sz + 2) * (c.alone + c.wave * (double)((n + 255) / 256) * waves);
+                const double traffic = c.node * n * (sz + end) * (ty + 1) * (tx + edge);
+                const double t = std::max(strip, traffic) * std::pow(1.0 + std::pow(std::min(strip, traffic) / std::max(strip, traffic), 9.0), 1.0 / 9.0);
+                if (best_t < 0.0 || t < best_t) {
+                    best_t = t;
+                    best = Shape3{tx, ty, mode, sz, 0};
+                }
             }
         }
     }
@@ -604,7 +618,7 @@ Shape3 auto_shape3(const lbac3_params& p) {
 }
 
 Shape3 shape3(const lbac3_ctx* h) {
-    return h->shape_set ? Shape3{h->tile_x, h->tile_y, h->mode, h->strip_z, h->z_major} : auto_shape3(h->p);
+    return h->shape_set ? Shape3{h->tile_x, h->tile_y, h->mode, h->strip_z, h->z_major} : h->by_size;
 }
 
 lbac3::Args3 make_args3(const lbac3_ctx* h, int src, int32_t k, const Shape3& sh) {
@@ -762,6 +776,7 @@ int lbac3_init(const lbac3_params* p, const double* phi0, lbac3_ctx** out) {
         }
     lbac3_ctx* h = new lbac3_ctx();
     h->p = *p;
+    h->by_size = auto_shape3(*p);
     auto bail = [&](int code, const std::string& msg) {
         g_init_error = msg;
         release3(h);
@@ -920,7 +935,7 @@ int lbac3_autotune(lbac3_ctx* h, int32_t steps, double* us_per_step) {
     for (int k = 1; k <= 16; ++k) strips.push_back((h->p.nz + k - 1) / k);
     std::sort(strips.begin(), strips.end());
     strips.erase(std::unique(strips.begin(), strips.end()), strips.end());
-    std::vector<Shape3> shapes{auto_shape3(h->p)};
+    std::vector<Shape3> shapes{h->by_size};
     for (const auto& sh : kShapes)
         for (int rp = 0; rp < 3; ++rp)
             for (int sz : strips)
