@@ -146,6 +146,20 @@ bool build_items(const std::vector<Geometry>& geo, const std::vector<int>& nby, 
     return true;
 }
 
+// Wavefronts of a row of an instance (its tiles' together).
+double row_waves(int nx) {
+    double w = 0.0;
+    for (const auto& t : column_tiles(nx)) w += (t.second + 4 * kBatchS + 63) / 64;
+    return w;
+}
+
+// Passes of every instance in a run, in full ones (a one-step pass is about 0.6 of one).
+std::vector<double> run_passes(const int64_t* nsteps, int count) {
+    std::vector<double> p(count);
+    for (int k = 0; k < count; ++k) p[k] = (double)(nsteps[k] / kBatchS) + 0.6 * (double)(nsteps[k] % kBatchS);
+    return p;
+}
+
 // Strips of every instance for a run: strip_h rows each, or fewer where the
 // run is short of workgroups.
 //
@@ -166,47 +180,58 @@ bool build_items(const std::vector<Geometry>& geo, const std::vector<int>& nby, 
 // 64 instances of 128^2 to 512^2, strips of 72 rows asked for: 20.3 ms as
 // asked, 12.5 cut like this.  A lone 512^2 with strips of 40, 512 steps: 10.5,
 // 5.2.  256 instances, which fill the device: 10.2 either way.
-std::vector<int> choose_strips(const std::vector<Geometry>& geo, int strip_h, const int64_t* nsteps, int cus) {
+//
+// current: the strips of the run before, chosen for the same strip_h, or null;
+// they are kept while they are about as good, since other ones cost the host a
+// new item list (0.3 ms for 2000 items).
+std::vector<int> choose_strips(const std::vector<Geometry>& geo, const std::vector<double>& waves, int strip_h,
+                               const std::vector<double>& passes, int cus, const std::vector<int>* current) {
     constexpr int Q = TileSRows<kBatchS>::kPeriod, kLow = 2 * Q;  // (rows of the shortest strips cut here)
     constexpr double kRow = 1.05, kBusy = 0.66;                  // us
     const int count = (int)geo.size();
     std::vector<int> uniform(count), best, nby(count);
-    std::vector<double> passes(count), waves(count, 0.0);
     double longest = 0.0;
     int top = 0;  // no strip is taller than the tallest instance
     for (int k = 0; k < count; ++k) {
         top = std::max(top, geo[k].ny);
         uniform[k] = nearest_strips(geo[k].ny, strip_h);
-        // (a one-step pass is about 0.6 of a full one)
-        passes[k] = (double)(nsteps[k] / kBatchS) + 0.6 * (double)(nsteps[k] % kBatchS);
         longest = std::max(longest, passes[k]);
-        for (const auto& t : column_tiles(geo[k].nx)) waves[k] += (t.second + 4 * kBatchS + 63) / 64;
     }
     top = std::min(top, strip_h);
-    double best_t = 0.0;
-    for (int h = kLow; h < top + Q; h += std::max(Q, h / 16 / Q * Q)) {
-        const double limit = longest * (h + 14);
+    // the run's estimated time with nby strips, or a negative number where a launch would have too many slots
+    auto estimate = [&](const std::vector<int>& nby) {
         double chain = 0.0, work = 0.0, slots = 0.0;
         for (int k = 0; k < count; ++k) {
-            const int ny = geo[k].ny;
-            nby[k] = uniform[k];
-            if (passes[k] > 0.0) {
-                const int hk = std::max(kLow, (int)std::min(limit / passes[k] - 14.0, 1e6) / Q * Q);
-                if (hk < strip_h) nby[k] = std::max(nby[k], std::min((ny + hk - 1) / hk, ny / kBatchMinStrip));
-            }
-            const double rows = ((double)ny / nby[k] + Q - 1) / Q * Q;  // about the tallest strip's
+            const double rows = ((double)geo[k].ny / nby[k] + Q - 1) / Q * Q;  // about the tallest strip's
             chain = std::max(chain, passes[k] * (rows + 14.0));
-            work += passes[k] * waves[k] / 4 * (ny + 20.0 * nby[k]);
+            work += passes[k] * waves[k] / 4 * (geo[k].ny + 20.0 * nby[k]);
             slots += passes[k] * nby[k] * waves[k];
         }
         const double c = chain * kRow, w = work * kBusy / cus;
-        const double t = std::max(c, w) + 0.4 * std::min(c, w);
-        if (slots <= (double)kBatchFineSlots && (best.empty() || t < best_t)) {
+        return slots <= (double)kBatchFineSlots ? std::max(c, w) + 0.4 * std::min(c, w) : -1.0;
+    };
+    double best_t = 0.0;
+    for (int h = kLow; h < top + Q; h += std::max(Q, h / 16 / Q * Q)) {
+        const double limit = longest * (h + 14);
+        for (int k = 0; k < count; ++k) {
+            nby[k] = uniform[k];
+            if (passes[k] > 0.0) {
+                const int hk = std::max(kLow, (int)std::min(limit / passes[k] - 14.0, 1e6) / Q * Q);
+                if (hk < strip_h) nby[k] = std::max(nby[k], std::min((geo[k].ny + hk - 1) / hk, geo[k].ny / kBatchMinStrip));
+            }
+        }
+        const double t = estimate(nby);
+        if (t >= 0.0 && (best.empty() || t < best_t)) {
             best = nby;
             best_t = t;
         }
     }
-    return best.empty() ? uniform : best;
+    if (best.empty()) return uniform;
+    if (current) {
+        const double t = estimate(*current);
+        if (t >= 0.0 && t <= 1.03 * best_t) return *current;
+    }
+    return best;
 }
 
 // Classes of the instances (see batch_kernel): instances dealt largest work
@@ -305,9 +330,18 @@ struct lbac_batch {
     bool failed = false;  // a run timed out: the state is undefined until the instances are set again
     // schedule
     int cus = 1;
+    std::vector<Geometry> geo;
+    std::vector<double> waves;  // row_waves of each instance
+    // what the last run's strips were chosen for: the passes in proportion to the
+    // most (the choice depends on no more, but for the limit of slots, and takes
+    // the host 0.1 ms for 1000 instances) and the height asked for
+    std::vector<double> chosen_share;
+    int chosen_h = 0;
+    std::vector<int> chosen;
     std::vector<int> strips;  // of each instance, as the item list was built
     std::vector<ItemH> items;
     int nitems = 0;
+    bool items_sent = false;     // d_items holds the list
     int64_t nslots[2] = {0, 0};  // slots of the two launches of the current run
     BatchInst* d_inst = nullptr;
     BatchItem* d_items = nullptr;
@@ -404,6 +438,7 @@ int ensure_tables(lbac_batch* b, const int64_t nent[2], const int64_t ncoarse[2]
         b->d_items = nullptr;
         b->d_done = nullptr;
         b->cap_items = 0;
+        b->items_sent = false;
         const int ci = std::max(b->nitems, 1);
         BHIP(b, hipMalloc(&b->d_items, sizeof(BatchItem) * ci));
         BHIP(b, hipMalloc(&b->d_done, sizeof(int32_t) * ci));
@@ -515,14 +550,25 @@ int run(lbac_batch* b, const int64_t* nsteps, bool dry, float* ms_out) {
     for (int k = 0; k < count; ++k)
         if (nsteps[k] < 0 || nsteps[k] > (int64_t)INT32_MAX) return bfail(b, LBAC_EINVAL, "step count out of range");
     if (b->strip_h < kBatchMinStrip) return bfail(b, LBAC_EINVAL, "strip height too small");
-    std::vector<Geometry> geo(count);
-    for (int k = 0; k < count; ++k) geo[k] = {b->inst[k]->p.nx, b->inst[k]->p.ny};
-    std::vector<int> strips = choose_strips(geo, b->strip_h, nsteps, b->cus);
-    if (b->strips != strips) {
+    const std::vector<Geometry>& geo = b->geo;
+    const std::vector<double> passes = run_passes(nsteps, count);
+    const double most = *std::max_element(passes.begin(), passes.end());
+    std::vector<double> share(passes);
+    for (double& v : share) v = most > 0.0 ? v / most : 0.0;
+    double slots = 0.0;
+    for (int k = 0; k < count && b->chosen_h > 0; ++k) slots += passes[k] * b->chosen[k] * b->waves[k];
+    if (b->chosen_h != b->strip_h || share != b->chosen_share || slots > (double)kBatchFineSlots) {
+        b->chosen = choose_strips(geo, b->waves, b->strip_h, passes, b->cus,
+                                  b->chosen_h == b->strip_h ? &b->chosen : nullptr);
+        b->chosen_share = std::move(share);
+        b->chosen_h = b->strip_h;
+    }
+    if (b->strips != b->chosen) {
         b->strips.clear();
-        if (!build_items(geo, strips, b->items)) return bfail(b, LBAC_EINVAL, "item dependency list too long");
+        if (!build_items(geo, b->chosen, b->items)) return bfail(b, LBAC_EINVAL, "item dependency list too long");
         b->nitems = (int)b->items.size();
-        b->strips = std::move(strips);
+        b->items_sent = false;
+        b->strips = b->chosen;
     }
     std::vector<int64_t> pf(count), pr(count);
     for (int k = 0; k < count; ++k) {
@@ -543,8 +589,8 @@ int run(lbac_batch* b, const int64_t* nsteps, bool dry, float* ms_out) {
     }
     int rc = ensure_tables(b, nent, ncoarse);
     if (rc != LBAC_OK) return rc;
-    std::vector<BatchItem> di(b->nitems);
-    for (int i = 0; i < b->nitems; ++i) {
+    std::vector<BatchItem> di(b->items_sent ? 0 : b->nitems);
+    for (int i = 0; i < (int)di.size(); ++i) {
         const ItemH& it = b->items[i];
         BatchItem& d = di[i];
         d.inst = it.inst;
@@ -585,7 +631,8 @@ int run(lbac_batch* b, const int64_t* nsteps, bool dry, float* ms_out) {
     BHIP(b, hipMemcpyAsync(b->d_nent, b->h_nent, 2 * sizeof(int32_t), hipMemcpyHostToDevice, b->stream));
     BHIP(b, hipMemcpyAsync(b->d_first, sl[0].first_item.data(), sizeof(int32_t) * (count + 1), hipMemcpyHostToDevice,
                            b->stream));
-    BHIP(b, hipMemcpyAsync(b->d_items, di.data(), sizeof(BatchItem) * b->nitems, hipMemcpyHostToDevice, b->stream));
+    if (!b->items_sent)
+        BHIP(b, hipMemcpyAsync(b->d_items, di.data(), sizeof(BatchItem) * b->nitems, hipMemcpyHostToDevice, b->stream));
     for (int L = 0; L < 2; ++L) {
         if (nent[L] > 0)
             BHIP(b, hipMemcpyAsync(b->d_entry[L], sl[L].entry.data(), sizeof(int32_t) * sl[L].entry.size(),
@@ -609,6 +656,7 @@ int run(lbac_batch* b, const int64_t* nsteps, bool dry, float* ms_out) {
     if (ms_out) BHIP(b, hipEventRecord(e1, b->stream));
     BHIP(b, hipMemcpyAsync(b->h_ctl, b->d_ctl, sizeof(BatchCtl), hipMemcpyDeviceToHost, b->stream));
     BHIP(b, hipStreamSynchronize(b->stream));  // host vectors above must outlive the copies
+    b->items_sent = true;
     if (ms_out) {
         BHIP(b, hipEventElapsedTime(ms_out, e0, e1));
         (void)hipEventDestroy(e0);
@@ -660,6 +708,8 @@ int lbac_batch_init(const lbac_params* params, const double* const* phi0, int32_
     }
     b->inst.assign(count, nullptr);
     for (int k = 0; k < count; ++k) {
+        b->geo.push_back({params[k].nx, params[k].ny});
+        b->waves.push_back(row_waves(params[k].nx));
         lbac_params p = params[k];
         p.stream = b->stream;
         lbac_ctx* c = nullptr;
