@@ -338,6 +338,14 @@ int lbac_batch_schedule_check(const int32_t* nx, const int32_t* ny, const int64_
                               int32_t strip_h, int32_t workers, int32_t protocol, uint64_t seed, int32_t* verdict,
                               int64_t* slots_run);
 
+/* The same check (protocol 0) of the schedule a run builds on a GPU of `cus`
+ * compute units: every instance in the strips lbac_batch_run cuts it into for
+ * these step counts (see lbac_batch_set_shape), which differ between
+ * instances, where lbac_batch_schedule_check cuts all at strip_h. */
+int lbac_batch_schedule_check_run(const int32_t* nx, const int32_t* ny, const int64_t* nsteps, int32_t count,
+                                  int32_t strip_h, int32_t cus, int32_t workers, uint64_t seed, int32_t* verdict,
+                                  int64_t* slots_run);
+
 /* Text of a status code, and of the last failure of a context. */
 const char* lbac_strerror(int code);
 const char* lbac_last_error(lbac_ctx* h);

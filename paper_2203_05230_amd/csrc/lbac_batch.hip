@@ -839,23 +839,20 @@ int lbac_batch_set_timeout(lbac_batch* b, double seconds, int32_t test_stall) {
 
 const char* lbac_batch_last_error(lbac_batch* b) { return b ? b->err.c_str() : "no batch"; }
 
-int lbac_batch_schedule_check(const int32_t* nx, const int32_t* ny, const int64_t* nsteps, int32_t count,
-                              int32_t strip_h, int32_t workers, int32_t protocol, uint64_t seed, int32_t* verdict,
-                              int64_t* slots_run) {
-    if (!nx || !ny || !nsteps || !verdict || count < 1 || strip_h < kBatchMinStrip || workers < 1 || protocol < 0 ||
-        protocol > 2)
-        return LBAC_EINVAL;
-    std::vector<Geometry> geo(count);
+}  // extern "C"
+
+namespace {
+
+// The check of a schedule (see lbac_batch_schedule_check) with the given strips.
+int check_schedule(const std::vector<Geometry>& geo, const std::vector<int>& strips, const int64_t* nsteps, int32_t workers,
+                   int32_t protocol, uint64_t seed, int32_t* verdict, int64_t* slots_run) {
+    const int count = (int)geo.size();
     std::vector<int64_t> pf(count), pr(count);
     for (int k = 0; k < count; ++k) {
-        if (nx[k] < 1 || ny[k] < 1 || nsteps[k] < 0 || nsteps[k] > (int64_t)INT32_MAX) return LBAC_EINVAL;
-        geo[k] = {nx[k], ny[k]};
         pf[k] = nsteps[k] / kBatchS;
         pr[k] = nsteps[k] % kBatchS;
     }
     std::vector<ItemH> items;
-    std::vector<int> strips(count);
-    for (int k = 0; k < count; ++k) strips[k] = nearest_strips(ny[k], strip_h);
     if (!build_items(geo, strips, items)) return LBAC_EINVAL;
     const int n = (int)items.size();
     const std::vector<int> cls_of = assign_classes(geo, nsteps);
@@ -1023,6 +1020,44 @@ int lbac_batch_schedule_check(const int32_t* nx, const int32_t* ny, const int64_
     }
     if (slots_run) *slots_run = ran;
     return LBAC_OK;
+}
+
+bool check_geometry(const int32_t* nx, const int32_t* ny, const int64_t* nsteps, int32_t count, std::vector<Geometry>& geo) {
+    for (int k = 0; k < count; ++k) {
+        if (nx[k] < 1 || ny[k] < 1 || nsteps[k] < 0 || nsteps[k] > (int64_t)INT32_MAX) return false;
+        geo.push_back({nx[k], ny[k]});
+    }
+    return true;
+}
+
+}  // namespace
+
+extern "C" {
+
+int lbac_batch_schedule_check(const int32_t* nx, const int32_t* ny, const int64_t* nsteps, int32_t count,
+                              int32_t strip_h, int32_t workers, int32_t protocol, uint64_t seed, int32_t* verdict,
+                              int64_t* slots_run) {
+    if (!nx || !ny || !nsteps || !verdict || count < 1 || strip_h < kBatchMinStrip || workers < 1 || protocol < 0 ||
+        protocol > 2)
+        return LBAC_EINVAL;
+    std::vector<Geometry> geo;
+    if (!check_geometry(nx, ny, nsteps, count, geo)) return LBAC_EINVAL;
+    std::vector<int> strips;
+    for (const Geometry& g : geo) strips.push_back(nearest_strips(g.ny, strip_h));
+    return check_schedule(geo, strips, nsteps, workers, protocol, seed, verdict, slots_run);
+}
+
+int lbac_batch_schedule_check_run(const int32_t* nx, const int32_t* ny, const int64_t* nsteps, int32_t count,
+                                  int32_t strip_h, int32_t cus, int32_t workers, uint64_t seed, int32_t* verdict,
+                                  int64_t* slots_run) {
+    if (!nx || !ny || !nsteps || !verdict || count < 1 || strip_h < kBatchMinStrip || cus < 1 || workers < 1)
+        return LBAC_EINVAL;
+    std::vector<Geometry> geo;
+    if (!check_geometry(nx, ny, nsteps, count, geo)) return LBAC_EINVAL;
+    std::vector<double> waves;
+    for (const Geometry& g : geo) waves.push_back(row_waves(g.nx));
+    const std::vector<int> strips = choose_strips(geo, waves, strip_h, run_passes(nsteps, count), cus, nullptr);
+    return check_schedule(geo, strips, nsteps, workers, 0, seed, verdict, slots_run);
 }
 
 }  // extern "C"

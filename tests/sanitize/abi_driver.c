@@ -160,6 +160,19 @@ static void schedule(void) {
             EXPECT(verdict == 0);
             EXPECT(ran > 0);
         }
+    /* the strips a run takes */
+    for (int w = 0; w < 3; ++w) {
+        int32_t verdict = -1;
+        int64_t ran = -1;
+        int64_t uneven[COUNT];
+        memcpy(uneven, ns, sizeof(ns));
+        uneven[3 + w] = 60 + 30 * w;
+        EXPECT(lbac_batch_schedule_check_run(nx, ny, uneven, COUNT, 72, w == 0 ? 1 : 256, workers[w], 7u, &verdict, &ran) ==
+               LBAC_OK);
+        EXPECT(verdict == 0);
+        EXPECT(ran > 0);
+    }
+    EXPECT(lbac_batch_schedule_check_run(nx, ny, ns, COUNT, 72, 0, 3, 7u, NULL, NULL) == LBAC_EINVAL);
     /* the two protocols that exist to be caught */
     int32_t verdict = -1;
     const int32_t one_nx[1] = {64}, one_ny[1] = {64};

@@ -99,3 +99,38 @@ def test_check_detects_hazards_without_the_waits(shapes):
     for seed in range(5):
         assert lbac.batch_schedule_check(shapes, [30] * len(shapes), 16, 8, seed=seed, protocol=1)[0] == 2
         assert lbac.batch_schedule_check(shapes, [30] * len(shapes), 16, 8, seed=seed, protocol=0)[0] == 0
+
+
+@pytest.mark.parametrize("workers", [1, 3, 40, 700])
+@pytest.mark.parametrize("cus", [1, 32, 256])
+def test_the_strips_of_a_run(cus, workers):
+    """The strips a run takes: instances with many passes cut to strips of
+    about 12 rows, those with few as asked, cuts at multiples of the march's
+    period; ragged, low, narrow and idle instances among them."""
+    rng = np.random.default_rng(cus)
+    shapes = [(int(a), int(b)) for a, b in zip(rng.integers(3, 300, 10), rng.integers(3, 300, 10))]
+    shapes += [(1, 64), (64, 1), (5, 3), (225, 41), (496, 40), (512, 24), (128, 200), (33, 181), (40, 97), (64, 64)]
+    nsteps = [int(v) for v in rng.integers(0, 12, len(shapes))]
+    nsteps[-4:] = [90, 61, 32, 0]
+    for strip_h in (8, 13, 72, 300):
+        verdict, ran = lbac.batch_schedule_check(shapes, nsteps, strip_h, workers, seed=workers, cus=cus)
+        assert verdict == 0, (strip_h, verdict)
+        assert ran >= lbac.batch_schedule_check(shapes, nsteps, strip_h, workers, seed=workers)[1]
+
+
+def test_a_run_cuts_the_longest_finer():
+    """On 256 compute units a lone instance is cut finer than asked; with one
+    unit, which it fills, it is not; and beside an instance of many passes one
+    of few keeps its strips."""
+    def slots(shapes, nsteps, cus):
+        verdict, ran = lbac.batch_schedule_check(shapes, nsteps, 48, 16, seed=2, cus=cus)
+        assert verdict == 0
+        return ran
+
+    assert slots([(200, 192)], [30], 256) > 2 * slots([(200, 192)], [30], 1) == 2 * 4 * 10
+    long, short = (200, 192), (200, 192)
+    assert slots([long, short], [90, 3], 256) == slots([long], [90], 256) + 4
+    with pytest.raises(lbac.LbacError):
+        lbac.batch_schedule_check([(16, 16)], [3], 16, 1, cus=0)
+    with pytest.raises(lbac.LbacError):
+        lbac.batch_schedule_check([(16, 16)], [3], 4, 1, cus=8)
