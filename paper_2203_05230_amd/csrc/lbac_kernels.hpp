@@ -208,28 +208,6 @@ struct Store<float, ST_F16> : StoreShifted<__half> {};
 template <>
 struct Store<float, ST_BF16> : StoreShifted<__hip_bfloat16> {};
 
-// ---- per-node pieces of the scheme ------------------------------------------
-// psi of Eq. (13) with the clip of phi to [0, 1] described after it; the
-// conventional model (Eq. (1)) takes its normal from phi itself.
-template <typename R, int MODEL>
-__device__ __forceinline__ R normal_source(R phi, R eps, R delta) {
-    if (MODEL == MODEL_CONVENTIONAL) return phi;
-    R pc = phi < R(0) ? R(0) : (phi > R(1) ? R(1) : phi);
-    return eps * log((pc + delta) / (R(1) - pc + delta));
-}
-
-// Sharpening magnitude.  Improved model: (1 - tanh^2(psi/(2 eps)))/(4 eps)
-// at psi of Eq. (13), which equals a b / (eps (a + b)^2) with a = phi_c + delta,
-// b = 1 - phi_c + delta; that form has no cancellation in the bulk.
-// Conventional model: phi (1 - phi) / eps.
-template <typename R, int MODEL>
-__device__ __forceinline__ R sharpening(R phi, R eps, R delta) {
-    if (MODEL == MODEL_CONVENTIONAL) return phi * (R(1) - phi) / eps;
-    R pc = phi < R(0) ? R(0) : (phi > R(1) ? R(1) : phi);
-    R a = pc + delta, b = R(1) - pc + delta, s = R(1) + R(2) * delta;
-    return a * b / (eps * s * s);
-}
-
 // ---------------------------------------------------------------------------
 // Fast elementary functions for the FP32 path (hardware log2, reciprocal and
 // square root, about 1 ulp); the FP64 path keeps the correctly rounded ones.
@@ -430,13 +408,9 @@ __device__ __forceinline__ void bstore(double v, __amdgpu_buffer_rsrc_t r, uint3
     w.y = (unsigned int)(bits >> 32);
     __builtin_amdgcn_raw_buffer_store_b64(w, r, (int)off, 0, 0);
 }
-// 16-bit store; aux 2 is the non-temporal hint
 template <typename H>
-__device__ __forceinline__ void bstore16(H v, __amdgpu_buffer_rsrc_t r, uint32_t off, int aux) {
-    if (aux == 2)
-        __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(unsigned short, v), r, (int)off, 0, 2);
-    else
-        __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(unsigned short, v), r, (int)off, 0, 0);
+__device__ __forceinline__ void bstore16(H v, __amdgpu_buffer_rsrc_t r, uint32_t off) {
+    __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(unsigned short, v), r, (int)off, 0, 0);
 }
 
 template <typename R, int ST>
@@ -454,16 +428,6 @@ struct Io<R, ST_PLAIN> {
             d[q] = static_cast<char*>(a.dst) + (size_t)q * a.plane_stride * sizeof(R);
         }
     }
-    // In the mirrored frame (y -> -y) population q lives in the plane of its
-    // mirror image: 2 <-> 4, 5 <-> 8, 6 <-> 7.
-    __device__ __forceinline__ Io(const StepArgs& a, bool mirror) {
-#pragma unroll
-        for (int q = 0; q < 9; ++q) {
-            const int m = mirror ? mirror_q(q) : q;
-            s[q] = static_cast<const char*>(a.src) + (size_t)m * a.plane_stride * sizeof(R);
-            d[q] = static_cast<char*>(a.dst) + (size_t)m * a.plane_stride * sizeof(R);
-        }
-    }
     __device__ __forceinline__ void load(uint32_t off, R (&v)[9]) const {
         const uint32_t b = off * (uint32_t)sizeof(R);
 #pragma unroll
@@ -475,13 +439,6 @@ struct Io<R, ST_PLAIN> {
 #pragma unroll
         for (int q = 0; q < 9; ++q) bstore(v[q], plane_rsrc(d[q]), b);
     }
-    // the same, non-temporal (FP32 only): used where the L2 is better spent
-    // on rows that are read again
-    __device__ __forceinline__ void store_nt(bool on, uint32_t off, const float (&v)[9], float /*phi*/) const {
-        const uint32_t b = on ? off * 4u : kDropOffset;
-#pragma unroll
-        for (int q = 0; q < 9; ++q) bstore_nt(v[q], plane_rsrc(d[q]), b);
-    }
 };
 
 template <typename H>
@@ -489,16 +446,13 @@ struct IoShifted {
     static constexpr bool kShifted = true;
     const char* s[9];  // s[0]: phi* plane (FP32); s[1..8]: g planes (16-bit)
     char* d[9];
-    // mirror: the mirrored frame y -> -y, population q read from and written
-    // to the plane of its mirror image (the phi* plane is its own image)
-    __device__ __forceinline__ explicit IoShifted(const StepArgs& a, bool mirror = false) {
+    __device__ __forceinline__ explicit IoShifted(const StepArgs& a) {
         s[0] = reinterpret_cast<const char*>(a.src_phi);
         d[0] = reinterpret_cast<char*>(a.dst_phi);
 #pragma unroll
         for (int q = 1; q < 9; ++q) {
-            const int m = mirror ? mirror_q(q) : q;
-            s[q] = static_cast<const char*>(a.src) + (size_t)(m - 1) * a.plane_stride * sizeof(H);
-            d[q] = static_cast<char*>(a.dst) + (size_t)(m - 1) * a.plane_stride * sizeof(H);
+            s[q] = static_cast<const char*>(a.src) + (size_t)(q - 1) * a.plane_stride * sizeof(H);
+            d[q] = static_cast<char*>(a.dst) + (size_t)(q - 1) * a.plane_stride * sizeof(H);
         }
     }
     // v[0] = phi*, v[i] = w_i phi* + g_i (see StoreShifted)
@@ -513,15 +467,8 @@ struct IoShifted {
     __device__ __forceinline__ void store(bool on, uint32_t off, const float (&v)[9], float phi) const {
         const uint32_t b2 = on ? off * 2u : kDropOffset, b4 = on ? off * 4u : kDropOffset;
 #pragma unroll
-        for (int q = 1; q < 9; ++q) bstore16(f2h<H>(__builtin_fmaf(-wq<float>(q), phi, v[q])), plane_rsrc(d[q]), b2, 0);
+        for (int q = 1; q < 9; ++q) bstore16(f2h<H>(__builtin_fmaf(-wq<float>(q), phi, v[q])), plane_rsrc(d[q]), b2);
         bstore(phi, plane_rsrc(d[0]), b4);
-    }
-    // the same with the non-temporal hint
-    __device__ __forceinline__ void store_nt(bool on, uint32_t off, const float (&v)[9], float phi) const {
-        const uint32_t b2 = on ? off * 2u : kDropOffset, b4 = on ? off * 4u : kDropOffset;
-#pragma unroll
-        for (int q = 1; q < 9; ++q) bstore16(f2h<H>(__builtin_fmaf(-wq<float>(q), phi, v[q])), plane_rsrc(d[q]), b2, 2);
-        bstore_nt(phi, plane_rsrc(d[0]), b4);
     }
 };
 template <>
@@ -1057,16 +1004,13 @@ __device__ __forceinline__ void closure_mlp(const uint16_t* __restrict__ w, cons
     cyo = cy;
 }
 
-// The network's correction at a node, in the frame the node's populations
-// are held in (mirror: the y axis reversed), added to its post-collision
-// populations: Eq. (9)-(11) are linear in G, so adding c_s^2 c to G changes
-// f*_i by (1 - 1/(2 tau)) w_i (c_i . c) for i >= 1 and leaves their sum phi;
-// the rest population is re-formed as the remainder.  The pairs i,
-// opposite(i) change by exact negatives, and a mirrored node rounds exactly
-// like its mirror image.
-__device__ __forceinline__ void closure_correct(float (&f)[9], float phi, float kforce, float ccx, float ccy,
-                                                bool mirror) {
-    const float kx = kforce * ccx, ky = kforce * (mirror ? -ccy : ccy);
+// The network's correction at a node, added to its post-collision populations:
+// Eq. (9)-(11) are linear in G, so adding c_s^2 c to G changes f*_i by
+// (1 - 1/(2 tau)) w_i (c_i . c) for i >= 1 and leaves their sum phi; the rest
+// population is re-formed as the remainder.  The pairs i, opposite(i) change
+// by exact negatives.
+__device__ __forceinline__ void closure_correct(float (&f)[9], float phi, float kforce, float ccx, float ccy) {
+    const float kx = kforce * ccx, ky = kforce * ccy;
     const float ax = wq<float>(1) * kx, ay = wq<float>(1) * ky;
     const float dx5 = wq<float>(5) * kx, dy5 = wq<float>(5) * ky;
     f[1] += ax;
@@ -1577,7 +1521,6 @@ __device__ __forceinline__ void stepS_tile_lds(const StepArgs& a, int x0, int w,
             px[i] = q / kMarkW;
             dx = min(dx + step(q, a.nx, kMarkW), 4);
         }
-        const bool narrow = a.nx < 16;  // (then every patch column)
 #pragma unroll
         for (int k = 0; k < S; ++k) {
             const int reach = 2 * (S - 1 - k);
@@ -1598,7 +1541,6 @@ __device__ __forceinline__ void stepS_tile_lds(const StepArgs& a, int x0, int w,
                         row[px[0]] = 1;
                         row[px[1]] = 1;
                         row[px[2]] = 1;
-                        if (narrow) row[0] = 1;
                     }
                     y += step(q, a.ny, kMarkH<S>);
                 }
@@ -1942,7 +1884,7 @@ static __global__ __launch_bounds__(kClWaves * kWave) void closure_apply_kernel(
             float f[9];
 #pragma unroll
             for (int q = 1; q < 9; ++q) f[q] = dst[q * a.plane_stride + off];
-            closure_correct(f, phi, kforce, ccx, ccy, false);
+            closure_correct(f, phi, kforce, ccx, ccy);
             dst[off] = f[0];
 #pragma unroll
             for (int q = 1; q < 9; ++q) dst[q * a.plane_stride + off] = f[q];

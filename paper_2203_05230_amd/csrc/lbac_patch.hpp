@@ -216,7 +216,7 @@ __device__ __forceinline__ void patch_steps(const StepArgs& a, int x0, int y0, P
                 float f[9];
 #pragma unroll
                 for (int q = 1; q < 9; ++q) f[q] = lds.f[q - 1][n];
-                closure_correct(f, phi[i], kc.kforce, lds.cor[slot[i]][0], lds.cor[slot[i]][1], false);
+                closure_correct(f, phi[i], kc.kforce, lds.cor[slot[i]][0], lds.cor[slot[i]][1]);
                 if (k == S - 1) {
                     io.store(x0 + lx[i] < a.nx && y0 + ly[i] < a.ny, off[i], f, phi[i]);
                 } else {
