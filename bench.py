@@ -120,13 +120,18 @@ def run_form(lbac, torch, case, phi0, precision, steps, warmup, launch=None, aut
     if autotune:
         sim.autotune(12)
     launch = sim.get_launch()
+    # whether the tuner kept the launches of a context whose shape nobody sets
+    # (the patch kernels): they take other numbers of steps than the reported
+    # variant, which is then the fastest that could be set
+    default = autotune and sim.steps_per_launch() != {3: 2, 4: 3}.get(launch[2], 1)
     if warmup:
         sim.step(warmup)
     torch.cuda.synchronize()
     sim.close()
     # timed run from the initial field
     sim = lbac.Simulation(c, phi0, stream=stream.cuda_stream)
-    sim.set_launch(*launch)
+    if not default:
+        sim.set_launch(*launch)
     if graph:
         sim.set_graph_chunk(graph)
     m0 = sim.mass()
@@ -153,7 +158,8 @@ def run_form(lbac, torch, case, phi0, precision, steps, warmup, launch=None, aut
     assert sim.stream() == stream.cuda_stream
     # practical ceiling: the same bytes moved in the step's access pattern by a plain copy
     copy_us = sim.copy_ceiling(20)
-    out = dict(ms_total=ms, wall_s=wall, launch=list(launch), e1=e1, e2=e2, mass_drift=abs(m1 - m0) / m0,
+    out = dict(ms_total=ms, wall_s=wall, launch=list(launch), shape="default" if default else list(launch),
+               e1=e1, e2=e2, mass_drift=abs(m1 - m0) / m0,
                bytes_per_node=sim.bytes_per_node(), steps_per_launch=spl, t_end=sim.time(),
                copy_us=copy_us, launch_ms=launch_ms, full_launches=full_launches, mass=m1)
     if keep_phi:
@@ -366,7 +372,7 @@ def c2_leg(lbac, torch, W, n, steps):
         for prec in ("f32", "f32_f16store", "f32_bf16store"):
             r = run_form(lbac, torch, case, phi0, prec, steps, 64, autotune=True, graph=96, keep_phi=ref is not None)
             runs[prec] = dict(mlups=round(n * n * steps / (r["ms_total"] * 1e-3) / 1e6, 1), e2=r["e2"], e1=r["e1"],
-                              mass_drift=r["mass_drift"], launch=r["launch"])
+                              mass_drift=r["mass_drift"], launch=r["shape"])
             if ref is not None:
                 runs[prec]["rel_l2_vs_oracle"] = float(np.linalg.norm(r["phi"] - ref[0]) / np.linalg.norm(ref[0]))
                 runs[prec]["mass_vs_oracle"] = abs(r["mass"] - ref[1]) / ref[1]
@@ -379,14 +385,14 @@ def c2_leg(lbac, torch, W, n, steps):
 def c1_leg(lbac, torch, W, steps):
     """The 64^2 single vortex in FP64 (R = 9.6 at (32, 48), eps 1, tau 0.8, U
     0.02, period = `steps`), the parity configuration, over one period from
-    phi0: E1, E2 and mass drift at t = T, and MLUPS with the launch shape
-    autotuned and the steps replayed from captured HIP graphs of 100 steps
-    (4096 nodes per step: latency- and launch-bound)."""
+    phi0: E1, E2 and mass drift at t = T, and MLUPS with the launches autotuned
+    ("default": those of a context whose shape nobody sets) and the steps
+    replayed from captured HIP graphs of 100 steps (4096 nodes per step: latency- and launch-bound)."""
     case = W.single_vortex_case(64, eps=1.0, tau=0.8, U=0.02, period_T=float(steps))
     phi0 = W.circle(64, 1.0)
     r = run_form(lbac, torch, case, phi0, "f64", steps, 0, autotune=True, graph=100)
     return dict(grid=64, steps=steps, precision="f64", mlups=round(64 * 64 * steps / (r["ms_total"] * 1e-3) / 1e6, 1),
-                e2=r["e2"], e1=r["e1"], mass_drift=r["mass_drift"], launch=r["launch"])
+                e2=r["e2"], e1=r["e1"], mass_drift=r["mass_drift"], launch=r["shape"])
 
 
 def leg_3d(lbac, torch, W, n, steps, launch=None):
@@ -637,7 +643,7 @@ def main():
                                       / (r["ms_total"] / args.steps * 1e-3) / 1e9, 1),
                         bytes_per_node=r["bytes_per_node"], e2=r["e2"], e1=r["e1"], mass_drift=r["mass_drift"],
                         e2_vs_plain=r["e2"] / main_run["e2"] if main_run["e2"] > 0 else None,
-                        launch=r["launch"])
+                        launch=r["shape"])
     batched = None
     if args.batch > 0:
         print("bench: batched form, %d instances" % args.batch, file=sys.stderr, flush=True)
@@ -701,7 +707,8 @@ def main():
              {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
               "frac": round(achieved / HBM_PEAK_GBS, 4)}),
             traffic=None if traffic is None else round(traffic, 0),
-            kernel="stepS_kernel_lds<improved, %d, %d, FP32 storage>" % (main_run["launch"][0], spl),
+            kernel="patch kernels" if main_run["shape"] == "default" else
+                   "stepS_kernel_lds<improved, %d, FP32 storage> on %d-column tiles" % (spl, main_run["launch"][0]),
             steps_per_launch=spl, launch_ms=round(launch_ms, 4), launches_timed=main_run["full_launches"],
             valu={"instructions_per_launch": valu,
                   "issue_frac": None if valu_issue_frac is None else round(valu_issue_frac, 4),

@@ -163,8 +163,9 @@ int lbac_set_state(lbac_ctx* h, const void* buf, size_t bytes);
  * step is a one-step launch.  strip_h: rows each tile marches (>= 1).
  * Until a shape is set, or chosen by lbac_autotune, launches follow the
  * grid's size: patches of nodes advanced several steps in LDS where the grid
- * is too small to fill the GPU with strips, else strips; lbac_get_launch then
- * reports a one-step shape.
+ * is too small to fill the GPU with strips (in FP64, whose strips take one
+ * step a launch, on any grid that has steps to take together), else strips;
+ * lbac_get_launch then reports a one-step shape.
  * Results do not depend on the shape or variant (bitwise; the 16-bit
  * storage forms round once per launch, so there they depend on S only).
  * LBAC_EINVAL for unsupported values. */
@@ -179,8 +180,9 @@ int lbac_get_launch(lbac_ctx* h, int32_t* variant, int32_t* bx, int32_t* strip_h
 /* Times every supported launch shape (variant; bx; strip_h among the
  * multiples of 8 up to 256, 512 and ceil(ny / k) for k = 1..32) over `steps`
  * launches each (state is left unchanged), and what launches do with no shape
- * set, and keeps the fastest per step (where that is the latter,
- * lbac_get_launch then gives the fastest shape that can be set);
+ * set, and keeps the fastest per step (where that is the latter, this
+ * context keeps making those launches and lbac_get_launch gives the fastest
+ * shape that can be set; another context makes them as long as none is set);
  * *us_per_step (may be NULL) gets its time per step. */
 int lbac_autotune(lbac_ctx* h, int32_t steps, double* us_per_step);
 

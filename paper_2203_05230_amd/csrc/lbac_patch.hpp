@@ -1,4 +1,5 @@
-// The step on patches: the form for grids whose strips cannot fill the device.
+// The step on patches: the form for grids whose strips cannot fill the device,
+// and in FP64, which has no multi-step strips, for any grid.
 //
 // A strip-marching tile (lbac_kernels.hpp) works through its rows one after
 // another, about 1 us per row whatever the grid, so on a grid of a few hundred
@@ -10,7 +11,9 @@
 // node's rest population in its thread's register); the region a step updates
 // shrinks by RC on each side, and the last step stores the patch.  Neighbouring
 // patches compute the 2H rows and columns they share both; on an idle device
-// that costs nothing.
+// that costs nothing, and in FP64 less than moving the state at every step: 384
+// and 1470 us per step at 4096^2 and 8192^2, 322 and 1341 with the conventional
+// model, where the one-step strips take 564 and 2112 (543 and 1945).
 //
 // Every node helper, its order of operations and its rounding are those of
 // the strip kernels, so the results are the same bit for bit.
