@@ -40,7 +40,7 @@ constexpr int oW1 = 0, ob1 = oW1 + kH * kIn, oW2 = ob1 + kH, ob2 = oW2 + kH * kH
               ob3 = oW3 + kOut * kH, kNParam = ob3 + kOut;
 static_assert(kNParam == LBAC_MLP_NPARAM, "parameter count");
 constexpr float kGeluK = 0.7978845608028654f;  // sqrt(2/pi)
-constexpr int kNS = 16;                        // samples per block (one wavefront)
+constexpr int kNS = 16;                        // samples a workgroup takes at a time
 constexpr int kKin = 28;                       // inputs padded to whole K-steps of 4
 
 typedef float f32x4_t __attribute__((ext_vector_type(4)));

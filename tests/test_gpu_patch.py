@@ -46,9 +46,9 @@ def check(a, b, steps):
     b.close()
 
 
-# FP32 shapes by size: 8x8, 16x16, 24x24, 32x16, 52x20; FP64: 8x8, 16x16,
-# 20x20, 24x24, 52x20; sizes on the patches' edges, one off them, smaller than
-# a grown patch, and degenerate
+# FP32 patches from 8x8 to 48x16, FP64 from 4x4 to 24x16, 16-bit storage from
+# 12x12 to 60x28; sizes on the patches' edges, one off them, smaller than a grown
+# patch, and degenerate
 @pytest.mark.parametrize("nx,ny", [(1, 1), (1, 70), (33, 1), (5, 3), (31, 32), (64, 64), (129, 127), (200, 203), (256, 256),
                                    (303, 290), (384, 385), (512, 500), (1040, 1000)])
 @pytest.mark.parametrize("precision", ["f32", "f64", "f32_f16store", "f32_bf16store"])
@@ -66,7 +66,7 @@ def test_patches_equal_strips_conventional_model(precision):
         check(a, b, (3, 14))
 
 
-# closure shapes by size: 8x8, 14x14, 20x20, 52x20
+# closure patches from 8x8 to 52x20
 @pytest.mark.parametrize("nx,ny", [(9, 7), (96, 101), (200, 190), (400, 420), (1000, 700)])
 def test_patches_equal_strips_with_the_closure(nx, ny):
     say("case: patches with the closure", nx, ny)
@@ -135,8 +135,7 @@ def test_two_pass_closure_equals_one_step(nx, ny, launch):
     assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
 
 
-# FP64 patches of 4x4, 8x8, 12x8, 13x13, 16x16 and 20x20, and the closure's
-# of 8x8, 14x14, 16x16, 20x20 and 26x26, off the patches' edges
+# the smaller patches of FP64 and of the closure, off the patches' edges
 @pytest.mark.parametrize("precision,closure,nx,ny", [
     ("f64", False, 61, 63), ("f64", False, 101, 99), ("f64", False, 145, 151), ("f64", False, 199, 209),
     ("f64", False, 255, 253), ("f64", False, 301, 299), ("f32", True, 127, 121), ("f32", True, 201, 197),
