@@ -492,7 +492,7 @@ Launch plan_launch(lbac_ctx* h, int64_t left) {
     }
     Launch& l = h->plans[wide ? 0 : std::min<int64_t>(left, kPlanSteps)];
     if (l.S == 0) {
-        const bool three = !wide && h->p.precision == LBAC_F32 && stepS_allowed(h) && left >= 3;
+        const bool three = !wide && h->p.precision == LBAC_F32 && left >= 3 && (!h->closure || look_grid(h));
         l.patch = false;
         l.S = three ? 3 : 1;
         const float strips = default_strips(h, three, l.variant, l.bx, l.strip_h);

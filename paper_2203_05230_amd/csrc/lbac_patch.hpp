@@ -466,10 +466,10 @@ lbac_host::PatchPlan lbac_host::plan_patch(const lbac_ctx* h, int64_t left) {
     // The closure's patches share three nodes a step on each side, so they read
     // more than the state once it no longer stays in the cache (4096^2, one step
     // of 26 x 26: 382 us).  And where there are several to a CU they wait for the
-    // network of the last ones, the longer the wider the band is: its width goes with log(1 / theta), and from theta = 0.02 to 1e-4 two
-    // steps of 52 x 20 take 285 -> 520 us per step at 4096^2, 81 -> 189 at 2048^2,
-    // one of 26 x 26 382 -> 501 and 100 -> 160, the one-step strips 293 -> 297
-    // and 105 -> 107.
+    // network of the last ones, the longer the wider the band is: its width goes
+    // with log(1 / theta), and from theta = 0.02 to 1e-4 two steps of 52 x 20 take
+    // 285 -> 520 us per step at 4096^2 and 81 -> 189 at 2048^2, one of 26 x 26 382
+    // -> 501 and 100 -> 160, the one-step strips 293 -> 297 and 105 -> 107.
     const float tail = h->closure ? std::max(1.f, -0.256f * std::log(h->cl_theta + 1e-10f)) : 1.f;
     const bool conv = h->p.model == LBAC_MODEL_CONVENTIONAL;
     // FP64 without the logarithms: 9.9, 17.2 and 25 us for one step of 28 x 28 at 600^2, 768^2 and 1024^2, where the
@@ -478,6 +478,11 @@ lbac_host::PatchPlan lbac_host::plan_patch(const lbac_ctx* h, int64_t left) {
     for (int i = 0; i < n; ++i) {
         if (t[i].S > left) continue;
         const int64_t tiles = (int64_t)((h->p.nx + t[i].pw - 1) / t[i].pw) * ((h->p.ny + t[i].ph - 1) / t[i].ph);
+        // on long grids a few rows high the network runs on every image of a row a patch covers, while a strip
+        // marches no more rows than there are (all of 37197 x 1 in the band: 82 us per step with patches of 26 x 26,
+        // 38 with one-step strips)
+        const int64_t rows = (int64_t)((h->p.ny + t[i].ph - 1) / t[i].ph) * t[i].ph;
+        if (h->closure && tiles > 256 && rows > (t[i].S == 1 ? 4 : 2) * (int64_t)h->p.ny) continue;
         const float wait = t[i].S == 1 ? std::min(0.6f + 0.4f * tail, 1.35f) : std::min(tail, 2.2f);
         float cost = t[i].first + (float)((tiles + 255) / 256 - 1) * t[i].more * wait;
         if (conv) cost *= t[i].conv * conv_all;
