@@ -567,46 +567,56 @@ bool tile_ok(int precision, int tile_x, int tile_y) {
 
 // The shape of a step when none has been set, by the grid's size.  A workgroup
 // marches its strip plane by plane, so a step takes at least the time of one
-// strip: its planes and two more, each `alone` and `wave` more per wavefront
-// (its own and its rim's) of the workgroups that share a compute unit.  And it
-// takes the time of its traffic, `node` per node a workgroup pulls, a row of
-// its tile counting `edge` nodes more (partial lines), a tile a row and a strip
-// `end` planes more.  Of the tiles, of strips of 1 to 64 planes and of the
-// variants that keep the pulled values and that prefetch the next plane's
-// (whose planes take longer with many workgroups to a unit, and whose traffic
-// less), the one with the least of the larger of the two is taken (their sum in
-// the ninth power, as the two meet): few planes where the grid is too small to
-// fill the device, wide tiles and long strips where it is large.  The constants
-// are fitted to steps of 62 grids of 16^3 to 320^3, uneven ones among them, in
-// every shape; the choice is within 17% of the best shape there, 4% on average,
-// and nowhere slower than 32 x 16 tiles in strips of 32 planes.
-// us per step, with those, with the variant bound to the tile (the earlier fit,
-// to sixteen grids) and with this one: FP32 64^3 124, 18.7 and 15.2, 160^3 183,
-// 200 and 156, 240^3 624, 634 and 543, 288^3 990, 1027 and 897; FP64 32^3 161,
-// 16.3 and 11.8, 128^3 266, 148 and 152, 200^3 854, 737 and 707.
+// strip: its planes and `fill` more, each `alone` and `wave` more per wavefront
+// of the compute unit's workgroups (their own and their rims', in whole rounds
+// over its four SIMDs).  And it takes the time of its traffic: `node` per node,
+// a row of a tile counting `edge` nodes more (partial lines), a tile `rim` rows
+// and a strip `end` planes more, and `crowd` of it more for each further
+// workgroup of a unit.  Of the tiles, of strips of 1 to 64 planes and of the
+// variants that keep the pulled values and that prefetch the next plane's, the
+// one with the least is taken (the two add up where they meet, in the ninth
+// power): few planes where the grid is too small to fill the device, wide tiles
+// and long strips where it is large.
+// The constants are fitted to steps of 265 grids of 16 to 320 nodes a side,
+// most of them uneven, in every shape; the choice takes 2.9% (FP64 2.0%) more
+// than the best shape there on average, 24% (12%) at most, where an earlier fit
+// to sixteen grids took 7.0% (7.5%) and 35% (39%); against that one it is 3.8%
+// (5.1%) faster on average, and slower by more than 2% on a tenth of the grids.
+// us per step, with 32 x 16 tiles in strips of 32 planes, the earlier fit and
+// this one: FP32 64^3 118, 18.6 and 15.5, 160^3 183, 201 and 158, 240^3 636, 631
+// and 470, 288^3 1012, 1018 and 956; FP64 32^3 152, 16.4 and 12.1, 128^3 260, 150
+// and 150, 240^3 1267, 1105 and 986.
 Shape3 auto_shape3(const lbac3_params& p) {
     const bool f64 = p.precision == LBAC_F64;
     struct Cost {
         double alone, wave, node;
     };
-    const Cost keep = f64 ? Cost{0.33, 0.36, 34.3e-6} : Cost{1.47, 0.16, 17.4e-6};
-    const Cost prefetch = f64 ? Cost{0.68, 0.36, 30.3e-6} : Cost{1.34, 0.20, 16.4e-6};
-    const double edge = f64 ? 26.0 : 50.0, end = f64 ? 1.0 : 0.92;
+    const Cost keep = f64 ? Cost{0.68, 0.317, 48.1e-6} : Cost{1.34, 0.097, 33.7e-6};
+    const Cost prefetch = f64 ? Cost{0.74, 0.311, 46.7e-6} : Cost{0.99, 0.173, 30.5e-6};
+    const double edge = f64 ? 13.9 : 17.6, rim = f64 ? 2.59 : 0.31, end = f64 ? 0.21 : 0.32;
+    const double fill = f64 ? 2.59 : 2.25, crowd = f64 ? 0.007 : 0.013;
     const int strips[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64};
+    auto ninth = [](double x) {
+        const double x3 = x * x * x;
+        return x3 * x3 * x3;
+    };
     Shape3 best{};
     double best_t = -1.0;
     for (const auto& sh : kShapes) {
         const int tx = sh[0], ty = sh[1];
         if (!tile_ok(p.precision, tx, ty)) continue;
         const int waves = tx * ty / 64 + (2 * (tx + 2) + 2 * ty + 63) / 64;
-        for (int mode : {0, 2}) {
-            const Cost& c = mode == 0 ? keep : prefetch;
-            for (int sz : strips) {
-                if (sz > p.nz) continue;
-                const int64_t n = (int64_t)((p.nx + tx - 1) / tx) * ((p.ny + ty - 1) / ty) * ((p.nz + sz - 1) / sz);
-                const double strip = (sz + 2) * (c.alone + c.wave * (double)((n + 255) / 256) * waves);
-                const double traffic = c.node * n * (sz + end) * (ty + 1) * (tx + edge);
-                const double t = std::max(strip, traffic) * std::pow(1.0 + std::pow(std::min(strip, traffic) / std::max(strip, traffic), 9.0), 1.0 / 9.0);
+        const int nbx = (p.nx + tx - 1) / tx, nby = (p.ny + ty - 1) / ty;
+        const double rows = (p.nx + nbx * edge) * (p.ny + nby * rim);
+        for (int sz : strips) {
+            if (sz > p.nz) continue;
+            const int nbz = (p.nz + sz - 1) / sz;
+            const int64_t k = ((int64_t)nbx * nby * nbz + 255) / 256;  // workgroups of a compute unit
+            const double planes = rows * (p.nz + nbz * end) * (1.0 + crowd * (double)std::min<int64_t>(k - 1, 4));
+            const double rounds = 4.0 * (double)((k * waves + 3) / 4);
+            for (int mode : {0, 2}) {
+                const Cost& c = mode == 0 ? keep : prefetch;
+                const double t = ninth((sz + fill) * (c.alone + c.wave * rounds)) + ninth(c.node * planes);
                 if (best_t < 0.0 || t < best_t) {
                     best_t = t;
                     best = Shape3{tx, ty, mode, sz, 0};
